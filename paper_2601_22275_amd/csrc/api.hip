@@ -255,7 +255,7 @@ int r_update_any<bf16_t>(const bf16_t* aR, const float* cR, const bf16_t* k, con
   const bool two_tiles = cfg.flash_variant == 1 ||
                          (cfg.flash_variant == 2 && (v != nullptr ? dm.b > 128 : dm.d == 64));
   if (flash_supported(dm) && two_tiles)
-    e = launch_r_update_flash2(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, cfg.entropy_mode, st);
+    e = launch_r_update_flash2(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st);
   else if (flash_supported(dm))
     e = launch_r_update_flash(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, cfg.entropy_mode, cfg.fused_apply != 0, st);
   else

@@ -32,7 +32,7 @@ namespace {
 __device__ __forceinline__ uint32_t average_bf16x2(uint32_t a, uint32_t b);
 __device__ __forceinline__ uint4 average_bf16x8(uint4 a, uint4 b);
 
-template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int BIAS = 0>
+template <int D, bool OUT_K, bool OUT_V, bool ENT, bool SPLIT, int BIAS = 0>
 __global__ void __launch_bounds__(64 * NW) flash_kernel(FlashParams P) {
   using G = RowGeo<D>;
   constexpr int ROW_BYTES = G::ROW_BYTES;
@@ -43,7 +43,8 @@ __global__ void __launch_bounds__(64 * NW) flash_kernel(FlashParams P) {
   constexpr int RPI = G::RPI;                 // rows filled by one 64-lane global -> LDS load
   auto swz = [](int row) { return G::swz(row); };
   extern __shared__ __attribute__((aligned(16))) char smem[];  // [K|V][NSLOT][64 rows][2 D bytes] [key biases]
-  static_assert(BIAS == 0 || (!SPLIT && ENT == 0), "the biased modes are whole-range passes without entropy");
+  static_assert(!ENT || OUT_K, "c_L comes from the R K accumulators");
+  static_assert(BIAS == 0 || (!SPLIT && !ENT), "the biased modes are whole-range passes without entropy");
 
   // XCD-aware placement: hardware deals workgroups to the 8 XCDs round-robin, so give each
   // XCD one contiguous range of work items; the query blocks of one (head, frame) then share
@@ -190,12 +191,11 @@ __global__ void __launch_bounds__(64 * NW) flash_kernel(FlashParams P) {
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[qt][ct][r] = 0.f;
-  float msc[QT], ltil[QT], hsum[QT];
+  float msc[QT], ltil[QT];
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     msc[qt] = NEG_BIG;
     ltil[qt] = 0.f;
-    hsum[qt] = 0.f;
     // BIAS == 2: the reference of a row is given and never moves (every exponent is <= 0 by construction)
     if (BIAS == 2) msc[qt] = P.qb_scale * P.qbias[qrow0 + grow[qt] * rs];
   }
@@ -298,14 +298,13 @@ __global__ void __launch_bounds__(64 * NW) flash_kernel(FlashParams P) {
     for (int qt = 0; qt < QT; ++qt) {
       const float dl = msc[qt] - mpend[qt];  // log2 of the rescale factor: <= 0, and 0 when nothing moved
       alpha[qt] = __builtin_amdgcn_exp2f(dl);
-      if (ENT == 1) hsum[qt] = alpha[qt] * (hsum[qt] + dl * ltil[qt]);  // h <- a h + a log(a) l
       ltil[qt] *= alpha[qt];
       msc[qt] = mpend[qt];
     }
     logits(next_ktile, next_st, snext);
     accumulate(prev_ktile, prev_st, pbprev);
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) subtile_probs<ENT>(scur[qt], sc[qt], msc[qt], ltil[qt], hsum[qt], pbcur[qt]);
+    for (int qt = 0; qt < QT; ++qt) subtile_probs(scur[qt], sc[qt], msc[qt], ltil[qt], pbcur[qt]);
     add_key_bias(snext, next_sub);
     look_ahead(snext);
     // Keep this step's vector results in this step: without the pins below the compiler sinks
@@ -314,7 +313,6 @@ __global__ void __launch_bounds__(64 * NW) flash_kernel(FlashParams P) {
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
       asm volatile("" : "+v"(pbcur[qt][0]), "+v"(pbcur[qt][1]), "+v"(ltil[qt]), "+v"(mpend[qt]));
-      if (ENT == 1) asm volatile("" : "+v"(hsum[qt]));
     }
     if (moved_now) {
 #pragma unroll
@@ -387,29 +385,10 @@ __global__ void __launch_bounds__(64 * NW) flash_kernel(FlashParams P) {
     if (BIAS == 2 && qvalid[qt] && g == 0) P.cl[row] = lt;              // ... and their sum is an output
     if (!SPLIT) {
       if (P.lse != nullptr && qvalid[qt] && g == 0) P.lse[row] = LN2 * (msc[qt] + __log2f(lt));
-      if (ENT == 1) {
-        // App. B: H = log S - L / S; here in base-2 units, c_L = -H
-        float h = hsum[qt] + __shfl_xor(hsum[qt], 32);
-        float H2 = __log2f(lt) - h * inv;
-        if (qvalid[qt] && g == 0) P.cl[row] = -LN2 * H2;
-      }
-      if (ENT == 2) {
-        // sum_l R_l z_l = scale * aR . (sum_l R_l K_l): c_L = scale * (aR . alpha_L) - logsumexp
-        float dot = 0.f;
-        const bf16_t* qp = P.q + row * D;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            uint2 w = *reinterpret_cast<const uint2*>(qp + 32 * ct + 8 * c + 4 * g);
-            dot += __uint_as_float(w.x << 16) * oacc[qt][ct][4 * c + 0];
-            dot += __uint_as_float(w.x & 0xffff0000u) * oacc[qt][ct][4 * c + 1];
-            dot += __uint_as_float(w.y << 16) * oacc[qt][ct][4 * c + 2];
-            dot += __uint_as_float(w.y & 0xffff0000u) * oacc[qt][ct][4 * c + 3];
-          }
-        dot += __shfl_xor(dot, 32);
-        float mean_t = dot * inv * sc[qt];          // sum_l R_l (s_l sc), log2 units
-        float lse2 = msc[qt] + __log2f(lt);
+      if (ENT) {
+        // App. B's h = sum p t from the accumulators (see row_dot): c_L = h / l - log l = sc (aR . alpha_L) - lse
+        const float mean_t = row_dot<D>(qreg[qt], oacc[qt]) * inv * sc[qt];  // sum_l R_l (s_l sc), log2 units
+        const float lse2 = msc[qt] + __log2f(lt);
         if (qvalid[qt] && g == 0) P.cl[row] = LN2 * (mean_t - lse2);
       }
       // lane (q, g) holds channels 32 ct + 8 c + 4 g .. + 3 of query q: 8-byte pieces
@@ -507,7 +486,7 @@ __global__ void __launch_bounds__(128) merge_splits_kernel(const float* __restri
 
 constexpr int kMaxBiasedKeys = 8192 - BK;  // biased modes keep one float per key (+ one tile of padding) behind the tile slots: 32 KB
 
-template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int BIAS = 0>
+template <int D, bool OUT_K, bool OUT_V, bool ENT, bool SPLIT, int BIAS = 0>
 hipError_t launch_flash(const FlashParams& P, hipStream_t st) {
   constexpr int TILE_LDS = 2 * NSLOT * BK * D * 2;  // four K slots + four V slots: 128 KB at d = 128
   constexpr int MAX_LDS = TILE_LDS + (BIAS != 0 ? (kMaxBiasedKeys + BK) * 4 : 0);
@@ -586,17 +565,16 @@ hipError_t launch_r_update_flash(const bf16_t* aR, const float* cR, const bf16_t
   P.total_blocks = (int)total;
   P.blocks_per_xcd = (P.total_blocks + 7) / 8;
   P.row_scale = row_scale; P.cr_min = cr_min;
-  const bool ident = entropy_mode == VMONARCH_ENTROPY_IDENTITY;
   // alpha_L and c_L from one pass over K; y = R V from a second pass that recomputes the
   // logits.  (One wave cannot hold both accumulator sets; flash_kv.hip shares them between two.)
   auto run = [&](auto dc) -> hipError_t {
     constexpr int D = decltype(dc)::value;
-    hipError_t e = ident ? launch_flash<D, true, false, 2, false>(P, st) : launch_flash<D, true, false, 1, false>(P, st);
+    hipError_t e = launch_flash<D, true, false, true, false>(P, st);
     if (e != hipSuccess || v == nullptr) return e;
     P.outk = nullptr;
     P.cl = nullptr;
     P.lse = nullptr;
-    return launch_flash<D, false, true, 0, false>(P, st);
+    return launch_flash<D, false, true, false, false>(P, st);
   };
   return dm.d == 128 ? run(std::integral_constant<int, 128>{}) : run(std::integral_constant<int, 64>{});
 }
@@ -640,7 +618,7 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   const bool ff2 = two_tile && row_list == nullptr && flash2_query_block() == BQ;
   if (ns == 1) {
     if (ff2) return launch_first_frame_flash2(q, k, v, out, lse, nullptr, nullptr, dm, nrows, 1, P.keys_per_split, st);
-    return d128 ? launch_flash<128, false, true, 0, false>(P, st) : launch_flash<64, false, true, 0, false>(P, st);
+    return d128 ? launch_flash<128, false, true, false, false>(P, st) : launch_flash<64, false, true, false, false>(P, st);
   }
   const size_t rows = (size_t)ns * dm.BH * nrows;
   const size_t need = rows * dm.d * sizeof(float) + ((rows * sizeof(float) + 255) & ~(size_t)255);
@@ -648,7 +626,7 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   P.part_lse = (float*)scratch;
   P.part_o = (float*)((char*)scratch + ((rows * sizeof(float) + 255) & ~(size_t)255));
   hipError_t e = ff2 ? launch_first_frame_flash2(q, k, v, out, lse, P.part_o, P.part_lse, dm, nrows, ns, P.keys_per_split, st)
-                     : (d128 ? launch_flash<128, false, true, 0, true>(P, st) : launch_flash<64, false, true, 0, true>(P, st));
+                     : (d128 ? launch_flash<128, false, true, false, true>(P, st) : launch_flash<64, false, true, false, true>(P, st));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(merge_splits_kernel, dim3((unsigned)((long long)dm.BH * nrows)), dim3(dm.d), 0, st, P.part_o,
                      P.part_lse, out, lse, ns, (long long)dm.BH * nrows, nrows, dm.N, row_list, (int)dm.N);
@@ -686,16 +664,16 @@ hipError_t launch_l_update_flash(const bf16_t* q, const bf16_t* aL, const float*
   const bool d128 = dm.d == 128;
   if (y != nullptr) {
     P.q = q; P.k = aL; P.v = y; P.outv = out; P.kbias = cL;
-    return d128 ? launch_flash<128, false, true, 0, false, 1>(P, st) : launch_flash<64, false, true, 0, false, 1>(P, st);
+    return d128 ? launch_flash<128, false, true, false, false, 1>(P, st) : launch_flash<64, false, true, false, false, 1>(P, st);
   }
   if (lse_scratch == nullptr) return hipErrorInvalidValue;
   P.q = q; P.k = aL; P.outk = nullptr; P.lse = lse_scratch; P.kbias = cL;
-  hipError_t e = d128 ? launch_flash<128, true, false, 0, false, 1>(P, st) : launch_flash<64, true, false, 0, false, 1>(P, st);
+  hipError_t e = d128 ? launch_flash<128, true, false, false, false, 1>(P, st) : launch_flash<64, true, false, false, false, 1>(P, st);
   if (e != hipSuccess) return e;
   P.q = aL; P.k = q; P.outk = aR; P.cl = cR; P.lse = nullptr;
   P.kbias = lse_scratch;          // natural log, like c_L: the same scale -log2(e) applies
   P.qbias = cL; P.qb_scale = LOG2E;
-  return d128 ? launch_flash<128, true, false, 0, false, 2>(P, st) : launch_flash<64, true, false, 0, false, 2>(P, st);
+  return d128 ? launch_flash<128, true, false, false, false, 2>(P, st) : launch_flash<64, true, false, false, false, 2>(P, st);
 }
 
 // Attention-sink averaging (Sec. 4.4): all N queries of a head against its first frame's b keys,
@@ -718,7 +696,7 @@ hipError_t launch_sink_average_flash(const bf16_t* q, const bf16_t* k, const bf1
   P.row_scale = 1.0f / sqrtf((float)dm.d);
   P.cr_min = 0.f;
   P.blend = 1;
-  return dm.d == 128 ? launch_flash<128, false, true, 0, false>(P, st) : launch_flash<64, false, true, 0, false>(P, st);
+  return dm.d == 128 ? launch_flash<128, false, true, false, false>(P, st) : launch_flash<64, false, true, false, false>(P, st);
 }
 
 }  // namespace vm

@@ -111,16 +111,14 @@ __device__ __forceinline__ float subtile_max(const f32x16& s) {
 
 // Probabilities of the sub-tile relative to the reference max `msc` (log2 units):
 // t = s * sc - msc, p = 2^t.  `pb[0..1]` receive the two bf16 B operands (16 keys each) of
-// the O^T += X^T P^T products.  Running sums (Alg. 1's l and, when ENT == 1, h):
+// the O^T += X^T P^T products.  Running sum (Alg. 1's l):
 //   lt = sum of the bf16-ROUNDED p (v_dot2 against ones).  The accumulators are divided by
 //        this one, so that the output is an exact convex combination of the rows with
 //        slightly perturbed weights; dividing by the unrounded sum instead leaves a 2^-9
 //        relative error on rows dominated by one key.  It also serves as l in the
-//        log-sum-exp and in H = log l - h / l (error ~1e-3 in c_L, one VALU op per score saved);
-//   h  = sum p * t with the unrounded p.
-template <int ENT>
-__device__ __forceinline__ void subtile_probs(const f32x16& s, float sc, float msc, float& lt, float& h,
-                                              bf16x8 pb[2]) {
+//        log-sum-exp and in H = log l - h / l (error ~1e-3 in c_L, one VALU op per score saved).
+// Alg. 1's third sum, h = sum p t, is formed in the epilogue (row_dot).
+__device__ __forceinline__ void subtile_probs(const f32x16& s, float sc, float msc, float& lt, bf16x8 pb[2]) {
   typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
   bf16x2 ones2;
   ones2[0] = (__bf16)1.0f;
@@ -130,7 +128,6 @@ __device__ __forceinline__ void subtile_probs(const f32x16& s, float sc, float m
   for (int r = 0; r < 16; ++r) {
     float t = __builtin_fmaf(s[r], sc, -msc);
     p[r] = __builtin_amdgcn_exp2f(t);
-    if (ENT == 1) h = __builtin_fmaf(p[r], t, h);
   }
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
@@ -144,6 +141,36 @@ __device__ __forceinline__ void subtile_probs(const f32x16& s, float sc, float m
     }
     __builtin_memcpy(&pb[c], w, 16);
   }
+}
+
+// q . acc for the lane's query row: qreg the row as the B operand of the logit products (the lane holds 8-channel
+// blocks 2 ks + g), acc its R K accumulators (the lane holds channels 4 g .. + 3 of every block; exchanging half
+// blocks between lanes q and q + 32 lines the two up).  This is where Alg. 1's third statistic comes from: h = sum_l
+// p_l t_l is linear in the keys,
+//   sum_l p_l t_l = sc (aR . sum_l p_l K_l) - m sum_l p_l,
+// and the accumulators hold sum_l p_l K_l in fp32 with the very p (rounded to bf16) that l and the products carry,
+// so one dot product per row takes the place of a multiply-add per score (and of two unpacks per pair where h has to
+// carry the rounded p).
+template <int D>
+__device__ __forceinline__ float row_dot(const bf16x8 (&qreg)[D / 16], const f32x16 (&acc)[D / 32]) {
+  float dot = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) {
+    uint32_t w[4];
+    __builtin_memcpy(w, &qreg[ks], 16);
+    const auto lo = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {  // 8-channel block 2 ks + e
+      const f32x16& a = acc[(2 * ks + e) / 4];
+      const int c = (2 * ks + e) % 4;
+      dot = __builtin_fmaf(__uint_as_float(lo[e] << 16), a[4 * c + 0], dot);
+      dot = __builtin_fmaf(__uint_as_float(lo[e] & 0xffff0000u), a[4 * c + 1], dot);
+      dot = __builtin_fmaf(__uint_as_float(hi[e] << 16), a[4 * c + 2], dot);
+      dot = __builtin_fmaf(__uint_as_float(hi[e] & 0xffff0000u), a[4 * c + 3], dot);
+    }
+  }
+  return dot + __shfl_xor(dot, 32);
 }
 
 // One half (8 scores per lane, one B operand of 16 keys) of subtile_probs<1>: registers 8 c .. 8 c + 7 of `s`.
