@@ -241,8 +241,10 @@ template <>
 int r_update_any<float>(const float* aR, const float* cR, const float* k, const float* v, float* aL, float* cL,
                         float* y, float* lse, const Dims& dm, float row_scale, float cr_min, const Settings&,
                         hipStream_t st) {
-  hipError_t e = launch_r_update_generic<float>(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st);
-  return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "r_update (plain-ALU f32) launch");
+  hipError_t e = f32_mfma_supported(dm, {aR, k, v, aL, y})
+                     ? launch_r_update_f32(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st)
+                     : launch_r_update_generic<float>(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st);
+  return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "r_update (f32) launch");
 }
 template <>
 int r_update_any<bf16_t>(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL,
@@ -270,8 +272,10 @@ int l_update_any(const E* q, const E* aL, const float* cL, const E* y, E* aR, fl
 template <>
 int l_update_any<float>(const float* q, const float* aL, const float* cL, const float* y, float* aR, float* cR,
                         float* out, float* lse_scratch, const Dims& dm, float q_scale, hipStream_t st) {
-  hipError_t e = launch_l_update_generic<float>(q, aL, cL, y, aR, cR, out, lse_scratch, dm, q_scale, st);
-  return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "l_update (plain-ALU f32) launch");
+  hipError_t e = l_update_f32_supported(dm, {q, aL, y, aR, out})
+                     ? launch_l_update_f32(q, aL, cL, y, aR, cR, out, dm, q_scale, st)
+                     : launch_l_update_generic<float>(q, aL, cL, y, aR, cR, out, lse_scratch, dm, q_scale, st);
+  return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "l_update (f32) launch");
 }
 template <>
 int l_update_any<bf16_t>(const bf16_t* q, const bf16_t* aL, const float* cL, const bf16_t* y, bf16_t* aR, float* cR,
@@ -291,10 +295,12 @@ template <typename E>
 int first_frame_any(const E* q, const E* k, const E* v, E* out, float* lse, void* scratch, size_t scratch_bytes,
                     const Dims& dm, int nrows, const int* rows, int flash_variant, hipStream_t st);
 template <>
-int first_frame_any<float>(const float* q, const float* k, const float* v, float* out, float* lse, void*, size_t,
-                           const Dims& dm, int nrows, const int* rows, int, hipStream_t st) {
-  hipError_t e = launch_first_frame_generic<float>(q, k, v, out, lse, dm, nrows, rows, st);
-  return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "first_frame (plain-ALU f32) launch");
+int first_frame_any<float>(const float* q, const float* k, const float* v, float* out, float* lse, void* scratch,
+                           size_t scratch_bytes, const Dims& dm, int nrows, const int* rows, int, hipStream_t st) {
+  hipError_t e = f32_mfma_supported(dm, {q, k, v, out})
+                     ? launch_attend_rows_f32(q, k, v, out, lse, dm, nrows, rows, scratch, scratch_bytes, st)
+                     : launch_first_frame_generic<float>(q, k, v, out, lse, dm, nrows, rows, st);
+  return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "first_frame (f32) launch");
 }
 template <>
 int first_frame_any<bf16_t>(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse, void* scratch,
@@ -312,7 +318,8 @@ template <typename E>
 int sink_average_any(const E* q, const E* k, const E* v, E* out, const Dims& dm, hipStream_t st);
 template <>
 int sink_average_any<float>(const float* q, const float* k, const float* v, float* out, const Dims& dm, hipStream_t st) {
-  hipError_t e = launch_sink_average_generic<float>(q, k, v, out, dm, st);
+  hipError_t e = f32_mfma_supported(dm, {q, k, v, out}) ? launch_sink_average_f32(q, k, v, out, dm, st)
+                                                        : launch_sink_average_generic<float>(q, k, v, out, dm, st);
   return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "sink_average (f32) launch");
 }
 template <>
@@ -395,7 +402,10 @@ int attention_impl(const void* q_, const void* k_, const void* v_, void* out_, i
     if (rc) return rc;
   } else if (recompute) {
     phase_mark(st, "first_frame");
-    rc = first_frame_any<E>(q, k, v, out, nullptr, ws + w.ff, w.total - w.ff, dm, dm.b, nullptr, cfg.flash_variant, st);
+    // f32: the sweeps are done with alpha_L and y, whose room (adjacent) takes the partial sums of the key ranges
+    const bool reuse = sizeof(E) == 4;
+    rc = first_frame_any<E>(q, k, v, out, nullptr, ws + (reuse ? w.aL : w.ff), reuse ? w.cL - w.aL : w.total - w.ff, dm,
+                            dm.b, nullptr, cfg.flash_variant, st);
     if (rc) return rc;
   }
   phase_mark(st, nullptr);

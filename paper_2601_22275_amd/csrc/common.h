@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 namespace vm {
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits in memory
@@ -88,6 +90,19 @@ hipError_t launch_sink_average_generic(const E* q, const E* k, const E* v, E* ou
 // p[h * head_stride + r] = value for r < count, h < nheads
 hipError_t launch_fill_head_prefix(float* p, float value, long long count, long long head_stride, int nheads,
                                    hipStream_t st);
+
+// f32.hip : float tensors on the fp32 matrix units (d == 32, 64 or 128, tensors on 16-byte boundaries; temporal factor:
+// T <= 32)
+bool f32_mfma_supported(const Dims& dm, std::initializer_list<const void*> tensors);
+hipError_t launch_r_update_f32(const float* aR, const float* cR, const float* k, const float* v, float* aL, float* cL,
+                               float* y, float* lse, const Dims& dm, float row_scale, float cr_min, hipStream_t st);
+// rows / nrows as in launch_first_frame_flash; scratch (may be null) lets a call with few rows split the keys
+hipError_t launch_attend_rows_f32(const float* q, const float* k, const float* v, float* out, float* lse, const Dims& dm,
+                                  int nrows, const int* rows, void* scratch, size_t scratch_bytes, hipStream_t st);
+hipError_t launch_sink_average_f32(const float* q, const float* k, const float* v, float* out, const Dims& dm, hipStream_t st);
+bool l_update_f32_supported(const Dims& dm, std::initializer_list<const void*> tensors);
+hipError_t launch_l_update_f32(const float* q, const float* aL, const float* cL, const float* y, float* aR, float* cR,
+                               float* out, const Dims& dm, float q_scale, hipStream_t st);
 
 // backward.hip : Alg. 2 on the plain ALUs (D_scratch: BH * N floats)
 size_t entropy_bwd_scratch_bytes(const Dims& dm);

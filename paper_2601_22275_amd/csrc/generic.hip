@@ -1,6 +1,6 @@
 // Plain-ALU kernels for spatio-temporal Monarch attention: any T, b and d <= 256, float or
-// bf16 tensors, float accumulation.  They serve the fp32 entry points and every bf16 shape
-// the MFMA kernels do not cover.  Written for clarity first; each follows the paper's
+// bf16 tensors, float accumulation.  They serve every shape and alignment
+// the matrix-core kernels do not take.  Written for clarity first; each follows the paper's
 // update equations directly (Sec. 3.1 Eqs. R / alpha_L, c_L / L / alpha_R, c_R; App. A).
 #include "common.h"
 
