@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvmonarch.so")
-SOURCES = ["api.hip", "generic.hip", "flash.hip", "flash_kv.hip", "flash2.hip", "lpass.hip", "backward.hip", "backward_mfma.hip", "f32.hip"]
+SOURCES = ["api.hip", "generic.hip", "flash.hip", "flash_kv.hip", "flash2.hip", "frame.hip", "lpass.hip", "backward.hip", "backward_mfma.hip", "f32.hip"]
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fvisibility=hidden",
     # keep the compiler from forming packed fp32 VALU instructions
@@ -21,6 +21,7 @@ FLAGS = [
 EXTRA = {"flash2.hip": ["-fno-honor-nans", "-Wno-inline-asm"],
          "flash.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans"],
          "flash_kv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans"],
+         "frame.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans"],
          "f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
          "backward_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 

@@ -1,0 +1,84 @@
+"""R-updates of short frames: the kernel that takes a whole frame per workgroup, at the edges of its 32-row tiles, against the
+CPU oracle and against the streaming kernels (flash variant 1), which form the same sums in another order.
+
+Tolerance: inputs, outputs and the softmax weights are bf16 (half an ulp is 2^-9 relative); alpha_L and y carry one rounding
+of every weight and one of the result, both random: sqrt(2) 2^-9 = 2.8e-3 in the relative norm at most.  Against the
+oracle 4e-3 is allowed, between the kernels 6e-3.  c_L and the log-sum-exp are float32 sums over weights rounded to bf16: the sum of up
+to 256 weights keeps at most 2^-9 of relative error, the logarithm turns that into 2^-9 absolute; 2^-8 is allowed."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import vmonarch_oracle as O
+from tests import util as U
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2601_22275_amd import binding
+    assert torch.cuda.is_available()
+    binding.lib()
+    return torch, binding, torch.device("cuda:0")
+
+
+def _inputs(T, b, d, seed):
+    rng = np.random.default_rng(seed)
+    aR, K, V = ([U.random_bits(rng, (T * b, d), 1.5, True) for _ in range(2)] for _ in range(3))
+    return aR, K, V, (0.03 + 2.5 * rng.random((2, T * b))).astype(np.float32)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("b", [1, 2, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 256, 257])
+@pytest.mark.parametrize("with_v", [True, False])
+def test_r_update_of_short_frames(env, b, d, with_v):
+    torch, binding, dev = env
+    T, s = 3, 1.0 / math.sqrt(d)
+    aR, K, V, cR = _inputs(T, b, d, 7 * b + d)
+    tq, tk, tv = (U.to_device(x, torch, dev) for x in (aR, K, V))
+    tc = torch.from_numpy(cR).to(dev).view(1, 2, -1)
+    call = lambda: [None if x is None else U.from_device(x) for x in
+                    binding.r_update_lse(tq, tc, tk, tv if with_v else None, T, 1, b, s, 0.1)]
+    aL, cL, y, lse = call()
+    binding.set_flash_variant(1)
+    try:
+        streamed = call()
+    finally:
+        binding.set_flash_variant(2)
+    for h in range(2):
+        c = np.maximum(cR[h].reshape(T, b).astype(np.float64), 0.1)
+        q3, k3, v3 = (U.to_f64(x[h]).reshape(T, b, d) for x in (aR, K, V))
+        oaL, ocL, R = O.r_update(q3 * s, c, k3, 0.1)
+        z = np.einsum("jid,jld->jil", q3 * s / c[:, :, None], k3)
+        ref_lse = (np.log(np.exp(z - z.max(2, keepdims=True)).sum(2)) + z.max(2)).reshape(-1)
+        assert U.rel_l2(aL[h], oaL.transpose(1, 0, 2).reshape(T * b, d)) <= 4e-3
+        assert U.rel_l2(aL[h], streamed[0][h]) <= 6e-3
+        assert U.max_abs(cL[h], ocL.T.reshape(-1)) <= 2.0 ** -8
+        assert U.max_abs(lse[h], ref_lse) <= 2.0 ** -8
+        if with_v:
+            assert U.rel_l2(y[h], np.matmul(R, v3).reshape(T * b, d)) <= 4e-3
+            assert U.rel_l2(y[h], streamed[2][h]) <= 6e-3
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_many_frames_and_no_row_scale(env, d):
+    """More frames than compute units, c_R absent, first and last frame against the oracle; a second call gives the same bits."""
+    torch, binding, dev = env
+    T, b, s = 700, 40, 1.0 / math.sqrt(d)
+    aR, K, V, _ = _inputs(T, b, d, 5)
+    tq, tk, tv = (U.to_device(x, torch, dev) for x in (aR, K, V))
+    first = binding.r_update(tq, None, tk, tv, T, 1, b, s, 0.1)
+    again = binding.r_update(tq, None, tk, tv, T, 1, b, s, 0.1)
+    assert all(torch.equal(x, w) for x, w in zip(first, again))
+    aL, cL, y = (U.from_device(x) for x in first)
+    for h in range(2):
+        for j in (0, T - 1):
+            rows = slice(j * b, (j + 1) * b)
+            q3, k3, v3 = (U.to_f64(x[h][rows])[None] for x in (aR, K, V))
+            oaL, ocL, R = O.r_update(q3 * s, np.ones((1, b)), k3, 0.1)
+            assert U.rel_l2(aL[h][rows], oaL[:, 0]) <= 4e-3
+            assert U.max_abs(cL[h][rows], ocL.reshape(-1)) <= 2.0 ** -8
+            assert U.rel_l2(y[h][rows], np.matmul(R, v3)[0]) <= 4e-3
