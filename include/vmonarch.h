@@ -326,8 +326,8 @@ int vmonarch_permute_tokens(const void* in, void* out, int B, int heads, int T, 
  * o, lse and H are the forward results (vmonarch_r_update_lse returns lse and cL = -H; its aL is
  * O for V := K, its y is O for V).  dH == NULL means no gradient through the entropy, which is
  * how the paper trains.  No gradient with respect to cR is returned.  Uses the workspace
- * (four floats per query row).  bf16 with d == 64 or 128 runs on MFMA kernels (three passes: dq,
- * dv, dk), everything else on plain-ALU kernels; results are bit-reproducible: nothing is
+ * (four floats per query row).  bf16 with d == 64 or 128 runs on MFMA kernels (two passes: dq;
+ * dk and dv), everything else on plain-ALU kernels; results are bit-reproducible: nothing is
  * accumulated across workgroups.
  */
 int vmonarch_entropy_attention_bwd(const void* q, const float* cR, const void* k, const void* v, const void* o,
