@@ -258,7 +258,8 @@ int r_update_any<bf16_t>(const bf16_t* aR, const float* cR, const bf16_t* k, con
   const bool two_tiles = cfg.flash_variant == 1 ||
                          (cfg.flash_variant == 2 && (v != nullptr ? dm.b > 128 : dm.d == 64));
   const bool short_frame = cfg.flash_variant == 2 && cfg.entropy_mode == VMONARCH_ENTROPY_ONLINE &&
-                           (v == nullptr || cfg.fused_apply != 0) && frame_supported(dm, v != nullptr);
+                           (v == nullptr || cfg.fused_apply != 0) &&
+                           (frame_supported(dm, v != nullptr) || frame_rows_supported(dm, v != nullptr));
   if (short_frame)
     e = launch_r_update_frame(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st);
   else if (flash_supported(dm) && two_tiles)

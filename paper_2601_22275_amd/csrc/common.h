@@ -140,6 +140,7 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
                                   hipStream_t st);
 // frame.hip : the same updates for short frames (b <= 192 .. 256; d == 64 or 128), one workgroup per frame
 bool frame_supported(const Dims& dm, bool with_v);
+bool frame_rows_supported(const Dims& dm, bool with_v);  // ... or per 128 rows of one
 hipError_t launch_r_update_frame(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL,
                                  bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min, hipStream_t st);
 // exact attention of nrows query rows per head (starting where q / out / lse point) over all N keys

@@ -63,6 +63,42 @@ def test_r_update_of_short_frames(env, b, d, with_v):
             assert U.rel_l2(y[h], streamed[2][h]) <= 6e-3
 
 
+@pytest.mark.parametrize("b", [257, 319, 320, 321, 352, 353, 383, 384, 385])
+@pytest.mark.parametrize("with_v", [True, False])
+def test_r_update_in_blocks_of_128_rows(env, b, with_v):
+    """More frames of 257 .. 384 tokens than fill the card once: every frame against the streaming kernels, the first and the
+    last one against the oracle."""
+    torch, binding, dev = env
+    T, d, s = 65, 64, 0.125
+    aR, K, V, cR = _inputs(T, b, d, b)
+    tq, tk, tv = (U.to_device(x, torch, dev) for x in (aR, K, V))
+    tc = torch.from_numpy(cR).to(dev).view(1, 2, -1)
+    call = lambda: [None if x is None else U.from_device(x) for x in
+                    binding.r_update_lse(tq, tc, tk, tv if with_v else None, T, 1, b, s, 0.1)]
+    aL, cL, y, lse = call()
+    binding.set_flash_variant(1)
+    try:
+        streamed = call()
+    finally:
+        binding.set_flash_variant(2)
+    for h in range(2):
+        for j in range(T):
+            rows = slice(j * b, (j + 1) * b)
+            assert U.rel_l2(aL[h][rows], streamed[0][h][rows]) <= 6e-3
+            assert not with_v or U.rel_l2(y[h][rows], streamed[2][h][rows]) <= 6e-3
+            if j not in (0, T - 1):
+                continue
+            c = np.maximum(cR[h][rows].astype(np.float64), 0.1)[None]
+            q3, k3, v3 = (U.to_f64(x[h][rows])[None] for x in (aR, K, V))
+            oaL, ocL, R = O.r_update(q3 * s, c, k3, 0.1)
+            z = (q3 * s / c[:, :, None] @ k3.transpose(0, 2, 1))[0]
+            assert U.rel_l2(aL[h][rows], oaL[:, 0]) <= 4e-3
+            assert U.max_abs(cL[h][rows], ocL.reshape(-1)) <= 2.0 ** -8
+            assert U.max_abs(lse[h][rows], np.log(np.exp(z - z.max(1, keepdims=True)).sum(1)) + z.max(1)) <= 2.0 ** -8
+            if with_v:
+                assert U.rel_l2(y[h][rows], np.matmul(R, v3)[0]) <= 4e-3
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_many_frames_and_no_row_scale(env, d):
     """More frames than compute units, c_R absent, first and last frame against the oracle; a second call gives the same bits."""
