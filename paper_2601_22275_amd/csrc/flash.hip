@@ -32,8 +32,9 @@ namespace {
 __device__ __forceinline__ uint32_t average_bf16x2(uint32_t a, uint32_t b);
 __device__ __forceinline__ uint4 average_bf16x8(uint4 a, uint4 b);
 
-template <int D, bool OUT_K, bool OUT_V, bool ENT, bool SPLIT, int BIAS = 0>
-__global__ void __launch_bounds__(64 * NW) flash_kernel(FlashParams P) {
+// WAVES: waves per SIMD the registers are to allow (4: two workgroups on a compute unit, see launch_temporal)
+template <int D, bool OUT_K, bool OUT_V, bool ENT, bool SPLIT, int BIAS = 0, int WAVES = 1>
+__global__ void __launch_bounds__(64 * NW, WAVES) flash_kernel(FlashParams P) {
   using G = RowGeo<D>;
   constexpr int ROW_BYTES = G::ROW_BYTES;
   constexpr int TILE_BYTES = BK * ROW_BYTES;  // 16 KB (d = 128) or 8 KB (d = 64)
@@ -493,11 +494,11 @@ __global__ void __launch_bounds__(128) merge_splits_kernel(const float* __restri
 
 constexpr int kMaxBiasedKeys = 8192 - BK;  // biased modes keep one float per key (+ one tile of padding) behind the tile slots: 32 KB
 
-template <int D, bool OUT_K, bool OUT_V, bool ENT, bool SPLIT, int BIAS = 0>
+template <int D, bool OUT_K, bool OUT_V, bool ENT, bool SPLIT, int BIAS = 0, int WAVES = 1>
 hipError_t launch_flash(const FlashParams& P, hipStream_t st) {
   constexpr int TILE_LDS = 2 * NSLOT * BK * D * 2;  // four K slots + four V slots: 128 KB at d = 128
   constexpr int MAX_LDS = TILE_LDS + (BIAS != 0 ? (kMaxBiasedKeys + BK) * 4 : 0);
-  auto kern = flash_kernel<D, OUT_K, OUT_V, ENT, SPLIT, BIAS>;
+  auto kern = flash_kernel<D, OUT_K, OUT_V, ENT, SPLIT, BIAS, WAVES>;
   static bool configured = false;  // the attribute is per function, set once per process
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);
@@ -652,6 +653,21 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
 // lse_scratch: BH * N floats (fitting sweep only).
 bool temporal_flash_supported(const Dims& dm) { return (dm.d == 128 || dm.d == 64) && dm.T <= kMaxBiasedKeys; }
 
+namespace {
+// One of the temporal factor's product passes.  Its key loops are short (T / 64 tiles), so what surrounds the loop (first
+// tiles and key terms from HBM, stores) and the wait for tiles count; at d = 64 two workgroups on a compute unit hide it from
+// each other if a wave makes do with 128 registers: 12 x 64 problems of 512: 97 -> 75 us fitting, 111 -> 91 us last; 6 x 64
+// of 1000: 162 -> 148 us last.  A launch that does not give every unit two, or whose key terms leave LDS for one (from about
+// 4000 frames), keeps all registers (2 x 24 of 512: 16.1 against 17.2 us).
+template <int D, bool OUT_K, bool OUT_V, int BIAS>
+hipError_t launch_temporal(const FlashParams& P, hipStream_t st) {
+  const int lds = 2 * NSLOT * BK * D * 2 + ((P.nk + BK - 1) / BK + 1) * BK * 4;
+  if constexpr (D == 64)
+    if (P.total_blocks > compute_units() && 2 * lds <= 160 * 1024) return launch_flash<D, OUT_K, OUT_V, false, false, BIAS, 4>(P, st);
+  return launch_flash<D, OUT_K, OUT_V, false, false, BIAS>(P, st);
+}
+}  // namespace
+
 hipError_t launch_l_update_flash(const bf16_t* q, const bf16_t* aL, const float* cL, const bf16_t* y, bf16_t* aR, float* cR,
                                  bf16_t* out, float* lse_scratch, const Dims& dm, float q_scale, hipStream_t st) {
   if (!temporal_flash_supported(dm)) return hipErrorInvalidValue;
@@ -671,7 +687,7 @@ hipError_t launch_l_update_flash(const bf16_t* q, const bf16_t* aL, const float*
   const bool d128 = dm.d == 128;
   if (y != nullptr) {
     P.q = q; P.k = aL; P.v = y; P.outv = out; P.kbias = cL;
-    return d128 ? launch_flash<128, false, true, false, false, 1>(P, st) : launch_flash<64, false, true, false, false, 1>(P, st);
+    return d128 ? launch_temporal<128, false, true, 1>(P, st) : launch_temporal<64, false, true, 1>(P, st);
   }
   if (lse_scratch == nullptr) return hipErrorInvalidValue;
   P.q = q; P.k = aL; P.lse = lse_scratch; P.kbias = cL;
@@ -680,7 +696,7 @@ hipError_t launch_l_update_flash(const bf16_t* q, const bf16_t* aL, const float*
   P.q = aL; P.k = q; P.outk = aR; P.cl = cR; P.lse = nullptr;
   P.kbias = lse_scratch;          // natural log, like c_L: the same scale -log2(e) applies
   P.qbias = cL; P.qb_scale = LOG2E;
-  return d128 ? launch_flash<128, true, false, false, false, 2>(P, st) : launch_flash<64, true, false, false, false, 2>(P, st);
+  return d128 ? launch_temporal<128, true, false, 2>(P, st) : launch_temporal<64, true, false, 2>(P, st);
 }
 
 // Attention-sink averaging (Sec. 4.4): all N queries of a head against its first frame's b keys,
