@@ -1,4 +1,4 @@
-// Device-side pieces shared by the bf16 MFMA blocked-softmax kernels (flash.hip, flash_kv.hip):
+// Device-side pieces shared by the bf16 MFMA blocked-softmax kernels (flash*.hip, frame.hip):
 // tile constants, the kernel parameter block, LDS read helpers and the per-sub-tile softmax
 // arithmetic.  Everything has internal linkage.
 #pragma once

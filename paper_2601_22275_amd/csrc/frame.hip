@@ -7,7 +7,8 @@
 // idles on padding (the streaming kernels' blocks of 256 or 128 query rows are padding for the most part here), a block
 // needs 4 KT .. 16 KT KB of LDS, so that many frames are in flight on a compute unit, and all of a frame's loads are
 // issued before the first is waited for.  Fitting / last update in us, before -> now, 12 heads, d = 64: 32 frames of 32 tokens
-// (one block's chain) 9.8 / 11.0 -> 4.7 / 5.0; 512 frames of 64 80 / 106 -> 25 / 40 (5.9 / 6.3 TB/s of the tensors).  Contractions and register layouts are the streaming kernels' (flash2.hip):
+// (one block's chain) 9.8 / 11.0 -> 4.7 / 5.0; 512 frames of 64 80 / 106 -> 25 / 40 (5.9 / 6.3 TB/s of the tensors).
+// Contractions and register layouts are the streaming kernels' (flash2.hip):
 //
 //   S^T = K Q^T     A = K rows from LDS, B = Q^T in registers; lane (q, g) holds query q's logits for half of the keys
 //   X^T P^T         A = X^T (X = K, then V) by LDS transpose reads, B = P^T from the softmax registers
