@@ -24,7 +24,7 @@
 // the four arrays and a third of the vector arithmetic drop out: that is the PLAIN form.
 // Measured, all gradients: 12 x 21 frames of 1560, d = 128, plain form: dQ 633 -> 575 us (819 TFLOP/s), dV + dK 467 + 742
 // -> 800 us (785 TFLOP/s), statistics 36 us -> inside dQ; 10 x 9 frames of 943, d = 64, general form: 66 + 59 + 76 + 8
-// -> 62 + 80 us.  The bound is the matrix pipe under its power limit (a large library product reaches 1150 TFLOP/s).
+// -> 62 + 80 us (eight waves per block; see waves below).  The bound is the matrix pipe under its power limit (a large library product reaches 1150 TFLOP/s).
 #include <type_traits>
 
 #include "common.h"
@@ -34,8 +34,13 @@ namespace vm {
 namespace {
 
 constexpr int BK = 64;    // stream rows per LDS tile
-constexpr int NW = 8;     // waves per workgroup, 32 owner rows each
-constexpr int BO = 32 * NW;
+// Waves per workgroup, 32 owner rows each.  At d = 64 two workgroups of four waves fit a compute unit: the smaller blocks leave less
+// of the last round idle and hide each other's start and end (all gradients, eight -> four waves: 90 frames of 943 131 -> 114 us,
+// 252 of 1560 722 -> 667, 128 of 512 level).  At d = 128 the tiles leave LDS for one.
+template <int D>
+constexpr int waves() {
+  return D == 64 ? 4 : 8;
+}
 constexpr int NSLOT = 3;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
@@ -92,8 +97,10 @@ constexpr int own_in_lds() {
 }
 
 template <int D, int MODE>
-__global__ void __launch_bounds__(64 * NW) bwd_kernel(BwdParams P) {
+__global__ void __launch_bounds__(64 * waves<D>(), 2) bwd_kernel(BwdParams P) {
   using G = RowGeo<D>;
+  constexpr int NW = waves<D>();
+  constexpr int BO = 32 * NW;
   constexpr int ROW_BYTES = G::ROW_BYTES;
   constexpr int TILE_BYTES = BK * ROW_BYTES;
   constexpr int SLOT_BYTES = 2 * TILE_BYTES;         // X1 tile, then X2 tile
@@ -386,7 +393,7 @@ __global__ void __launch_bounds__(64 * NW) bwd_kernel(BwdParams P) {
 
 template <int D, int MODE>
 hipError_t launch_bwd(const BwdParams& P, hipStream_t st) {
-  constexpr int LDS_BYTES = 2 * NSLOT * BK * D * 2 + NSLOT * BK * 16 + NW * own_in_lds<D, MODE>() * 1024;
+  constexpr int LDS_BYTES = 2 * NSLOT * BK * D * 2 + NSLOT * BK * 16 + waves<D>() * own_in_lds<D, MODE>() * 1024;
   auto kern = bwd_kernel<D, MODE>;
   static bool configured = false;
   if (!configured) {
@@ -394,7 +401,7 @@ hipError_t launch_bwd(const BwdParams& P, hipStream_t st) {
     if (e != hipSuccess) return e;
     configured = true;
   }
-  hipLaunchKernelGGL(kern, dim3(P.blocks_per_xcd * 8), dim3(64 * NW), LDS_BYTES, st, P);
+  hipLaunchKernelGGL(kern, dim3(P.blocks_per_xcd * 8), dim3(64 * waves<D>()), LDS_BYTES, st, P);
   return hipGetLastError();
 }
 
@@ -414,7 +421,8 @@ hipError_t launch_entropy_bwd_mfma(const bf16_t* q, const float* cR, const bf16_
   P.o = o; P.cR = cR; P.lse = lse; P.H = H; P.dH = dH; P.stats = (float4*)scratch;
   P.row_scale = row_scale; P.cr_min = cr_min;
   P.n = dm.b;
-  P.nob = (dm.b + BO - 1) / BO;
+  const int owner_rows = 32 * (dm.d == 64 ? waves<64>() : waves<128>());
+  P.nob = (dm.b + owner_rows - 1) / owner_rows;
   const long long total = (long long)dm.BH * dm.T * P.nob;
   if (total > 0x3fffffffLL) return hipErrorInvalidValue;
   P.total_blocks = (int)total;
