@@ -55,12 +55,11 @@ extern "C" {
 #define VMONARCH_ERR_WORKSPACE (-3)   /* caller workspace too small / allocation failed */
 #define VMONARCH_ERR_HIP (-4)         /* a HIP runtime call failed */
 
-/* How the R-update obtains c_L = sum_l R log R (Eq. alpha_L/c_L).  The two differ on the kernel in which two waves
- * share a query tile (vmonarch_set_fused_apply) and on the plain-ALU kernels only: the other MFMA kernels take Alg. 1's
- * h = sum_l p z from their fp32 accumulators of sum_l p K (h is linear in K) in either mode, with the weights that
- * the outputs and the log-sum-exp carry. */
-#define VMONARCH_ENTROPY_ONLINE 0   /* Alg. 1 / App. B: third statistic h beside (m, l) */
-#define VMONARCH_ENTROPY_IDENTITY 1 /* c_L = (aR . alpha_L) * scale - logsumexp */
+/* How the R-update obtains c_L = sum_l R log R (Eq. alpha_L/c_L).  ONLINE: fp32 sums relative to the row's
+ * reference.  IDENTITY: a difference of two terms of the logits' size, so its error grows with them; it is what bf16
+ * calls with d == 64 or 128 may choose, every other call is ONLINE. */
+#define VMONARCH_ENTROPY_ONLINE 0   /* Alg. 1 / App. B: third running statistic h beside (m, l) */
+#define VMONARCH_ENTROPY_IDENTITY 1 /* c_L = (aR . alpha_L) * scale - logsumexp, from the outputs */
 
 /* The `recompute` argument of vmonarch_attention[_f32]. */
 #define VMONARCH_RECOMPUTE_NONE 0

@@ -263,7 +263,7 @@ int r_update_any<bf16_t>(const bf16_t* aR, const float* cR, const bf16_t* k, con
   if (short_frame)
     e = launch_r_update_frame(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st);
   else if (flash_supported(dm) && two_tiles)
-    e = launch_r_update_flash2(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st);
+    e = launch_r_update_flash2(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, cfg.entropy_mode, st);
   else if (flash_supported(dm))
     e = launch_r_update_flash(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, cfg.entropy_mode, cfg.fused_apply != 0, st);
   else

@@ -137,7 +137,7 @@ hipError_t launch_r_update_flash_fused(const bf16_t* aR, const float* cR, const 
 // v == nullptr: alpha_L, c_L (fitting sweep); v given: also y, from one evaluation of the softmax
 hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL,
                                   float* cL, bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min,
-                                  hipStream_t st);
+                                  int entropy_mode, hipStream_t st);
 // frame.hip : the same updates for short frames (b <= 192 .. 256; d == 64 or 128), one workgroup per frame
 bool frame_supported(const Dims& dm, bool with_v);
 bool frame_rows_supported(const Dims& dm, bool with_v);  // ... or per 128 rows of one

@@ -32,8 +32,9 @@ namespace {
 __device__ __forceinline__ uint32_t average_bf16x2(uint32_t a, uint32_t b);
 __device__ __forceinline__ uint4 average_bf16x8(uint4 a, uint4 b);
 
+// ENT: c_L not wanted (0), online (1) or in the identity form (2).
 // WAVES: waves per SIMD the registers are to allow (4: two workgroups on a compute unit, see launch_temporal)
-template <int D, bool OUT_K, bool OUT_V, bool ENT, bool SPLIT, int BIAS = 0, int WAVES = 1>
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int BIAS = 0, int WAVES = 1>
 __global__ void __launch_bounds__(64 * NW, WAVES) flash_kernel(FlashParams P) {
   using G = RowGeo<D>;
   constexpr int ROW_BYTES = G::ROW_BYTES;
@@ -44,8 +45,8 @@ __global__ void __launch_bounds__(64 * NW, WAVES) flash_kernel(FlashParams P) {
   constexpr int RPI = G::RPI;                 // rows filled by one 64-lane global -> LDS load
   auto swz = [](int row) { return G::swz(row); };
   extern __shared__ __attribute__((aligned(16))) char smem[];  // [K|V][NSLOT][64 rows][2 D bytes] [key biases]
-  static_assert(!ENT || OUT_K, "c_L comes from the R K accumulators");
-  static_assert(BIAS == 0 || (!SPLIT && !ENT), "the biased modes are whole-range passes without entropy");
+  static_assert(ENT == 0 || OUT_K, "c_L belongs to the pass over K");
+  static_assert(BIAS == 0 || (!SPLIT && ENT == 0), "the biased modes are whole-range passes without entropy");
   // The biased pass over K without entropy is the first of the temporal factor's two (launch_l_update_flash): only the
   // rows' log-sum-exp is wanted, so the products (half of its matrix and LDS work) are left out: 97 -> 60 us for 12 x 64
   // problems of 512 x 512 at d = 64.
@@ -196,11 +197,13 @@ __global__ void __launch_bounds__(64 * NW, WAVES) flash_kernel(FlashParams P) {
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[qt][ct][r] = 0.f;
-  float msc[QT], ltil[QT];
+  float msc[QT], ltil[QT], lsum[QT], hsum[QT];
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     msc[qt] = NEG_BIG;
     ltil[qt] = 0.f;
+    lsum[qt] = 0.f;
+    hsum[qt] = 0.f;
     // BIAS == 2: the reference of a row is given and never moves (every exponent is <= 0 by construction)
     if (BIAS == 2) msc[qt] = P.qb_scale * P.qbias[qrow0 + grow[qt] * rs];
   }
@@ -303,13 +306,17 @@ __global__ void __launch_bounds__(64 * NW, WAVES) flash_kernel(FlashParams P) {
     for (int qt = 0; qt < QT; ++qt) {
       const float dl = msc[qt] - mpend[qt];  // log2 of the rescale factor: <= 0, and 0 when nothing moved
       alpha[qt] = __builtin_amdgcn_exp2f(dl);
+      if (ENT == 1) {
+        hsum[qt] = alpha[qt] * (hsum[qt] + dl * lsum[qt]);  // h <- a h + a log(a) l
+        lsum[qt] *= alpha[qt];
+      }
       ltil[qt] *= alpha[qt];
       msc[qt] = mpend[qt];
     }
     logits(next_ktile, next_st, snext);
     if (!LSE_ONLY) accumulate(prev_ktile, prev_st, pbprev);
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) subtile_probs(scur[qt], sc[qt], msc[qt], ltil[qt], pbcur[qt]);
+    for (int qt = 0; qt < QT; ++qt) subtile_probs<ENT == 1>(scur[qt], sc[qt], msc[qt], ltil[qt], lsum[qt], hsum[qt], pbcur[qt]);
     add_key_bias(snext, next_sub);
     look_ahead(snext);
     // Keep this step's vector results in this step: without the pins below the compiler sinks
@@ -318,6 +325,7 @@ __global__ void __launch_bounds__(64 * NW, WAVES) flash_kernel(FlashParams P) {
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
       asm volatile("" : "+v"(pbcur[qt][0]), "+v"(pbcur[qt][1]), "+v"(ltil[qt]), "+v"(mpend[qt]));
+      if (ENT == 1) asm volatile("" : "+v"(lsum[qt]), "+v"(hsum[qt]));
     }
     if (!LSE_ONLY && moved_now) {
 #pragma unroll
@@ -393,12 +401,16 @@ __global__ void __launch_bounds__(64 * NW, WAVES) flash_kernel(FlashParams P) {
     }
     if (BIAS == 2 && qvalid[qt] && g == 0) P.cl[row] = lt;              // ... and their sum is an output
     if (!SPLIT) {
-      if (P.lse != nullptr && qvalid[qt] && g == 0) P.lse[row] = LN2 * (msc[qt] + __log2f(lt));
-      if (ENT) {
-        // App. B's h = sum p t from the accumulators (see row_dot): c_L = h / l - log l = sc (aR . alpha_L) - lse
+      const float l = ENT == 1 ? lsum[qt] + __shfl_xor(lsum[qt], 32) : lt;
+      if (P.lse != nullptr && qvalid[qt] && g == 0) P.lse[row] = LN2 * (msc[qt] + __log2f(l));
+      if (ENT == 1) {
+        // App. B: H = log S - L / S; here in base-2 units, c_L = -H
+        const float h = hsum[qt] + __shfl_xor(hsum[qt], 32);
+        if (qvalid[qt] && g == 0) P.cl[row] = LN2 * (h / l - __log2f(l));
+      }
+      if (ENT == 2) {
         const float mean_t = row_dot<D>(qreg[qt], oacc[qt]) * inv * sc[qt];  // sum_l R_l (s_l sc), log2 units
-        const float lse2 = msc[qt] + __log2f(lt);
-        if (qvalid[qt] && g == 0) P.cl[row] = LN2 * (mean_t - lse2);
+        if (qvalid[qt] && g == 0) P.cl[row] = LN2 * (mean_t - (msc[qt] + __log2f(l)));
       }
       // lane (q, g) holds channels 32 ct + 8 c + 4 g .. + 3 of query q: 8-byte pieces
 #pragma unroll
@@ -494,7 +506,7 @@ __global__ void __launch_bounds__(128) merge_splits_kernel(const float* __restri
 
 constexpr int kMaxBiasedKeys = 8192 - BK;  // biased modes keep one float per key (+ one tile of padding) behind the tile slots: 32 KB
 
-template <int D, bool OUT_K, bool OUT_V, bool ENT, bool SPLIT, int BIAS = 0, int WAVES = 1>
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int BIAS = 0, int WAVES = 1>
 hipError_t launch_flash(const FlashParams& P, hipStream_t st) {
   constexpr int TILE_LDS = 2 * NSLOT * BK * D * 2;  // four K slots + four V slots: 128 KB at d = 128
   constexpr int MAX_LDS = TILE_LDS + (BIAS != 0 ? (kMaxBiasedKeys + BK) * 4 : 0);
@@ -573,16 +585,17 @@ hipError_t launch_r_update_flash(const bf16_t* aR, const float* cR, const bf16_t
   P.total_blocks = (int)total;
   P.blocks_per_xcd = (P.total_blocks + 7) / 8;
   P.row_scale = row_scale; P.cr_min = cr_min;
+  const bool ident = entropy_mode == VMONARCH_ENTROPY_IDENTITY;
   // alpha_L and c_L from one pass over K; y = R V from a second pass that recomputes the
   // logits.  (One wave cannot hold both accumulator sets; flash_kv.hip shares them between two.)
   auto run = [&](auto dc) -> hipError_t {
     constexpr int D = decltype(dc)::value;
-    hipError_t e = launch_flash<D, true, false, true, false>(P, st);
+    hipError_t e = ident ? launch_flash<D, true, false, 2, false>(P, st) : launch_flash<D, true, false, 1, false>(P, st);
     if (e != hipSuccess || v == nullptr) return e;
     P.outk = nullptr;
     P.cl = nullptr;
     P.lse = nullptr;
-    return launch_flash<D, false, true, false, false>(P, st);
+    return launch_flash<D, false, true, 0, false>(P, st);
   };
   return dm.d == 128 ? run(std::integral_constant<int, 128>{}) : run(std::integral_constant<int, 64>{});
 }
@@ -626,7 +639,7 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   const bool ff2 = two_tile && row_list == nullptr && flash2_query_block() == BQ;
   if (ns == 1) {
     if (ff2) return launch_first_frame_flash2(q, k, v, out, lse, nullptr, nullptr, dm, nrows, 1, P.keys_per_split, st);
-    return d128 ? launch_flash<128, false, true, false, false>(P, st) : launch_flash<64, false, true, false, false>(P, st);
+    return d128 ? launch_flash<128, false, true, 0, false>(P, st) : launch_flash<64, false, true, 0, false>(P, st);
   }
   const size_t rows = (size_t)ns * dm.BH * nrows;
   const size_t need = rows * dm.d * sizeof(float) + ((rows * sizeof(float) + 255) & ~(size_t)255);
@@ -634,7 +647,7 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   P.part_lse = (float*)scratch;
   P.part_o = (float*)((char*)scratch + ((rows * sizeof(float) + 255) & ~(size_t)255));
   hipError_t e = ff2 ? launch_first_frame_flash2(q, k, v, out, lse, P.part_o, P.part_lse, dm, nrows, ns, P.keys_per_split, st)
-                     : (d128 ? launch_flash<128, false, true, false, true>(P, st) : launch_flash<64, false, true, false, true>(P, st));
+                     : (d128 ? launch_flash<128, false, true, 0, true>(P, st) : launch_flash<64, false, true, 0, true>(P, st));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(merge_splits_kernel, dim3((unsigned)((long long)dm.BH * nrows)), dim3(dm.d), 0, st, P.part_o,
                      P.part_lse, out, lse, ns, (long long)dm.BH * nrows, nrows, dm.N, row_list, (int)dm.N);
@@ -663,8 +676,8 @@ template <int D, bool OUT_K, bool OUT_V, int BIAS>
 hipError_t launch_temporal(const FlashParams& P, hipStream_t st) {
   const int lds = 2 * NSLOT * BK * D * 2 + ((P.nk + BK - 1) / BK + 1) * BK * 4;
   if constexpr (D == 64)
-    if (P.total_blocks > compute_units() && 2 * lds <= 160 * 1024) return launch_flash<D, OUT_K, OUT_V, false, false, BIAS, 4>(P, st);
-  return launch_flash<D, OUT_K, OUT_V, false, false, BIAS>(P, st);
+    if (P.total_blocks > compute_units() && 2 * lds <= 160 * 1024) return launch_flash<D, OUT_K, OUT_V, 0, false, BIAS, 4>(P, st);
+  return launch_flash<D, OUT_K, OUT_V, 0, false, BIAS>(P, st);
 }
 }  // namespace
 
@@ -691,7 +704,7 @@ hipError_t launch_l_update_flash(const bf16_t* q, const bf16_t* aL, const float*
   }
   if (lse_scratch == nullptr) return hipErrorInvalidValue;
   P.q = q; P.k = aL; P.lse = lse_scratch; P.kbias = cL;
-  hipError_t e = d128 ? launch_flash<128, true, false, false, false, 1>(P, st) : launch_flash<64, true, false, false, false, 1>(P, st);
+  hipError_t e = d128 ? launch_flash<128, true, false, 0, false, 1>(P, st) : launch_flash<64, true, false, 0, false, 1>(P, st);
   if (e != hipSuccess) return e;
   P.q = aL; P.k = q; P.outk = aR; P.cl = cR; P.lse = nullptr;
   P.kbias = lse_scratch;          // natural log, like c_L: the same scale -log2(e) applies
@@ -719,7 +732,7 @@ hipError_t launch_sink_average_flash(const bf16_t* q, const bf16_t* k, const bf1
   P.row_scale = 1.0f / sqrtf((float)dm.d);
   P.cr_min = 0.f;
   P.blend = 1;
-  return dm.d == 128 ? launch_flash<128, false, true, false, false>(P, st) : launch_flash<64, false, true, false, false>(P, st);
+  return dm.d == 128 ? launch_flash<128, false, true, 0, false>(P, st) : launch_flash<64, false, true, 0, false>(P, st);
 }
 
 }  // namespace vm

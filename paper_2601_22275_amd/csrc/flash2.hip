@@ -40,9 +40,9 @@ constexpr int BQ2 = 32 * Q2 * W2;  // query rows per workgroup
 // outputs no precision until 2^t nears overflow.  c_L needs one precaution: the sum h of p t and the sum l of p
 // must weigh every key alike, or their mismatch (about 1e-3 relative when l holds the bf16-rounded p and h the
 // unrounded ones) is multiplied by the mean of t, which a stale reference lets grow to 32; both carry the
-// ROUNDED p here (see the epilogue).  Moving a reference is expensive in this kernel (the accumulators sit in
-// accumulation registers and pass through ordinary ones to be rescaled), and in the last sweep's update, where
-// c_R sharpens some rows tenfold, a margin of 2^8 would move one in most steps.
+// UNROUNDED p here, beside the rounded sum that the outputs are divided by.  Moving a reference is expensive in this
+// kernel (the accumulators sit in accumulation registers and pass through ordinary ones to be rescaled), and in the
+// last sweep's update, where c_R sharpens some rows tenfold, a margin of 2^8 would move one in most steps.
 constexpr float RESCALE_TH2 = 32.0f;
 // Where a moving reference is put: this far (log2 units) above the row maximum that moved it, the first one
 // included.  Any reference gives the same results (the sums and the accumulators carry the common factor
@@ -76,7 +76,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // handling cannot see, so wherever vector code follows an MFMA closely this wait is written out.
 #define F2_MFMA_RESULT_WAIT() asm volatile("s_nop 7\n\ts_nop 3" ::: "memory")
 
-template <int D, bool OUT_K, bool OUT_V, bool SPLIT>
+// ENT: c_L not wanted (0), online (1) or in the identity form (2)
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT>
 __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   using G = RowGeo<D>;
   constexpr int ROW_BYTES = G::ROW_BYTES;
@@ -253,11 +254,13 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
       for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[x][qt][ct][r] = 0.f;
-  float msc[Q2], ltil[Q2];
+  float msc[Q2], ltil[Q2], lsum[Q2], hsum[Q2];
 #pragma unroll
   for (int qt = 0; qt < Q2; ++qt) {
     msc[qt] = NEG_BIG;
     ltil[qt] = 0.f;
+    lsum[qt] = 0.f;
+    hsum[qt] = 0.f;
   }
 
   // ---- the MFMAs, as inline assembly ---------------------------------------------------------
@@ -331,7 +334,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   bf16x2 ones2;
   ones2[0] = (__bf16)1.0f;
   ones2[1] = (__bf16)1.0f;
-  // Two scores of one query tile: t = s sc - m, p = 2^t, bf16 pair, l += rounded p.  The three
+  // Two scores of one query tile: t = s sc - m, p = 2^t, bf16 pair, sums of the rounded p, of p and of p t.  The three
   // stages of a pair (scale, exponent, the rest) are dependent instructions; each stage goes to an MFMA slot of its
   // own (the stages that share a slot then belong to different pairs and issue back to back), so that a single
   // wave does not sit out the latency of its own chain.
@@ -355,10 +358,18 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     bf16x2 pr;
     pr[0] = (__bf16)pq[K & 1][0];  // round to nearest even; the pair is one v_cvt_pk_bf16_f32
     pr[1] = (__bf16)pq[K & 1][1];
+    if (ENT == 1) {
+      lsum[qt] += pq[K & 1][0];
+      hsum[qt] = __builtin_fmaf(pq[K & 1][0], tq[K & 1][0], hsum[qt]);
+      lsum[qt] += pq[K & 1][1];
+      hsum[qt] = __builtin_fmaf(pq[K & 1][1], tq[K & 1][1], hsum[qt]);
+    }
+    // last, so that it does not wait for the conversion (12 x 32 frames of 2048, d = 64, last update: 753 -> 734 us)
     ltil[qt] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, ltil[qt], false);
     pbcur[qt][j >> 2][2 * (j & 3)] = pr[0];
     pbcur[qt][j >> 2][2 * (j & 3) + 1] = pr[1];
     asm volatile("" : "+v"(ltil[qt]));
+    if (ENT == 1) asm volatile("" : "+v"(lsum[qt]), "+v"(hsum[qt]));
   };
   float mpend[Q2];     // references that take effect at the start of the next step
   bool moved = false;  // wave-uniform: some reference moves at the start of the next step
@@ -404,13 +415,17 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     const bool moved_now = moved;
     float alpha[Q2];
     if (moved_now) {
-      // a reference moves (rare: only when a row maximum outgrew it by 2^RESCALE_TH): the running sum now
-      // (App. B), the accumulators at the end of the step, after the products of
+      // a reference moves (rare: only when a row maximum outgrew it by 2^RESCALE_TH): the running sums now
+      // (App. B: h <- a h + a log(a) l), the accumulators at the end of the step, after the products of
       // sub-tile n-1, which were formed against the old reference
 #pragma unroll
       for (int qt = 0; qt < Q2; ++qt) {
         const float dl = msc[qt] - mpend[qt];  // log2 of the rescale factor, <= 0
         alpha[qt] = __builtin_amdgcn_exp2f(dl);
+        if (ENT == 1) {
+          hsum[qt] = alpha[qt] * (hsum[qt] + dl * lsum[qt]);
+          lsum[qt] *= alpha[qt];
+        }
         ltil[qt] *= alpha[qt];
         msc[qt] = mpend[qt];
       }
@@ -584,15 +599,16 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     const float lt = ltil[qt] + __shfl_xor(ltil[qt], 32);
     const float inv = lt > 0.f ? 1.0f / lt : 0.f;
     if (!SPLIT) {
-      if (P.lse != nullptr && qvalid && g_e == 0) P.lse[row] = LN2 * (msc[qt] + __log2f(lt));
-      if (OUT_K) {
-        // App. B's h = sum p t from the accumulators (see row_dot): c_L = h / l - log l = sc (aR . alpha_L) - lse.
-        // Two unpacks and two multiply-adds per pair of scores less in the key loop: last / fitting update of 12 heads
-        // x 32 frames x 2048^2, d = 64: 0.72 -> 0.67 / 0.50 -> 0.42 ms; last update of 12 x 81 x 1456^2, d = 128:
-        // 1.66 -> 1.59 ms.
+      const float l = ENT == 1 ? lsum[qt] + __shfl_xor(lsum[qt], 32) : lt;
+      if (P.lse != nullptr && qvalid && g_e == 0) P.lse[row] = LN2 * (msc[qt] + __log2f(l));
+      if (ENT == 1) {
+        // App. B: H = log S - L / S; here in base-2 units, c_L = -H
+        const float h = hsum[qt] + __shfl_xor(hsum[qt], 32);
+        if (qvalid && g_e == 0) P.cl[row] = LN2 * (h / l - __log2f(l));
+      }
+      if (ENT == 2) {
         const float mean_t = row_dot<D>(qreg[qt], oacc[0][qt]) * inv * sc[qt];  // sum_l R_l (s_l sc), log2 units
-        const float lse2 = msc[qt] + __log2f(lt);
-        if (qvalid && g_e == 0) P.cl[row] = LN2 * (mean_t - lse2);
+        if (qvalid && g_e == 0) P.cl[row] = LN2 * (mean_t - (msc[qt] + __log2f(l)));
       }
       // lane (q, g) holds channels 32 ct + 8 c + 4 g .. + 3 of query q: 8-byte pieces
 #pragma unroll
@@ -654,11 +670,11 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   }
 }
 
-template <int D, bool OUT_K, bool OUT_V, bool SPLIT>
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT>
 hipError_t launch_flash2(const FlashParams& P, hipStream_t st) {
   // four K slots always (the logits need them), four V slots when values are multiplied: 128 KB at d = 128
   constexpr int LDS_BYTES = (OUT_V ? 2 : 1) * NSLOT * BK * D * 2;
-  auto kern = flash2_kernel<D, OUT_K, OUT_V, SPLIT>;
+  auto kern = flash2_kernel<D, OUT_K, OUT_V, ENT, SPLIT>;
   static bool configured = false;  // the attribute is per function, set once per process
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
@@ -698,14 +714,14 @@ hipError_t launch_first_frame_flash2(const bf16_t* q, const bf16_t* k, const bf1
   P.row_scale = 1.0f / sqrtf((float)dm.d);
   P.cr_min = 0.f;
   const bool split = ns > 1;
-  if (dm.d == 128) return split ? launch_flash2<128, false, true, true>(P, st) : launch_flash2<128, false, true, false>(P, st);
-  return split ? launch_flash2<64, false, true, true>(P, st) : launch_flash2<64, false, true, false>(P, st);
+  if (dm.d == 128) return split ? launch_flash2<128, false, true, 0, true>(P, st) : launch_flash2<128, false, true, 0, false>(P, st);
+  return split ? launch_flash2<64, false, true, 0, true>(P, st) : launch_flash2<64, false, true, 0, false>(P, st);
 }
 
 // One R-update on the one-wave-per-SIMD kernel: alpha_L, c_L (and lse if not null), plus y when v is given.
 hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL,
                                   float* cL, bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min,
-                                  hipStream_t st) {
+                                  int entropy_mode, hipStream_t st) {
   if (!(dm.d == 128 || dm.d == 64) || (v == nullptr) != (y == nullptr)) return hipErrorInvalidValue;
   FlashParams P = {};
   P.q = aR; P.cR = cR; P.k = k; P.v = v; P.outk = aL; P.outv = y; P.cl = cL; P.lse = lse;
@@ -723,9 +739,14 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
   // for the same tile at about the same time and all but the first request hit its L2 (starting each block at its own
   // tile instead measured 1.9x the algorithmic HBM reads at the same speed)
   P.own_tile_first = 0;
+  const bool ident = entropy_mode == VMONARCH_ENTROPY_IDENTITY;
   const bool d128 = dm.d == 128;
-  if (v != nullptr) return d128 ? launch_flash2<128, true, true, false>(P, st) : launch_flash2<64, true, true, false>(P, st);
-  return d128 ? launch_flash2<128, true, false, false>(P, st) : launch_flash2<64, true, false, false>(P, st);
+  if (v != nullptr) {
+    if (ident) return d128 ? launch_flash2<128, true, true, 2, false>(P, st) : launch_flash2<64, true, true, 2, false>(P, st);
+    return d128 ? launch_flash2<128, true, true, 1, false>(P, st) : launch_flash2<64, true, true, 1, false>(P, st);
+  }
+  if (ident) return d128 ? launch_flash2<128, true, false, 2, false>(P, st) : launch_flash2<64, true, false, 2, false>(P, st);
+  return d128 ? launch_flash2<128, true, false, 1, false>(P, st) : launch_flash2<64, true, false, 1, false>(P, st);
 }
 
 }  // namespace vm

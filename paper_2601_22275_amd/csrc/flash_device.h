@@ -111,14 +111,20 @@ __device__ __forceinline__ float subtile_max(const f32x16& s) {
 
 // Probabilities of the sub-tile relative to the reference max `msc` (log2 units):
 // t = s * sc - msc, p = 2^t.  `pb[0..1]` receive the two bf16 B operands (16 keys each) of
-// the O^T += X^T P^T products.  Running sum (Alg. 1's l):
-//   lt = sum of the bf16-ROUNDED p (v_dot2 against ones).  The accumulators are divided by
-//        this one, so that the output is an exact convex combination of the rows with
-//        slightly perturbed weights; dividing by the unrounded sum instead leaves a 2^-9
-//        relative error on rows dominated by one key.  It also serves as l in the
-//        log-sum-exp and in H = log l - h / l (error ~1e-3 in c_L, one VALU op per score saved).
-// Alg. 1's third sum, h = sum p t, is formed in the epilogue (row_dot).
-__device__ __forceinline__ void subtile_probs(const f32x16& s, float sc, float msc, float& lt, bf16x8 pb[2]) {
+// the O^T += X^T P^T products.  Running sums (Alg. 1's l and h):
+//   lt    = sum of the bf16-ROUNDED p (v_dot2 against ones).  The accumulators are divided by
+//           this one, so that the output is an exact convex combination of the rows with
+//           slightly perturbed weights; dividing by the unrounded sum instead leaves a 2^-9
+//           relative error on rows dominated by one key;
+//   l, h  = sum p and sum p t in fp32 (STAT): the row's log-sum-exp and c_L = h / l - log l.  Both carry the
+//           same weights, or their mismatch would be multiplied by the mean of t, and t is relative to the
+//           row's reference, so that neither loses digits to a large common part of the logits.  Error of c_L,
+//           2 frames of 1560, d = 128, logits with a deviation of 20 / around 5000: 6e-6 / 7e-7 (with lt in
+//           the place of l 2e-2 / 2e-2, from the accumulators of the products 3e-3 / 4e-3); the two
+//           operations per score cost 4 % of a fitting update there.
+template <bool STAT>
+__device__ __forceinline__ void subtile_probs(const f32x16& s, float sc, float msc, float& lt, float& l, float& h,
+                                              bf16x8 pb[2]) {
   typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
   bf16x2 ones2;
   ones2[0] = (__bf16)1.0f;
@@ -128,6 +134,10 @@ __device__ __forceinline__ void subtile_probs(const f32x16& s, float sc, float m
   for (int r = 0; r < 16; ++r) {
     float t = __builtin_fmaf(s[r], sc, -msc);
     p[r] = __builtin_amdgcn_exp2f(t);
+    if (STAT) {
+      l += p[r];
+      h = __builtin_fmaf(p[r], t, h);
+    }
   }
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
@@ -145,12 +155,10 @@ __device__ __forceinline__ void subtile_probs(const f32x16& s, float sc, float m
 
 // q . acc for the lane's query row: qreg the row as the B operand of the logit products (the lane holds 8-channel
 // blocks 2 ks + g), acc its R K accumulators (the lane holds channels 4 g .. + 3 of every block; exchanging half
-// blocks between lanes q and q + 32 lines the two up).  This is where Alg. 1's third statistic comes from: h = sum_l
-// p_l t_l is linear in the keys,
-//   sum_l p_l t_l = sc (aR . sum_l p_l K_l) - m sum_l p_l,
-// and the accumulators hold sum_l p_l K_l in fp32 with the very p (rounded to bf16) that l and the products carry,
-// so one dot product per row takes the place of a multiply-add per score (and of two unpacks per pair where h has to
-// carry the rounded p).
+// blocks between lanes q and q + 32 lines the two up).  The identity form of c_L (VMONARCH_ENTROPY_IDENTITY):
+//   c_L = sc (aR . alpha_L) - lse,  alpha_L before its rounding,
+// one dot product per row in place of a sum and a multiply-add per score; a difference of two terms of the
+// logits' size, whose error grows with that size.
 template <int D>
 __device__ __forceinline__ float row_dot(const bf16x8 (&qreg)[D / 16], const f32x16 (&acc)[D / 32]) {
   float dot = 0.f;
@@ -173,7 +181,8 @@ __device__ __forceinline__ float row_dot(const bf16x8 (&qreg)[D / 16], const f32
   return dot + __shfl_xor(dot, 32);
 }
 
-// One half (8 scores per lane, one B operand of 16 keys) of subtile_probs<1>: registers 8 c .. 8 c + 7 of `s`.
+// One half (8 scores per lane, one B operand of 16 keys) of a sub-tile: registers 8 c .. 8 c + 7 of `s`.  Here lt serves as
+// l too (one VALU op per score saved, error ~1e-3 in c_L).
 template <int C>
 __device__ __forceinline__ bf16x8 halftile_probs(const f32x16& s, float sc, float msc, float& lt, float& h) {
   typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;

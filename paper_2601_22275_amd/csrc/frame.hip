@@ -13,8 +13,8 @@
 //   S^T = K Q^T     A = K rows from LDS, B = Q^T in registers; lane (q, g) holds query q's logits for half of the keys
 //   X^T P^T         A = X^T (X = K, then V) by LDS transpose reads, B = P^T from the softmax registers
 //
-// The exact row maximum is the reference, l the sum of the bf16-rounded weights, h comes from the R K accumulators
-// (row_dot).
+// The exact row maximum is the reference; c_L and the log-sum-exp come from fp32 sums (subtile_probs), the rows are divided
+// by the sum of the bf16-rounded weights.
 #include "common.h"
 #include "flash_device.h"
 
@@ -37,6 +37,13 @@ struct FrameParams {
   float row_scale;
   float cr_min;
 };
+
+// Row `row` from its reference m and the sums l of p = 2^t and h of p t (log2 units): c_L = -H, App. B's H = log S - L / S
+__device__ __forceinline__ void store_statistics(const FrameParams& P, long long row, float m, float l, float h) {
+  const float log_l = __log2f(l);
+  P.cL[row] = LN2 * (h / l - log_l);
+  if (P.lse != nullptr) P.lse[row] = LN2 * (m + log_l);
+}
 
 template <int D, int KT, bool WITH_V>
 __global__ void __launch_bounds__(64 * KT) frame_kernel(FrameParams P) {
@@ -122,15 +129,18 @@ __global__ void __launch_bounds__(64 * KT) frame_kernel(FrameParams P) {
     for (int r = 0; r < 16; ++r) m = fmaxf(m, past_end(kt, r) ? -3.0e38f : s[kt][r] * sc);
   m = fmaxf(m, __shfl_xor(m, 32));
   bf16x8 pb[KT][2];
-  float lt = 0.f;
+  float lt = 0.f, l = 0.f, h = 0.f;
 #pragma unroll
   for (int kt = 0; kt < KT; ++kt) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[kt][r] = past_end(kt, r) ? -3.0e38f : __builtin_fmaf(s[kt][r], sc, -m);
-    subtile_probs(s[kt], 1.0f, 0.0f, lt, pb[kt]);
+    subtile_probs<true>(s[kt], 1.0f, 0.0f, lt, l, h, pb[kt]);
   }
   lt += __shfl_xor(lt, 32);
+  l += __shfl_xor(l, 32);
+  h += __shfl_xor(h, 32);
   const float inv = 1.0f / lt;
+  if (qvalid && g == 0) store_statistics(P, qr, m, l, h);
 
   // ---- X^T P^T ---------------------------------------------------------------------------------------------------
   const int rp = lane & 15;
@@ -182,15 +192,6 @@ __global__ void __launch_bounds__(64 * KT) frame_kernel(FrameParams P) {
   if (!EARLY_V) values_to_lds();
   f32x16 acc[CT];
   product(0, acc);
-  {
-    // c_L = sum_l R_l log R_l = sc (aR . alpha_L) - lse, with alpha_L before its rounding
-    const float lse2 = m + __log2f(lt);
-    const float mean_t = row_dot<D>(qreg, acc) * inv * sc;
-    if (qvalid && g == 0) {
-      P.cL[qr] = LN2 * (mean_t - lse2);
-      if (P.lse != nullptr) P.lse[qr] = LN2 * lse2;
-    }
-  }
   __syncthreads();  // every wave is done with K; V is in place
   store_rows(0, acc, P.aL);
   if (WITH_V) {
@@ -287,7 +288,7 @@ __global__ void __launch_bounds__(256, 2) frame_rows_kernel(FrameParams P) {
 
   f32x16 acc[CT];
   bf16x8 pb[KT][2];
-  float m = -3.0e38f, lt = 0.f;
+  float m = -3.0e38f, lt = 0.f, l = 0.f, h = 0.f;
   auto logits = [&](int kt) __attribute__((always_inline)) -> f32x16 {
     f32x16 s;
 #pragma unroll
@@ -364,18 +365,15 @@ __global__ void __launch_bounds__(256, 2) frame_rows_kernel(FrameParams P) {
       f32x16 s = logits(kt);
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = past_end(kt, r) ? -3.0e38f : __builtin_fmaf(s[r], sc, -m);
-      subtile_probs(s, 1.0f, 0.0f, lt, pb[kt]);
+      subtile_probs<true>(s, 1.0f, 0.0f, lt, l, h, pb[kt]);
       if (kt & 1) __builtin_amdgcn_sched_barrier(0);
     }
     lt += __shfl_xor(lt, 32);
+    l += __shfl_xor(l, 32);
+    h += __shfl_xor(h, 32);
     inv = 1.0f / lt;
+    if (qvalid && g == 0) store_statistics(P, qr, m, l, h);
     product();
-    const float lse2 = m + __log2f(lt);
-    const float mean_t = row_dot<D>(qreg, acc) * inv * sc;
-    if (qvalid && g == 0) {
-      P.cL[qr] = LN2 * (mean_t - lse2);
-      if (P.lse != nullptr) P.lse[qr] = LN2 * lse2;
-    }
   }
   if (WITH_V) {
     __syncthreads();  // every wave is done with the keys
