@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(64 * KT) frame_kernel(FrameParams P) {
   lt += __shfl_xor(lt, 32);
   l += __shfl_xor(l, 32);
   h += __shfl_xor(h, 32);
-  const float inv = 1.0f / lt;
+  const float inv = lt > 0.f ? 1.0f / lt : 0.f;  // no key with a finite logit: zeros, as in the streaming kernels
   if (qvalid && g == 0) store_statistics(P, qr, m, l, h);
 
   // ---- X^T P^T ---------------------------------------------------------------------------------------------------
@@ -371,7 +371,7 @@ __global__ void __launch_bounds__(256, 2) frame_rows_kernel(FrameParams P) {
     lt += __shfl_xor(lt, 32);
     l += __shfl_xor(l, 32);
     h += __shfl_xor(h, 32);
-    inv = 1.0f / lt;
+    inv = lt > 0.f ? 1.0f / lt : 0.f;
     if (qvalid && g == 0) store_statistics(P, qr, m, l, h);
     product();
   }
