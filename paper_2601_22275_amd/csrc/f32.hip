@@ -20,13 +20,14 @@
 #include <type_traits>
 
 #include "common.h"
+#include "f32_select.h"
 
 namespace vm {
 
 namespace {
 
-constexpr int BT = 32;                  // query rows of a tile, key rows of a tile, frames of a position
-constexpr int WAVES = 4;                // waves per workgroup of the blocked-softmax kernel
+constexpr int BT = kF32Tile;            // query rows of a tile, key rows of a tile, frames of a position
+constexpr int WAVES = kF32Waves;        // waves per workgroup of the blocked-softmax kernel
 constexpr float F32_LOWEST = -3.0e38f;  // reference of a row that has seen no key yet
 
 struct F32Params {
@@ -349,7 +350,7 @@ hipError_t launch_attend(F32Params& P, hipStream_t st) {
 template <bool OUT_K, bool OUT_V>
 hipError_t launch_attend_d(F32Params& P, int d, hipStream_t st) {
   const long long total = (long long)P.nproblems * P.nqt * P.nsplit;
-  if (total > 0x3fffffffLL) return hipErrorInvalidValue;
+  if (!f32_attend_fits((long long)P.nproblems * P.nsplit, P.nq)) return hipErrorInvalidValue;
   P.total = (int)total;
   if (d == 128) return launch_attend<128, OUT_K, OUT_V>(P, st);
   if (d == 64) return launch_attend<64, OUT_K, OUT_V>(P, st);
@@ -485,9 +486,10 @@ bool head_dim_ok(const Dims& dm) { return dm.d == 32 || dm.d == 64 || dm.d == 12
 
 }  // namespace
 
-// The calls these kernels take: the head dimensions above and tensors on 16-byte boundaries (rows then are too).
-bool f32_mfma_supported(const Dims& dm, std::initializer_list<const void*> tensors) {
-  return head_dim_ok(dm) && aligned16(tensors);
+// The calls the blocked-softmax kernel takes, `problems` of nq query rows: the head dimensions above, tensors on 16-byte
+// boundaries (rows then are too) and query tiles that one launch holds (a frame of one token is a tile too).
+bool f32_attend_supported(const Dims& dm, long long problems, long long nq, std::initializer_list<const void*> tensors) {
+  return head_dim_ok(dm) && aligned16(tensors) && f32_attend_fits(problems, nq);
 }
 
 hipError_t launch_r_update_f32(const float* aR, const float* cR, const float* k, const float* v, float* aL, float* cL,
@@ -499,7 +501,6 @@ hipError_t launch_r_update_f32(const float* aR, const float* cR, const float* k,
   P.nqt = (dm.b + BT - 1) / BT;
   P.nsplit = 1;
   P.tiles_per_split = P.nqt;
-  if ((long long)dm.BH * dm.T > 0x3fffffffLL) return hipErrorInvalidValue;
   P.nproblems = dm.BH * dm.T;
   P.row_scale = row_scale; P.cr_min = cr_min;
   return v != nullptr ? launch_attend_d<true, true>(P, dm.d, st) : launch_attend_d<true, false>(P, dm.d, st);
@@ -562,7 +563,7 @@ hipError_t launch_sink_average_f32(const float* q, const float* k, const float* 
 }
 
 bool l_update_f32_supported(const Dims& dm, std::initializer_list<const void*> tensors) {
-  return dm.T <= BT && f32_mfma_supported(dm, tensors);
+  return dm.T <= BT && head_dim_ok(dm) && aligned16(tensors) && grid_fits(dm.b, 64);
 }
 
 hipError_t launch_l_update_f32(const float* q, const float* aL, const float* cL, const float* y, float* aR, float* cR,
