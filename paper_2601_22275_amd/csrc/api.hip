@@ -241,7 +241,7 @@ template <>
 int r_update_any<float>(const float* aR, const float* cR, const float* k, const float* v, float* aL, float* cL,
                         float* y, float* lse, const Dims& dm, float row_scale, float cr_min, const Settings&,
                         hipStream_t st) {
-  hipError_t e = f32_attend_supported(dm, (long long)dm.BH * dm.T, dm.b, {aR, k, v, aL, y})
+  hipError_t e = f32_attend_supported(dm, v != nullptr, (long long)dm.BH * dm.T, dm.b, dm.b, {aR, k, v, aL, y})
                      ? launch_r_update_f32(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st)
                      : launch_r_update_generic<float>(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st);
   return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "r_update (f32) launch");
@@ -303,7 +303,7 @@ int first_frame_any(const E* q, const E* k, const E* v, E* out, float* lse, void
 template <>
 int first_frame_any<float>(const float* q, const float* k, const float* v, float* out, float* lse, void* scratch,
                            size_t scratch_bytes, const Dims& dm, int nrows, const int* rows, int, hipStream_t st) {
-  hipError_t e = f32_attend_supported(dm, dm.BH, nrows, {q, k, v, out})
+  hipError_t e = f32_attend_supported(dm, true, dm.BH, nrows, dm.N, {q, k, v, out})
                      ? launch_attend_rows_f32(q, k, v, out, lse, dm, nrows, rows, scratch, scratch_bytes, st)
                      : launch_first_frame_generic<float>(q, k, v, out, lse, dm, nrows, rows, st);
   return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "first_frame (f32) launch");
@@ -324,7 +324,7 @@ template <typename E>
 int sink_average_any(const E* q, const E* k, const E* v, E* out, const Dims& dm, hipStream_t st);
 template <>
 int sink_average_any<float>(const float* q, const float* k, const float* v, float* out, const Dims& dm, hipStream_t st) {
-  hipError_t e = f32_attend_supported(dm, dm.BH, dm.N, {q, k, v, out})
+  hipError_t e = f32_attend_supported(dm, true, dm.BH, dm.N, dm.b, {q, k, v, out})
                      ? launch_sink_average_f32(q, k, v, out, dm, st)
                      : launch_sink_average_generic<float>(q, k, v, out, dm, st);
   return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "sink_average (f32) launch");

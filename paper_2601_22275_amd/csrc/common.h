@@ -92,7 +92,8 @@ hipError_t launch_fill_head_prefix(float* p, float value, long long count, long 
                                    hipStream_t st);
 
 // f32.hip : float tensors on the fp32 matrix units (see the two predicates)
-bool f32_attend_supported(const Dims& dm, long long problems, long long nq, std::initializer_list<const void*> tensors);
+bool f32_attend_supported(const Dims& dm, bool with_v, long long problems, long long nq, long long nk,
+                          std::initializer_list<const void*> tensors);
 hipError_t launch_r_update_f32(const float* aR, const float* cR, const float* k, const float* v, float* aL, float* cL,
                                float* y, float* lse, const Dims& dm, float row_scale, float cr_min, hipStream_t st);
 // rows / nrows as in launch_first_frame_flash; scratch (may be null) lets a call with few rows split the keys

@@ -486,10 +486,13 @@ bool head_dim_ok(const Dims& dm) { return dm.d == 32 || dm.d == 64 || dm.d == 12
 
 }  // namespace
 
-// The calls the blocked-softmax kernel takes, `problems` of nq query rows: the head dimensions above, tensors on 16-byte
-// boundaries (rows then are too) and query tiles that one launch holds (a frame of one token is a tile too).
-bool f32_attend_supported(const Dims& dm, long long problems, long long nq, std::initializer_list<const void*> tensors) {
-  return head_dim_ok(dm) && aligned16(tensors) && f32_attend_fits(problems, nq);
+// The calls the blocked-softmax kernel takes, `problems` of nq query rows and nk keys: the head dimensions above, tensors on
+// 16-byte boundaries (rows then are too), query tiles that one launch holds (a frame of one token is a tile too), and keys
+// enough that it is the faster one.
+bool f32_attend_supported(const Dims& dm, bool with_v, long long problems, long long nq, long long nk,
+                          std::initializer_list<const void*> tensors) {
+  return head_dim_ok(dm) && aligned16(tensors) && f32_attend_fits(problems, nq) &&
+         !f32_few_keys(dm.d, with_v, problems, nq, nk);
 }
 
 hipError_t launch_r_update_f32(const float* aR, const float* cR, const float* k, const float* v, float* aL, float* cL,
