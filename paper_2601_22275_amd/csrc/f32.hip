@@ -113,6 +113,12 @@ __global__ void __launch_bounds__(64 * WAVES) f32_attend_kernel(F32Params P) {
       rk[i] = *reinterpret_cast<const f32x4*>(kb + row * D + ld_col);
       if (OUT_V) rv[i] = *reinterpret_cast<const f32x4*>(vb + row * D + ld_col);
     }
+    if (OUT_V && tile * BT + BT > P.nk) {
+      // ... whose values are zeros: an infinite value of the last row times weight zero would be NaN
+#pragma unroll
+      for (int i = 0; i < NL; ++i)
+        if (tile * BT + i * RPL + ld_row >= P.nk) rv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   };
   auto to_lds = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -443,9 +449,12 @@ __global__ void __launch_bounds__(64) f32_temporal_kernel(const float* __restric
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     if (8 * (r >> 2) + (r & 3) >= T) continue;  // neither of the two frames of this step exists
-    const int f = min(8 * (r >> 2) + 4 * g + (r & 3), T - 1);
+    const int f = 8 * (r >> 2) + 4 * g + (r & 3);
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[ct] = mfma(src[f * RS + 32 * ct + ql], u[r], acc[ct]);
+    for (int ct = 0; ct < CT; ++ct) {
+      const float x = src[min(f, T - 1) * RS + 32 * ct + ql];
+      acc[ct] = mfma(f < T ? x : 0.f, u[r], acc[ct]);  // (not a copy: infinite values times weight zero)
+    }
   }
   // staged over alpha_L (read for the last time above) and written as whole rows
   wave_lds_fence();

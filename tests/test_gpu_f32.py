@@ -93,3 +93,25 @@ def test_listed_rows(env, d):
         ref = O.softmax_attention(q64, k64, v64, 1.0 / math.sqrt(d))
         assert U.rel_l2(out[h][valid], ref[valid]) <= TOL
         assert np.all(out[h][rest] == 3.0)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("T,b", [(3, 33), (7, 40), (29, 1)])
+def test_infinite_value_in_the_last_row(env, T, b, d):
+    """The rows that fill a tile past the last key or frame carry weight zero, and no infinity to multiply it with."""
+    torch, binding, dev = env
+    rng = np.random.default_rng(T + b + d)
+    q, k, v = (U.random_bits(rng, (T * b, d), 0.5, False) for _ in range(3))
+    v[b - 1::b, 3] = np.inf      # the last token of every frame ...
+    v[(T - 1) * b:, 5] = -np.inf  # ... and every token of the last frame
+    tq, tk, tv = (U.to_device([x], torch, dev) for x in (q, k, v))
+    _, _, y = binding.r_update(tq, None, tk, tv, T, 1, b, 0.1, 0.1)
+    out = binding.l_update(tq, tk, torch.zeros((1, 1, T * b), device=dev), tv, T, 1, b, 0.1)
+    rows = binding.recompute_rows(tq, tk, tv, T, 1, b, torch.zeros_like(tq), 0, 2)
+    y, out, rows = (U.from_device(x)[0] for x in (y, out, rows))
+    frame, position = np.divmod(np.arange(T * b), b)
+    assert np.all(np.isposinf(y[:, 3])) and np.all(np.isneginf(y[frame == T - 1, 5]))
+    assert np.all(np.isposinf(out[position == b - 1, 3])) and np.all(np.isneginf(out[:, 5]))
+    assert np.all(np.isposinf(rows[:2, 3])) and np.all(np.isneginf(rows[:2, 5]))
+    rest = [c for c in range(d) if c not in (3, 5)]
+    assert np.all(np.isfinite(y[:, rest])) and np.all(np.isfinite(out[:, rest])) and np.all(np.isfinite(rows[:2, rest]))
