@@ -312,8 +312,8 @@ __global__ void __launch_bounds__(64 * WAVES) f32_attend_kernel(F32Params P) {
 
 // Sums of the key ranges of one query row, 64 threads: out = sum_s o_s e^(m_s - M) / sum_s S_s e^(m_s - M).
 __global__ void __launch_bounds__(64) f32_merge_kernel(const float* __restrict__ part_o, const float2* __restrict__ part_ms,
-                                                       float* __restrict__ out, float* __restrict__ lse, int nsplit,
-                                                       int nq, int nproblems, long long rows_per_problem, int d) {
+                                                       float* __restrict__ out, int nsplit, int nq, int nproblems,
+                                                       long long rows_per_problem, int d) {
   const int r = blockIdx.x, prob = blockIdx.y;
   const long long step = (long long)nproblems * nq;
   const long long row = (long long)prob * nq + r;
@@ -326,7 +326,6 @@ __global__ void __launch_bounds__(64) f32_merge_kernel(const float* __restrict__
     for (int s = 0; s < nsplit; ++s) o += part_o[(s * step + row) * d + c] * expf(part_ms[s * step + row].x - M);
     out[((long long)prob * rows_per_problem + r) * d + c] = o / S;
   }
-  if (lse != nullptr && threadIdx.x == 0) lse[(long long)prob * rows_per_problem + r] = M + logf(S);
 }
 
 template <int D, bool OUT_K, bool OUT_V, int KW>
@@ -536,7 +535,7 @@ hipError_t launch_attend_rows_f32(const float* q, const float* k, const float* v
   const long long tiles = (dm.N + BT - 1) / BT;
   const long long items = (long long)dm.BH * P.nqt;
   long long ns = 1;
-  if (rows == nullptr && scratch != nullptr) {
+  if (rows == nullptr && lse == nullptr && scratch != nullptr) {
     ns = (dm.d == 128 ? 256 : 512) / items;
     ns = ns < tiles / 8 ? ns : tiles / 8;
     const long long per_range = (long long)dm.BH * nrows * (dm.d * (long long)sizeof(float) + (long long)sizeof(float2));
@@ -553,8 +552,8 @@ hipError_t launch_attend_rows_f32(const float* q, const float* k, const float* v
   }
   hipError_t e = launch_attend_d<false, true>(P, dm.d, st);
   if (e != hipSuccess || ns == 1) return e;
-  hipLaunchKernelGGL(f32_merge_kernel, dim3(nrows, dm.BH), dim3(64), 0, st, P.part_o, P.part_ms, out, lse, P.nsplit, nrows,
-                     dm.BH, dm.N, dm.d);
+  hipLaunchKernelGGL(f32_merge_kernel, dim3(nrows, dm.BH), dim3(64), 0, st, P.part_o, P.part_ms, out, P.nsplit, nrows, dm.BH,
+                     dm.N, dm.d);
   return hipGetLastError();
 }
 
