@@ -1,6 +1,6 @@
 """The four forms of the bf16 backward (with and without a gradient through the entropy, with and without row scales; with
 neither the dK, dV pass takes its plain form) at the edges of its 32-row sub-tiles, 64-row tiles, the three-tile LDS rotation
-and the 256-row owner blocks, against the CPU oracle on the forward results the library itself gave.
+and the owner blocks (128 rows at d = 64, 256 at d = 128), and with more blocks than fill the card once, against the CPU oracle on the forward results the library itself gave.
 
 Tolerance: P and dS enter the products rounded to bf16 (2^-9 relative each), dS = P (dP - D) loses up to two more bits where
 dP and D cancel (the inputs are random, dP - D is of dP's size in most elements), the results are rounded once more:
@@ -27,7 +27,7 @@ def env():
 
 @pytest.mark.parametrize("with_dh,with_cr", [(False, False), (False, True), (True, False), (True, True)])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("b", [2, 31, 32, 33, 63, 64, 65, 129, 192, 193, 255, 256, 257, 289, 513])
+@pytest.mark.parametrize("b", [2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 192, 193, 255, 256, 257, 289, 384, 385, 513])
 def test_backward_forms(env, b, d, with_dh, with_cr):
     torch, binding, dev = env
     T, rng = 2, np.random.default_rng(11 * b + d)
@@ -51,3 +51,33 @@ def test_backward_forms(env, b, d, with_dh, with_cr):
         ref = O.entropy_attention_backward(q[j], k[j], v[j], o[j], do[j], l64[j, :, 0], h64[j, :, 0], dh, s / c)
         for name, g, r in zip(("dq", "dk", "dv"), got, ref):
             assert U.rel_l2(g[j], r) <= 1e-2, name
+
+
+@pytest.mark.parametrize("with_dh,with_cr", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_more_blocks_than_the_card_holds(env, d, with_dh, with_cr):
+    """3 heads x 100 frames of 129 tokens: 600 owner blocks at d = 64, two of which share a compute unit.  The first, a middle and
+    the last frame against the oracle, every frame against a second call."""
+    torch, binding, dev = env
+    T, b, heads, rng = 100, 129, 3, np.random.default_rng(d)
+    Q, K, V, dO = ([U.random_bits(rng, (T * b, d), 1.0, True) for _ in range(heads)] for _ in range(4))
+    tq, tk, tv, tdo = (U.to_device(x, torch, dev) for x in (Q, K, V, dO))
+    cR = (0.03 + 1.5 * rng.random((heads, T * b))).astype(np.float32) if with_cr else None
+    dH = rng.normal(size=(heads, T * b)).astype(np.float32) if with_dh else None
+    tcr, tdh = (None if x is None else torch.from_numpy(x).to(dev).view(1, heads, -1) for x in (cR, dH))
+    s, cr_min = 1.0 / math.sqrt(d), 0.1
+    _, cL, y, lse = binding.r_update_lse(tq, tcr, tk, tv, T, 1, b, s, cr_min)
+    H = (-cL).contiguous()
+    got = binding.entropy_attention_bwd(tq, tcr, tk, tv, y, tdo, lse, H, tdh, T, 1, b, s, cr_min)
+    again = binding.entropy_attention_bwd(tq, tcr, tk, tv, y, tdo, lse, H, tdh, T, 1, b, s, cr_min)
+    assert all(torch.equal(x, w) for x, w in zip(got, again))
+    got = [U.from_device(x) for x in got]
+    y, lse, H = (U.from_device(x).astype(np.float64) for x in (y, lse, H))
+    for h, j in ((0, 0), (1, 51), (2, T - 1)):
+        rows = slice(j * b, (j + 1) * b)
+        q, k, v, do = (U.to_f64(x[h][rows]) for x in (Q, K, V, dO))
+        c = np.ones(b) if cR is None else np.maximum(cR[h][rows].astype(np.float64), cr_min)
+        dh = None if dH is None else dH[h][rows].astype(np.float64)
+        ref = O.entropy_attention_backward(q, k, v, y[h][rows], do, lse[h][rows], H[h][rows], dh, s / c)
+        for name, g, r in zip(("dq", "dk", "dv"), got, ref):
+            assert U.rel_l2(g[h][rows], r) <= 1e-2, name
