@@ -367,13 +367,27 @@ def main() -> int:
     roofline = None
     hbm_phase = None
     variant = binding.get_flash_variant()
-    fused = bf16 and d in (64, 128) and args.entropy == "online" and binding.get_fused_apply() and variant == 0
+    online = args.entropy == "online"
+    fused = bf16 and d in (64, 128) and online and binding.get_fused_apply() and variant == 0
+
+    def frame_kernel(with_v):
+        """The short-frame kernel that takes an R-update of this workload, or None (the library's rule for variant 2)."""
+        if not bf16 or d not in (64, 128) or variant != 2 or not online or (with_v and not binding.get_fused_apply()):
+            return None
+        if b <= ((256 if d == 64 else 192) if with_v else 224):
+            return "frame_kernel"
+        if d == 64 and 256 < b <= (384 if with_v else 352) and BH * T > 128:
+            return "frame_rows_kernel"
+        return None
     if "r_update_last" in phases:
         # dominant kernel (the longest single launch of a call): the R-update of the last sweep, which forms
         # the logits, R K (alpha_L), c_L and R V (y) in one launch: three b x b x d products per frame.
         # (With the two-pass form the phase is two launches.)
         fl, t_ms = 6.0 * BH * T * b * b * d, phases["r_update_last"]
-        if bf16 and d in (64, 128) and variant in (1, 2):
+        short = frame_kernel(True)
+        if short:
+            kern, what = short, f"{short} (last R-update of short frames: logits, R K, c_L and R V in one launch)"
+        elif bf16 and d in (64, 128) and variant in (1, 2):
             kern, what = "flash2_kernel", "flash2_kernel (last R-update: logits, R K, c_L and R V in one launch, one wave per SIMD)"
         elif fused:
             kern, what = "flash_kv_kernel", "flash_kv_kernel (last R-update: logits, R K, c_L and R V in one launch)"
@@ -389,7 +403,8 @@ def main() -> int:
             # the fitting sweeps' R-update (logits + R K), one launch each
             fl2, t2 = 4.0 * BH * T * b * b * d, phases["r_update"]
             two_tiles = variant == 1 or (variant == 2 and d == 64)
-            roofline["fitting_r_update"] = {"kernel": "flash2_kernel (logits + R K)" if two_tiles else "flash_kernel (logits + R K)",
+            fit = frame_kernel(False) or ("flash2_kernel" if two_tiles else "flash_kernel")
+            roofline["fitting_r_update"] = {"kernel": f"{fit} (logits + R K)",
                                             "flops_per_launch": fl2,
                                             "ms_per_launch": t2, "achieved": fl2 / (t2 * 1e-3) / 1e12,
                                             "frac": fl2 / (t2 * 1e-3) / 1e12 / BF16_MFMA_PEAK_TFLOPS}

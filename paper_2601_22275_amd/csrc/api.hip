@@ -33,8 +33,8 @@ int g_cr_control = VMONARCH_CONTROL_NONE;
 int g_cl_control = VMONARCH_CONTROL_NONE;
 float g_cl_value = NAN;  // NaN: -log(b), the c_L of a uniform row of R
 int g_entropy_mode = VMONARCH_ENTROPY_ONLINE;
-// which bf16 MFMA kernel runs an R-update: 0 the two-waves-per-SIMD kernels (flash.hip, flash_kv.hip; the faster
-// ones as measured on MI355X), 1 the one-wave-per-SIMD kernel with two query tiles per wave (flash2.hip)
+// which bf16 MFMA kernel runs an R-update: 0 the two-waves-per-SIMD kernels (flash.hip, flash_kv.hip), 1 the
+// one-wave-per-SIMD kernel with two query tiles per wave (flash2.hip), 2 the one measured faster (see r_update_any)
 int g_flash_variant = 2;
 
 std::mutex g_ws_mutex;
@@ -251,10 +251,13 @@ int r_update_any<bf16_t>(const bf16_t* aR, const float* cR, const bf16_t* k, con
                          bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min, const Settings& cfg,
                          hipStream_t st) {
   hipError_t e;
-  // variant 2: every update on the kernel that was measured faster for it.  Short frames (see frame_supported) on the kernel
-  // that takes a whole frame per workgroup.  Otherwise with values the two-tile kernel, unless a frame has at most 128
-  // tokens (its 256-row query blocks would be mostly padding; the wave-pair kernel's hold 128); without values the two-tile
-  // kernel at d = 64, the one-tile kernel at d = 128.
+  // variant 2: every update on the kernel that was measured faster for it.  Short frames (see frame_supported) on the kernels
+  // that take a frame, or 128 rows of one, per workgroup; they form c_L online and y in the same launch, so calls that choose
+  // the identity form or two launches stay on the streaming kernels.  Those: with values the two-tile kernel, unless a frame
+  // has at most 128 tokens (its 256-row query blocks would be mostly padding; launch_r_update_flash takes the one-tile kernel
+  // in two launches for such calls; the wave-pair kernel runs in variant 0 only); without values the two-tile kernel at
+  // d = 64, the one-tile kernel at d = 128 (130 frames of 300 / 1000 tokens 28.6 / 105 us, on the two-tile kernel 32.1 / 107; level at
+  // 1456 .. 2048; 252 of 3600 1731 / 1685).
   const bool two_tiles = cfg.flash_variant == 1 ||
                          (cfg.flash_variant == 2 && (v != nullptr ? dm.b > 128 : dm.d == 64));
   const bool short_frame = cfg.flash_variant == 2 && cfg.entropy_mode == VMONARCH_ENTROPY_ONLINE &&

@@ -22,9 +22,11 @@
 // much LDS time as the operand of an MFMA, and LDS is the narrowest path here (an MFMA's worth of operand
 // per MFMA already).  Without dH and c_R (row scale the same for all rows) sc2 and b are constants, two of
 // the four arrays and a third of the vector arithmetic drop out: that is the PLAIN form.
-// Measured, all gradients: 12 x 21 frames of 1560, d = 128, plain form: dQ 633 -> 575 us (819 TFLOP/s), dV + dK 467 + 742
-// -> 800 us (785 TFLOP/s), statistics 36 us -> inside dQ; 10 x 9 frames of 943, d = 64, general form: 66 + 59 + 76 + 8
-// -> 62 + 80 us (eight waves per block; see waves below).  The bound is the matrix pipe under its power limit (a large library product reaches 1150 TFLOP/s).
+// Measured inside back-to-back calls, three passes and a statistics kernel -> two passes: 12 x 21 frames of 1560, d =
+// 128, plain form: dQ 506 -> 462 us (1019 TFLOP/s issued), dV + dK 381 + 608 -> 603 us (1042 TFLOP/s), statistics 36 us
+// -> inside dQ; 10 x 9 frames of 943, d = 64, general form: 57 + 53 + 67 + 7 -> 42 + 60 us (739, 684 TFLOP/s).  At d =
+// 128 the matrix pipes are busy for 0.54 of the cycles and two waves per SIMD (all that the registers allow) do not
+// fill the rest; a large library product reaches 1150 TFLOP/s.  At d = 64 vector work per score weighs twice as much.
 #include <type_traits>
 
 #include "common.h"

@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(64 * NW, WAVES) flash_kernel(FlashParams P) {
   static_assert(ENT == 0 || OUT_K, "c_L belongs to the pass over K");
   static_assert(BIAS == 0 || (!SPLIT && ENT == 0), "the biased modes are whole-range passes without entropy");
   // The biased pass over K without entropy is the first of the temporal factor's two (launch_l_update_flash): only the
-  // rows' log-sum-exp is wanted, so the products (half of its matrix and LDS work) are left out: 97 -> 60 us for 12 x 64
+  // rows' log-sum-exp is wanted, so the products (half of its matrix and LDS work) are left out: 86 -> 58 us for 12 x 64
   // problems of 512 x 512 at d = 64.
   constexpr bool LSE_ONLY = BIAS == 1 && OUT_K;
 
@@ -669,7 +669,7 @@ bool temporal_flash_supported(const Dims& dm) { return (dm.d == 128 || dm.d == 6
 namespace {
 // One of the temporal factor's product passes.  Its key loops are short (T / 64 tiles), so what surrounds the loop (first
 // tiles and key terms from HBM, stores) and the wait for tiles count; at d = 64 two workgroups on a compute unit hide it from
-// each other if a wave makes do with 128 registers: 12 x 64 problems of 512: 97 -> 75 us fitting, 111 -> 91 us last; 6 x 64
+// each other if a wave makes do with 128 registers: 12 x 64 problems of 512: 86 -> 72 us fitting, 98 -> 85 us last; 6 x 64
 // of 1000: 162 -> 148 us last.  A launch that does not give every unit two, or whose key terms leave LDS for one (from about
 // 4000 frames), keeps all registers (2 x 24 of 512: 16.1 against 17.2 us).
 template <int D, bool OUT_K, bool OUT_V, int BIAS>

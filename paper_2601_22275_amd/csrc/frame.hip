@@ -6,8 +6,9 @@
 // block's dependent chain.  One workgroup therefore takes one frame with exactly KT waves, 32 queries each: no wave
 // idles on padding (the streaming kernels' blocks of 256 or 128 query rows are padding for the most part here), a block
 // needs 4 KT .. 16 KT KB of LDS, so that many frames are in flight on a compute unit, and all of a frame's loads are
-// issued before the first is waited for.  Fitting / last update in us, before -> now, 12 heads, d = 64: 32 frames of 32 tokens
-// (one block's chain) 9.8 / 11.0 -> 4.7 / 5.0; 512 frames of 64 80 / 106 -> 25 / 40 (5.9 / 6.3 TB/s of the tensors).
+// issued before the first is waited for.  Fitting / last update in us, streaming kernels -> this one, 12 heads, d = 64: 32 frames
+// of 32 tokens (one block's chain) 7.9 / 10.4 -> 4.0 / 5.0; 512 frames of 64 70 / 100 -> 25 / 40 (6.0 / 6.3 TB/s of
+// the tensors, which fit the last-level cache there: more than the 5.2 TB/s of a copy through HBM).
 // Contractions and register layouts are the streaming kernels' (flash2.hip):
 //
 //   S^T = K Q^T     A = K rows from LDS, B = Q^T in registers; lane (q, g) holds query q's logits for half of the keys
@@ -402,19 +403,23 @@ hipError_t launch_rows(const FrameParams& P, unsigned frames, hipStream_t st) {
 
 }  // namespace
 
-// Where the whole-frame kernel is the faster one, by sweeps of b = 24 .. 256 with 384 frames and with 390,000 tokens.  Without values up to
-// 224 tokens: many frames 29 against 53 us at 128 tokens (d = 64), level from 161 on (50 / 49 us at 192), few frames
-// 13 / 15 us there; at d = 128 59 / 97 us at 128 tokens, 101 / 112 at 224.  With values up to 256 tokens at d = 64
-// (66 / 89 us there) and 192 at d = 128 (142 / 174 us): with a seventh tile of logits that one spills and is level.
+// Where the whole-frame kernel is the faster one, by sweeps of b = 1 .. 256 with 2 .. 3000 frames.  Without values up
+// to 224 tokens: many frames 29 against 53 us at 128 tokens (d = 64), level from 161 on (50 / 49 us at 192), few frames
+// 13 / 15 us there; at d = 128 59 / 97 us at 128 tokens, 101 / 112 at 224.  With values up to 256 tokens at d = 64 (66
+// / 89 us there) and 192 at d = 128 (142 / 174 us): with a seventh tile of logits that one spills and is level.
 bool frame_supported(const Dims& dm, bool with_v) {
   if (dm.d != 64 && dm.d != 128) return false;
   return dm.b <= (!with_v ? 224 : dm.d == 64 ? 256 : 192) && (long long)dm.BH * dm.T <= 0x7fffff;
 }
 
-// Where the 128-row blocks are faster (sweeps of 193 .. 512 tokens, 128 .. 2000 frames): d = 64, up to 384 tokens with values
-// (see the kernel), 352 without (1216 frames of 323 87 -> 81 us; level at 384).  From 448 tokens on, and at d = 128, where the keys
-// leave room for one block on a unit, they lose (448, d = 64, without values: 71 -> 88 us).  Up to 128 frames the streaming
-// kernel's two blocks a frame are one round of the 256 compute units, and it is level or ahead (19 against 20 us).
+// Where the 128-row blocks are taken (sweeps of 193 .. 512 tokens, 128 .. 2000 frames): d = 64, up to 384 tokens with
+// values (see the kernel), 352 without (1216 frames of 323 87 -> 81 us; level at 384).  From 448 tokens on they lose
+// (448, d = 64, without values: 71 -> 88 us).  Up to 128 frames the streaming kernel's two blocks a frame are one round
+// of the 256 compute units; the two kernels are then within 4 % with values (19 / 20 us) and the blocks 4 .. 8 % ahead
+// without (257 tokens 13.2 / 12.2 us): one line for both.  At d = 128 the keys leave room for one block on a unit: from
+// 257 tokens on they lose nearly everywhere (257, 128 frames: 15.7 / 22.9 us, with values 25.9 / 32.0); at 193 and 256
+// tokens they win while the blocks are one round (128 frames, with values: 22.0 / 16.6 and 23.3 / 18.4 us) and lose
+// beyond (256 frames: 26.6 / 32.4 and 28.9 / 33.9), which is left alone.
 bool frame_rows_supported(const Dims& dm, bool with_v) {
   const long long frames = (long long)dm.BH * dm.T;
   return dm.d == 64 && dm.b > 256 && dm.b <= (with_v ? 384 : 352) && frames > 128 && frames <= 0x7fffff;
