@@ -3,8 +3,9 @@ CPU oracle and against the streaming kernels (flash variant 1), which form the s
 
 Tolerance: inputs, outputs and the softmax weights are bf16 (half an ulp is 2^-9 relative); alpha_L and y carry one rounding
 of every weight and one of the result, both random: sqrt(2) 2^-9 = 2.8e-3 in the relative norm at most.  Against the
-oracle 4e-3 is allowed, between the kernels 6e-3.  c_L and the log-sum-exp are float32 sums over weights rounded to bf16: the sum of up
-to 256 weights keeps at most 2^-9 of relative error, the logarithm turns that into 2^-9 absolute; 2^-8 is allowed."""
+oracle 4e-3 is allowed, between the kernels 6e-3.  c_L and the log-sum-exp are held to 2^-8, what sums over weights
+rounded to bf16 would keep (2^-9 relative, which the logarithm makes absolute, and as much again); the bound of the
+float32 sums that they are is in test_gpu_row_statistics.py."""
 import math
 
 import numpy as np
