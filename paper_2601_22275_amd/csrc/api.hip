@@ -256,10 +256,11 @@ int r_update_any<bf16_t>(const bf16_t* aR, const float* cR, const bf16_t* k, con
   // the identity form or two launches stay on the streaming kernels.  Those: with values the two-tile kernel, unless a frame
   // has at most 128 tokens (its 256-row query blocks would be mostly padding; launch_r_update_flash takes the one-tile kernel
   // in two launches for such calls; the wave-pair kernel runs in variant 0 only); without values the two-tile kernel at
-  // d = 64, the one-tile kernel at d = 128 (130 frames of 300 / 1000 tokens 28.6 / 105 us, on the two-tile kernel 32.1 / 107; level at
-  // 1456 .. 2048; 252 of 3600 1731 / 1685).
+  // d = 64 and, at d = 128, for frames of more than 448 tokens (one-tile / two-tile kernel, 130 frames of 300 28.5 / 29.2, 400
+  // 35.6 / 36.3, 512 40.8 / 40.4, 1000 103.5 / 99.5, 1560 194.9 / 183.7 us; 252 of 3584 1602 / 1455: short key loops leave the
+  // single wave of a SIMD its start and end to wait for).
   const bool two_tiles = cfg.flash_variant == 1 ||
-                         (cfg.flash_variant == 2 && (v != nullptr ? dm.b > 128 : dm.d == 64));
+                         (cfg.flash_variant == 2 && (v != nullptr ? dm.b > 128 : dm.d == 64 || dm.b > 448));
   const bool short_frame = cfg.flash_variant == 2 && cfg.entropy_mode == VMONARCH_ENTROPY_ONLINE &&
                            (v == nullptr || cfg.fused_apply != 0) &&
                            (frame_supported(dm, v != nullptr) || frame_rows_supported(dm, v != nullptr));

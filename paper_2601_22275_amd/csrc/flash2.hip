@@ -14,8 +14,7 @@
 //   S^T = K Q^T     A = K rows read from LDS (ds_read_b128), B = Q^T held in registers.  One A
 //                   operand serves both query tiles: half the LDS bytes per MFMA of a
 //                   one-tile wave.  In the result lane (q, g) holds the logits of query q for
-//                   16 of the 32 keys, so max, sum and entropy are per-lane scalars and need
-//                   one exchange with lane^32 for the max only.
+//                   16 of the 32 keys, so the sums are per-lane scalars.
 //   O^T += X^T P^T  A = X^T (X = K for alpha_L, X = V for y) fetched from the same row-major
 //                   LDS tile with the LDS transpose read (ds_read_b64_tr_b16), again shared by
 //                   both query tiles; B = P^T, the S^T accumulator converted to bf16 in place.
@@ -35,20 +34,22 @@ namespace {
 constexpr int W2 = 4;             // waves per workgroup, one per SIMD
 constexpr int Q2 = 2;             // 32-query tiles per wave
 constexpr int BQ2 = 32 * Q2 * W2;  // query rows per workgroup
-// A reference max moves only when a row maximum outgrew it by 2^32.  The probabilities are formed in fp32 and
-// rounded to bf16, which has fp32's exponent range, and the sums are fp32, so a stale reference costs the
-// outputs no precision until 2^t nears overflow.  c_L needs one precaution: the sum h of p t and the sum l of p
-// must weigh every key alike, or their mismatch (about 1e-3 relative when l holds the bf16-rounded p and h the
-// unrounded ones) is multiplied by the mean of t, which a stale reference lets grow to 32; both carry the
-// UNROUNDED p here, beside the rounded sum that the outputs are divided by.  Moving a reference is expensive in this
-// kernel (the accumulators sit in accumulation registers and pass through ordinary ones to be rescaled), and in the
-// last sweep's update, where c_R sharpens some rows tenfold, a margin of 2^8 would move one in most steps.
-constexpr float RESCALE_TH2 = 32.0f;
-// Where a moving reference is put: this far (log2 units) above the row maximum that moved it, the first one
-// included.  Any reference gives the same results (the sums and the accumulators carry the common factor
-// 2^-reference, and fp32 / bf16 have exponent range to spare: the largest probability of a row is then 2^-64, keys
-// more than 2^-62 below the row maximum flush to zero); a high one makes later moves rare, which matters where
-// attention is sharp (logits many times their usual spread: row maxima then jump by more than 2^32 from tile to tile).
+// No running row maximum is kept.  A row's reference comes from the maximum of its first 32 logits, and any reference gives the
+// same results: the sums and the accumulators carry the common factor 2^-reference, the weights are formed in fp32 and rounded
+// to bf16, which has fp32's exponent range, so a stale reference costs the outputs no precision until 2^t nears overflow.  What
+// would overflow shows in the sums: a sub-tile whose weights add up to more than this in any lane is formed again, before its
+// products, against references from its own row maxima (`redo`).  The maxima and their bookkeeping were 18 % of the vector
+// instructions, which bound the loop (busy 0.85 of the cycles at d = 64 without values).  Measured, R-update without / with
+// values: 12 x 32 frames of 2048, d = 64: 472 -> 441 / 713 -> 654 us (934, 945 TFLOP/s); 12 x 21 of 1536, d = 128: 317 -> 298 /
+// 453 -> 431 us (1021, 1060).
+// c_L needs one precaution: the sum h of p t and the sum l of p must weigh every key alike, or their mismatch (about 1e-3
+// relative when l holds the bf16-rounded p and h the unrounded ones) is multiplied by the mean of t, which a stale reference
+// lets grow to 32; both carry the UNROUNDED p here, beside the rounded sum that the outputs are divided by.
+constexpr float STEP_MAX2 = 4294967296.0f;  // 2^32
+// Where a reference is put: this far (log2 units) above the row maximum, the first one included.  The largest probability of a
+// row is then 2^-64 (keys more than 2^-62 below the row maximum flush to zero), and a new reference is needed only where the
+// maximum grows by 2^92 or more: moving one passes the accumulators through ordinary registers and forms a sub-tile twice, and
+// attention can be sharp (c_R raises logits up to tenfold; row maxima then jump by more than 2^32 from tile to tile).
 constexpr float HEADROOM2 = 64.0f;
 
 __device__ __forceinline__ uint32_t avg_bf16x2(uint32_t a, uint32_t b) {
@@ -283,8 +284,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   // ---- one step = one 32-key sub-tile, as a fixed sequence of groups ------------------------
   // Software pipeline over sub-tiles n = 0, 1, ...  Step n carries, in the one wave,
   //   matrix:  S^T of sub-tile n+1 (both query tiles), then O^T += X^T P^T of sub-tile n-1;
-  //   vector:  p = 2^t, running sums and bf16 P^T of sub-tile n, then the row maxima of sub-tile
-  //            n+1 (which decide whether the references move at step n+1).
+  //   vector:  p = 2^t, sums and bf16 P^T of sub-tile n, whose sums then say whether its references held.
   // A group is the two MFMAs (query tile 0, query tile 1) that share one A operand from LDS: KS groups of
   // logits, then 2 CT NX groups of products in the order (16-key half c, channel tile ct, product x).  The
   // operand of group i + PF is requested while group i runs (a ring of four operand registers; NG is a
@@ -339,6 +339,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   // own (the stages that share a slot then belong to different pairs and issue back to back), so that a single
   // wave does not sit out the latency of its own chain.
   float tq[2][2], pq[2][2];  // in flight between the stages, by parity of the pair
+  float ltstep[Q2], lstep[Q2], hstep[Q2];  // this step's part of the sums
   auto score_scale = [&](auto kc, f32x16 (&scur)[Q2]) __attribute__((always_inline)) {
     constexpr int K = decltype(kc)::value;  // 0 .. 15
     constexpr int qt = K & 1;
@@ -359,42 +360,86 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     pr[0] = (__bf16)pq[K & 1][0];  // round to nearest even; the pair is one v_cvt_pk_bf16_f32
     pr[1] = (__bf16)pq[K & 1][1];
     if (ENT == 1) {
-      lsum[qt] += pq[K & 1][0];
-      hsum[qt] = __builtin_fmaf(pq[K & 1][0], tq[K & 1][0], hsum[qt]);
-      lsum[qt] += pq[K & 1][1];
-      hsum[qt] = __builtin_fmaf(pq[K & 1][1], tq[K & 1][1], hsum[qt]);
+      lstep[qt] = j == 0 ? pq[K & 1][0] : lstep[qt] + pq[K & 1][0];
+      hstep[qt] = j == 0 ? pq[K & 1][0] * tq[K & 1][0] : __builtin_fmaf(pq[K & 1][0], tq[K & 1][0], hstep[qt]);
+      lstep[qt] += pq[K & 1][1];
+      hstep[qt] = __builtin_fmaf(pq[K & 1][1], tq[K & 1][1], hstep[qt]);
     }
     // last, so that it does not wait for the conversion (12 x 32 frames of 2048, d = 64, last update: 753 -> 734 us)
-    ltil[qt] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, ltil[qt], false);
+    ltstep[qt] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, j == 0 ? 0.f : ltstep[qt], false);
     pbcur[qt][j >> 2][2 * (j & 3)] = pr[0];
     pbcur[qt][j >> 2][2 * (j & 3) + 1] = pr[1];
-    asm volatile("" : "+v"(ltil[qt]));
-    if (ENT == 1) asm volatile("" : "+v"(lsum[qt]), "+v"(hsum[qt]));
+    asm volatile("" : "+v"(ltstep[qt]));
+    if (ENT == 1) asm volatile("" : "+v"(lstep[qt]), "+v"(hstep[qt]));
   };
-  float mpend[Q2];     // references that take effect at the start of the next step
-  bool moved = false;  // wave-uniform: some reference moves at the start of the next step
-  float cand[Q2];
-  auto row_max = [&](auto qc, f32x16 (&snext)[Q2]) __attribute__((always_inline)) {
+  auto row_max = [&](auto qc, f32x16 (&snext)[Q2]) __attribute__((always_inline)) -> float {
     constexpr int qt = decltype(qc)::value;
-    cand[qt] = subtile_max(snext[qt]) * sc[qt];
-    asm volatile("" : "+v"(cand[qt]));
+    return subtile_max(snext[qt]) * sc[qt];
   };
-  auto decide = [&]() __attribute__((always_inline)) {
-    const bool grow = (cand[0] > msc[0] + RESCALE_TH2) || (cand[1] > msc[1] + RESCALE_TH2);
-    moved = __any(grow);
+  // rows keys_left .. 31 of the last sub-tile are copies of the last valid row: push their logits far down so that they get
+  // probability zero
+  auto mask_tail = [&](f32x16 (&s)[Q2], int keys_left) __attribute__((always_inline)) {
 #pragma unroll
-    for (int qt = 0; qt < Q2; ++qt) {
-      // a reference that moves goes HEADROOM2 above the row's maximum: the next move then needs a maximum
-      // 2^(HEADROOM2 + RESCALE_TH2) times the present one
-      mpend[qt] = moved ? fmaxf(msc[qt], cand[qt] + HEADROOM2) : msc[qt];
-      asm volatile("" : "+v"(mpend[qt]));
+    for (int r = 0; r < 16; ++r) {
+      const float off = (8 * (r >> 2) + 4 * g + (r & 3)) >= keys_left ? -1.0e9f : 0.f;
+#pragma unroll
+      for (int qt = 0; qt < Q2; ++qt) s[qt][r] += off;
     }
   };
-  // which MFMA slot carries which vector piece
-  constexpr int SLOT_MAX0 = 2 * KS + 2;                      // two MFMAs after the last logit MFMA: its result is ready
-  constexpr int SLOT_MAX1 = 2 * KS + 4 < NSL ? 2 * KS + 4 : NSL - 1;
-  constexpr int SLOT_DECIDE = NSL - 1;
-  static_assert(SLOT_MAX0 < NSL && SLOT_MAX1 >= SLOT_MAX0 && SLOT_DECIDE >= SLOT_MAX1, "the maxima follow the logits inside the step");
+  // logits of the 32 keys at byte offset `off` (slot and sub-tile), plain form, ready to be read
+  auto plain_logits = [&](int off, f32x16 (&s)[Q2]) __attribute__((always_inline)) {
+    static_for<0, KS>([&](auto kc) {
+      constexpr int ks = decltype(kc)::value;
+      const bf16x8 a = rd_row(a_off[ks] + off);
+      if constexpr (ks == 0) {
+        mfma_first(s[0], a, qreg[0][ks]);
+        mfma_first(s[1], a, qreg[1][ks]);
+      } else {
+        mfma_v(s[0], a, qreg[0][ks]);
+        mfma_v(s[1], a, qreg[1][ks]);
+      }
+    });
+    F2_MFMA_RESULT_WAIT();
+    F2_FENCE();
+  };
+  // A reference has to move: the sub-tile just finished (keys at byte offset `off`; its products are not issued yet) is formed
+  // again against new references, everything before it is rescaled (App. B: h <- a h + a log(a) l).
+  auto redo = [&](int off, bf16x8 (&pbcur)[Q2][2], int keys_left) __attribute__((always_inline)) {
+    f32x16 s[Q2];
+    plain_logits(off, s);
+    if (keys_left < 32) mask_tail(s, keys_left);
+#pragma unroll
+    for (int qt = 0; qt < Q2; ++qt) {
+      const float cand = qt == 0 ? row_max(std::integral_constant<int, 0>{}, s) : row_max(std::integral_constant<int, 1>{}, s);
+      const float m = fmaxf(msc[qt], cand + HEADROOM2);
+      const float dl = msc[qt] - m;  // log2 of the rescale factor, <= 0
+      const float alpha = __builtin_amdgcn_exp2f(dl);
+      if (ENT == 1) {
+        hsum[qt] = alpha * (hsum[qt] + dl * lsum[qt]);
+        lsum[qt] *= alpha;
+      }
+      ltil[qt] *= alpha;
+      msc[qt] = m;
+#pragma unroll
+      for (int x = 0; x < NX; ++x)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          // one tile at a time (the empty statements tie the tile's copies out of and back into the
+          // accumulation registers to this place, so they do not pile up beside the loop's registers)
+          asm volatile("" : "+a"(oacc[x][qt][ct]));
+          scale_acc(oacc[x][qt][ct], alpha);
+          asm volatile("" : "+a"(oacc[x][qt][ct]));
+          F2_FENCE();
+        }
+    }
+    static_for<0, 16>([&](auto kc) {
+      score_scale(kc, s);
+      score_exp(kc);
+      score_sums(kc, pbcur);
+    });
+    asm volatile("s_nop 1" ::: "memory");
+    F2_FENCE();
+  };
 
   // S_OFF / PV_OFF: byte offsets (slot and sub-tile) this step's logits and products read;
   // NS_OFF / NPV_OFF: the same for the step that follows (its first operands are requested here).
@@ -402,34 +447,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
                   bf16x8 (&pbcur)[Q2][2], int keys_left) __attribute__((always_inline)) {
     constexpr int S_OFF = decltype(s_c)::value, PV_OFF = decltype(pv_c)::value;
     constexpr int NS_OFF = decltype(ns_c)::value, NPV_OFF = decltype(npv_c)::value;
-    if (keys_left < 32) {
-      // ragged end of the key range: rows keys_left .. 31 of this sub-tile are copies of the
-      // last valid row; push their logits far down so that they get probability zero
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float off = (8 * (r >> 2) + 4 * g + (r & 3)) >= keys_left ? -1.0e9f : 0.f;
-#pragma unroll
-        for (int qt = 0; qt < Q2; ++qt) scur[qt][r] += off;
-      }
-    }
-    const bool moved_now = moved;
-    float alpha[Q2];
-    if (moved_now) {
-      // a reference moves (rare: only when a row maximum outgrew it by 2^RESCALE_TH): the running sums now
-      // (App. B: h <- a h + a log(a) l), the accumulators at the end of the step, after the products of
-      // sub-tile n-1, which were formed against the old reference
-#pragma unroll
-      for (int qt = 0; qt < Q2; ++qt) {
-        const float dl = msc[qt] - mpend[qt];  // log2 of the rescale factor, <= 0
-        alpha[qt] = __builtin_amdgcn_exp2f(dl);
-        if (ENT == 1) {
-          hsum[qt] = alpha[qt] * (hsum[qt] + dl * lsum[qt]);
-          lsum[qt] *= alpha[qt];
-        }
-        ltil[qt] *= alpha[qt];
-        msc[qt] = mpend[qt];
-      }
-    }
+    if (keys_left < 32) mask_tail(scur, keys_left);
     F2_FENCE();
     static_for<0, NG>([&](auto gc) {
       constexpr int GI = decltype(gc)::value;
@@ -455,31 +473,19 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
           if constexpr (S1 == SL) score_exp(kc);
           if constexpr (S2 == SL) score_sums(kc, pbcur);
         });
-        if constexpr (SL == SLOT_MAX0) row_max(std::integral_constant<int, 0>{}, snext);
-        if constexpr (SL == SLOT_MAX1) row_max(std::integral_constant<int, 1>{}, snext);
-        if constexpr (SL == SLOT_DECIDE) decide();
         F2_FENCE();
       });
     });
 #pragma unroll
     for (int qt = 0; qt < Q2; ++qt) asm volatile("" : "+v"(pbcur[qt][0]), "+v"(pbcur[qt][1]));
-    if (moved_now) {
-      F2_MFMA_RESULT_WAIT();  // the last products above are still in the pipe
-      F2_FENCE();
+    if (__any(ltstep[0] > STEP_MAX2 || ltstep[1] > STEP_MAX2)) redo(NPV_OFF, pbcur, keys_left);
 #pragma unroll
-      for (int x = 0; x < NX; ++x)
-#pragma unroll
-        for (int qt = 0; qt < Q2; ++qt)
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) {
-            // one tile at a time (the empty statements tie the tile's copies out of and back into the
-            // accumulation registers to this place, so they do not pile up beside the loop's registers)
-            asm volatile("" : "+a"(oacc[x][qt][ct]));
-            scale_acc(oacc[x][qt][ct], alpha[qt]);
-            asm volatile("" : "+a"(oacc[x][qt][ct]));
-            F2_FENCE();
-          }
-      asm volatile("s_nop 1" ::: "memory");
+    for (int qt = 0; qt < Q2; ++qt) {
+      ltil[qt] += ltstep[qt];
+      if (ENT == 1) {
+        lsum[qt] += lstep[qt];
+        hsum[qt] += hstep[qt];
+      }
     }
   };
   if (ntiles > 0) {
@@ -501,23 +507,10 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     // block) only helps to load the tiles.
     const bool active = qb * BQ2 + wave * (32 * Q2) < P.nq;
     if (active) {
-      // logits and row maxima of sub-tile 0, plain form
-      static_for<0, KS>([&](auto kc) {
-        constexpr int ks = decltype(kc)::value;
-        const bf16x8 a = rd_row(a_off[ks]);
-        if constexpr (ks == 0) {
-          mfma_first(sA[0], a, qreg[0][ks]);
-          mfma_first(sA[1], a, qreg[1][ks]);
-        } else {
-          mfma_v(sA[0], a, qreg[0][ks]);
-          mfma_v(sA[1], a, qreg[1][ks]);
-        }
-      });
-      F2_MFMA_RESULT_WAIT();
-      F2_FENCE();
-      row_max(std::integral_constant<int, 0>{}, sA);
-      row_max(std::integral_constant<int, 1>{}, sA);
-      decide();
+      // logits of sub-tile 0, plain form; their row maxima are the first references
+      plain_logits(0, sA);
+      msc[0] = fmaxf(msc[0], row_max(std::integral_constant<int, 0>{}, sA) + HEADROOM2);
+      msc[1] = fmaxf(msc[1], row_max(std::integral_constant<int, 1>{}, sA) + HEADROOM2);
       // operands of the first groups of the first step (sub-tile 1 of slot 0; products against slot 3)
       static_for<0, PF>([&](auto gc) { request(gc, 32 * ROW_BYTES, 3 * TILE_BYTES + 32 * ROW_BYTES); });
     }

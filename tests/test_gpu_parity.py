@@ -181,14 +181,15 @@ def test_r_update_random_shapes_both_forms(env, seed, fused):
         assert U.max_abs(gcL[h].reshape(T, b), rcL.T) <= 2e-2, (T, b, d, with_cr)
 
 
-@pytest.mark.parametrize("spike", [7.0, 72.0])
+@pytest.mark.parametrize("spike", [7.0, 72.0, 400.0])
 @pytest.mark.parametrize("d", [64, 128])
 def test_r_update_when_the_reference_max_moves_in_every_tile(env, d, fused, spike):
     """Keys with ever larger logits in later tiles, one spike key per tile, and queries that respond to the
     spikes with different strength: the kernels' reference maxima move in almost every tile, in the wave that
     produces the probabilities and in the one that adopts them, while the mass below the spikes still matters for
     many rows.  Spikes of 7 per tile raise the strongest rows' maxima by 2^8 per tile (the margin of the kernels
-    with two waves per SIMD), spikes of 72 by more than 2^56 (margin plus headroom of the kernel with one)."""
+    with two waves per SIMD), spikes of 72 by more than 2^56 (margin plus headroom of the kernel with one), spikes of 400 by more than
+    2^192, so that the weights of a sub-tile overflow before its reference has moved."""
     torch, binding, dev = env
     b = 600                                           # 10 key tiles, ragged; 5 query blocks of 128
     rng = np.random.default_rng(77 + d)
