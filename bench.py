@@ -259,7 +259,7 @@ def main() -> int:
     ap.add_argument("--entropy", choices=["online", "identity"], default="online")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--flash-variant", type=int, choices=[0, 1, 2], default=None,
-                    help="bf16 MFMA R-update kernels: 0 two waves per SIMD, 1 one wave per SIMD with two query tiles per "
+                    help="bf16 MFMA R-update kernels: 0 two waves per SIMD, 1 up to two query tiles per "
                          "wave, 2 the latter for the update with values only (default: the library's setting)")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run one token-permutation copy of known size (reference for HBM byte counters)")
@@ -374,11 +374,7 @@ def main() -> int:
         """The short-frame kernel that takes an R-update of this workload, or None (the library's rule for variant 2)."""
         if not bf16 or d not in (64, 128) or variant != 2 or not online or (with_v and not binding.get_fused_apply()):
             return None
-        if b <= ((256 if d == 64 else 192) if with_v else 224):
-            return "frame_kernel"
-        if d == 64 and 256 < b <= (384 if with_v else 352) and BH * T > 128:
-            return "frame_rows_kernel"
-        return None
+        return "frame_kernel" if b <= ((224 if d == 64 else 192) if with_v else 160) else None
     if "r_update_last" in phases:
         # dominant kernel (the longest single launch of a call): the R-update of the last sweep, which forms
         # the logits, R K (alpha_L), c_L and R V (y) in one launch: three b x b x d products per frame.
@@ -388,7 +384,7 @@ def main() -> int:
         if short:
             kern, what = short, f"{short} (last R-update of short frames: logits, R K, c_L and R V in one launch)"
         elif bf16 and d in (64, 128) and variant in (1, 2):
-            kern, what = "flash2_kernel", "flash2_kernel (last R-update: logits, R K, c_L and R V in one launch, one wave per SIMD)"
+            kern, what = "flash2_kernel", "flash2_kernel (last R-update: logits, R K, c_L and R V in one launch)"
         elif fused:
             kern, what = "flash_kv_kernel", "flash_kv_kernel (last R-update: logits, R K, c_L and R V in one launch)"
         else:
@@ -402,8 +398,7 @@ def main() -> int:
         if "r_update" in phases:
             # the fitting sweeps' R-update (logits + R K), one launch each
             fl2, t2 = 4.0 * BH * T * b * b * d, phases["r_update"]
-            two_tiles = variant == 1 or (variant == 2 and d == 64)
-            fit = frame_kernel(False) or ("flash2_kernel" if two_tiles else "flash_kernel")
+            fit = frame_kernel(False) or ("flash2_kernel" if variant in (1, 2) else "flash_kernel")
             roofline["fitting_r_update"] = {"kernel": f"{fit} (logits + R K)",
                                             "flops_per_launch": fl2,
                                             "ms_per_launch": t2, "achieved": fl2 / (t2 * 1e-3) / 1e12,

@@ -87,8 +87,8 @@ float vmonarch_get_cr_min(void);
  * entropy.  1 (default): alpha_L, c_L and y = R V come from one evaluation of the logits and the softmax
  * (flash variant 0: two waves share a query tile; variant 2: the kernels named there).  0: the kernels
  * with two waves per SIMD (variant 0, and variant 2 for frames of at most 128 tokens) run one pass for
- * alpha_L / c_L and a second for y, and variant 2 does not use its short-frame kernels.  The kernel with
- * one wave per SIMD (see vmonarch_set_flash_variant) always takes one pass.  Same results up to
+ * alpha_L / c_L and a second for y, and variant 2 does not use its short-frame kernels.  The kernel of
+ * variant 1 (see vmonarch_set_flash_variant) always takes one pass.  Same results up to
  * rounding order.  Process-wide. */
 int vmonarch_set_fused_apply(int enable);
 int vmonarch_get_fused_apply(void);
@@ -103,13 +103,11 @@ int vmonarch_set_manual_control(int cr_control, int cl_control, float cl_value);
 int vmonarch_get_manual_control(int* cr_control, int* cl_control, float* cl_value);
 
 /* Which bf16 MFMA kernel runs an R-update: 0 the kernels with two waves per SIMD and one 32-query
- * tile per wave; 1 the kernel with one wave per SIMD and two query tiles per wave, whose
- * accumulators live in accumulation registers (measured a few per cent faster for the update with
- * values and, at d = 64, without; slower without values at d = 128); 2 (default) each update on
- * the kernel measured faster for it: short frames (up to 192 .. 256 tokens, at d = 64 in launches of
- * more than 128 frames up to 384; online entropy and fused apply only) on kernels that take a whole
- * frame, or 128 rows of one, per workgroup; else that of 1 for the update with values (frames of
- * more than 128 tokens) and for d = 64, those of 0 otherwise.  Exact attention of a contiguous row range
+ * tile per wave; 1 the kernel whose waves take one or two 32-query tiles by the size of the launch
+ * and whose accumulators live in accumulation registers; 2 (default) each update on the kernel
+ * measured faster for it: short frames (up to 160 .. 224 tokens; online entropy and fused apply only)
+ * on the kernel that takes a whole frame per workgroup; else that of 1, but for updates with values of
+ * at most 128 tokens, which take that of 0. Exact attention of a contiguous row range
  * (first frame, vmonarch_recompute_rows) runs on the kernel of 1 unless the variant is 0; a row
  * list (vmonarch_recompute_tokens) and the sink averaging always run on the kernels of 0.  Same
  * results up to rounding order.  Process-wide. */

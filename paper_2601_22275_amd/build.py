@@ -8,7 +8,10 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvmonarch.so")
-SOURCES = ["api.hip", "generic.hip", "flash.hip", "flash_kv.hip", "flash2.hip", "frame.hip", "lpass.hip", "backward.hip", "backward_mfma.hip", "f32.hip"]
+# (source, object, flags of its own): flash2.hip is compiled once per head dimension
+SOURCES = [(s, s.replace(".hip", ".o"), []) for s in ("api.hip", "generic.hip", "flash.hip", "flash_kv.hip", "frame.hip", "lpass.hip",
+                                                      "backward.hip", "backward_mfma.hip", "f32.hip")]
+SOURCES += [("flash2.hip", f"flash2_{d}.o", [f"-DVM_FLASH2_D={d}"]) for d in (64, 128)]
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fvisibility=hidden",
     # keep the compiler from forming packed fp32 VALU instructions
@@ -30,9 +33,9 @@ def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
     procs = []
-    for src in SOURCES:
-        obj = os.path.join(CSRC, src.replace(".hip", ".o"))
-        cmd = [hipcc, *FLAGS, *EXTRA.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
+    for src, obj, flags in SOURCES:
+        obj = os.path.join(CSRC, obj)
+        cmd = [hipcc, *FLAGS, *EXTRA.get(src, []), *flags, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))

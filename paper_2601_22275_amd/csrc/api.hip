@@ -34,7 +34,7 @@ int g_cl_control = VMONARCH_CONTROL_NONE;
 float g_cl_value = NAN;  // NaN: -log(b), the c_L of a uniform row of R
 int g_entropy_mode = VMONARCH_ENTROPY_ONLINE;
 // which bf16 MFMA kernel runs an R-update: 0 the two-waves-per-SIMD kernels (flash.hip, flash_kv.hip), 1 the
-// one-wave-per-SIMD kernel with two query tiles per wave (flash2.hip), 2 the one measured faster (see r_update_any)
+// kernel with up to two query tiles per wave (flash2.hip), 2 the one measured faster (see r_update_any)
 int g_flash_variant = 2;
 
 std::mutex g_ws_mutex;
@@ -251,23 +251,18 @@ int r_update_any<bf16_t>(const bf16_t* aR, const float* cR, const bf16_t* k, con
                          bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min, const Settings& cfg,
                          hipStream_t st) {
   hipError_t e;
-  // variant 2: every update on the kernel that was measured faster for it.  Short frames (see frame_supported) on the kernels
-  // that take a frame, or 128 rows of one, per workgroup; they form c_L online and y in the same launch, so calls that choose
-  // the identity form or two launches stay on the streaming kernels.  Those: with values the two-tile kernel, unless a frame
-  // has at most 128 tokens (its 256-row query blocks would be mostly padding; launch_r_update_flash takes the one-tile kernel
-  // in two launches for such calls; the wave-pair kernel runs in variant 0 only); without values the two-tile kernel at
-  // d = 64 and, at d = 128, for frames of more than 448 tokens (one-tile / two-tile kernel, 130 frames of 300 28.5 / 29.2, 400
-  // 35.6 / 36.3, 512 40.8 / 40.4, 1000 103.5 / 99.5, 1560 194.9 / 183.7 us; 252 of 3584 1602 / 1455: short key loops leave the
-  // single wave of a SIMD its start and end to wait for).
-  const bool two_tiles = cfg.flash_variant == 1 ||
-                         (cfg.flash_variant == 2 && (v != nullptr ? dm.b > 128 : dm.d == 64 || dm.b > 448));
+  // variant 2: every update on the kernel that was measured faster for it.  Short frames (see frame_supported) on the kernel
+  // that takes a frame per workgroup; it forms c_L online and y in the same launch, so calls that choose the identity form or two
+  // launches stay on the streaming kernels.  Those: the kernel of flash2.hip, but for updates with values of at most 128 tokens
+  // (launch_r_update_flash takes the one-tile kernel in two launches for such calls; the wave-pair kernel runs in variant 0 only).
+  const bool two_tiles = cfg.flash_variant == 1 || (cfg.flash_variant == 2 && (v == nullptr || dm.b > 128));
   const bool short_frame = cfg.flash_variant == 2 && cfg.entropy_mode == VMONARCH_ENTROPY_ONLINE &&
-                           (v == nullptr || cfg.fused_apply != 0) &&
-                           (frame_supported(dm, v != nullptr) || frame_rows_supported(dm, v != nullptr));
+                           (v == nullptr || cfg.fused_apply != 0) && frame_supported(dm, v != nullptr);
   if (short_frame)
     e = launch_r_update_frame(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, st);
   else if (flash_supported(dm) && two_tiles)
-    e = launch_r_update_flash2(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, cfg.entropy_mode, st);
+    e = dm.d == 128 ? launch_r_update_flash2<128>(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, cfg.entropy_mode, st)
+                    : launch_r_update_flash2<64>(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, cfg.entropy_mode, st);
   else if (flash_supported(dm))
     e = launch_r_update_flash(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min, cfg.entropy_mode, cfg.fused_apply != 0, st);
   else

@@ -133,14 +133,14 @@ hipError_t launch_r_update_flash(const bf16_t* aR, const float* cR, const bf16_t
 hipError_t launch_r_update_flash_fused(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL,
                                        float* cL, bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min,
                                        hipStream_t st);
-// flash2.hip : the same passes with one wave per SIMD and two query tiles per wave (d == 64 or 128);
+// flash2.hip : the same passes with up to two query tiles per wave (D = dm.d, 64 or 128);
 // v == nullptr: alpha_L, c_L (fitting sweep); v given: also y, from one evaluation of the softmax
+template <int D>
 hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL,
                                   float* cL, bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min,
                                   int entropy_mode, hipStream_t st);
-// frame.hip : the same updates for short frames (b <= 192 .. 256; d == 64 or 128), one workgroup per frame
+// frame.hip : the same updates for short frames (b <= 160 .. 224; d == 64 or 128), one workgroup per frame
 bool frame_supported(const Dims& dm, bool with_v);
-bool frame_rows_supported(const Dims& dm, bool with_v);  // ... or per 128 rows of one
 hipError_t launch_r_update_frame(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL,
                                  bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min, hipStream_t st);
 // exact attention of nrows query rows per head (starting where q / out / lse point) over all N keys
@@ -150,9 +150,9 @@ size_t first_frame_flash_scratch_bytes(const Dims& dm, int nrows);
 hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse,
                                     void* scratch, size_t scratch_bytes, const Dims& dm, int nrows, const int* rows,
                                     bool two_tile, hipStream_t st);
-int flash2_query_block();  // query rows per workgroup of flash2.hip's kernel
-// flash2.hip : the same pass (contiguous rows only) on the kernel with two query tiles per wave; the caller has cut the
+// flash2.hip : the same pass (contiguous rows only) on that kernel; the caller has cut the
 // keys into ns ranges of keys_per_split and owns the partial-result buffers
+template <int D>
 hipError_t launch_first_frame_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse,
                                      float* part_o, float* part_lse, const Dims& dm, int nrows, int ns,
                                      int keys_per_split, hipStream_t st);

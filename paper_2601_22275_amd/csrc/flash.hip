@@ -635,10 +635,13 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   const bool d128 = dm.d == 128;
   // contiguous rows can run on the kernel with two query tiles per wave (same blocks, ranges and partial results;
   // measured 2 .. 3 % faster on the long key loops of this pass); a row list is gathered by this file's kernel only
-  // (the key ranges and the partial-result buffers above are sized for this file's query blocks: the other kernel's must match)
-  const bool ff2 = two_tile && row_list == nullptr && flash2_query_block() == BQ;
+  const bool ff2 = two_tile && row_list == nullptr;
+  auto two_tile_pass = [&](float* part_o, float* part_lse) {
+    return d128 ? launch_first_frame_flash2<128>(q, k, v, out, lse, part_o, part_lse, dm, nrows, ns, P.keys_per_split, st)
+                : launch_first_frame_flash2<64>(q, k, v, out, lse, part_o, part_lse, dm, nrows, ns, P.keys_per_split, st);
+  };
   if (ns == 1) {
-    if (ff2) return launch_first_frame_flash2(q, k, v, out, lse, nullptr, nullptr, dm, nrows, 1, P.keys_per_split, st);
+    if (ff2) return two_tile_pass(nullptr, nullptr);
     return d128 ? launch_flash<128, false, true, 0, false>(P, st) : launch_flash<64, false, true, 0, false>(P, st);
   }
   const size_t rows = (size_t)ns * dm.BH * nrows;
@@ -646,7 +649,7 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   if (scratch == nullptr || scratch_bytes < need) return hipErrorInvalidValue;
   P.part_lse = (float*)scratch;
   P.part_o = (float*)((char*)scratch + ((rows * sizeof(float) + 255) & ~(size_t)255));
-  hipError_t e = ff2 ? launch_first_frame_flash2(q, k, v, out, lse, P.part_o, P.part_lse, dm, nrows, ns, P.keys_per_split, st)
+  hipError_t e = ff2 ? two_tile_pass(P.part_o, P.part_lse)
                      : (d128 ? launch_flash<128, false, true, 0, true>(P, st) : launch_flash<64, false, true, 0, true>(P, st));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(merge_splits_kernel, dim3((unsigned)((long long)dm.BH * nrows)), dim3(dm.d), 0, st, P.part_o,

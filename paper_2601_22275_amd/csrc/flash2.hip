@@ -1,23 +1,23 @@
 // bf16 MFMA kernel for every blocked-softmax pass of spatio-temporal Monarch attention on gfx950,
-// with one wave per SIMD and two 32-query tiles per wave: the R-update of a fitting sweep
+// with one or two 32-query tiles per wave: the R-update of a fitting sweep
 // (Eq. R + Eq. alpha_L/c_L: logits, alpha_L = R K and c_L), the R-update of the last sweep (the
 // same plus y = R V of App. A, from ONE evaluation of the logits and of the softmax) and the
 // first-frame recomputation (Sec. 3.3).  All three are Alg. 1 with the running max / sum /
 // entropy of App. B.
 //
-// One workgroup = 4 waves = 256 query rows; a wave owns 64 query rows (two tiles of 32) for the
-// whole key loop and the full register file of its SIMD (512 registers), which is what lets one
-// wave hold both accumulator sets (R K and R V: 2 x 2 x 4 tiles of 16 registers) beside its
-// queries and logits.  Keys (and values) stream through LDS in 64-row tiles, four slots per
+// One workgroup = 4 waves.  With two tiles a wave owns 64 query rows for the whole key loop and, at d = 128 with values, the
+// full register file of its SIMD (512 registers), which is what lets one wave hold both accumulator sets (R K and R V:
+// 2 x 2 x 4 tiles of 16 registers) beside its queries and logits.  With one tile (32 rows, 128 in a workgroup) two or three
+// workgroups share a compute unit; which launch takes which: short_blocks_faster.  Keys (and values) stream through LDS in 64-row tiles, four slots per
 // tensor, loaded two tiles ahead.  Both contractions use v_mfma_f32_32x32x16_bf16:
 //
 //   S^T = K Q^T     A = K rows read from LDS (ds_read_b128), B = Q^T held in registers.  One A
-//                   operand serves both query tiles: half the LDS bytes per MFMA of a
-//                   one-tile wave.  In the result lane (q, g) holds the logits of query q for
+//                   operand serves all query tiles of the wave: with two, half the
+//                   LDS bytes per MFMA.  In the result lane (q, g) holds the logits of query q for
 //                   16 of the 32 keys, so the sums are per-lane scalars.
 //   O^T += X^T P^T  A = X^T (X = K for alpha_L, X = V for y) fetched from the same row-major
 //                   LDS tile with the LDS transpose read (ds_read_b64_tr_b16), again shared by
-//                   both query tiles; B = P^T, the S^T accumulator converted to bf16 in place.
+//                   the query tiles; B = P^T, the S^T accumulator converted to bf16 in place.
 //
 // The 16-byte chunk c of key row r is stored at chunk c ^ swz(r) (RowGeo in common.h) so that
 // both the row-wise b128 reads and the transpose reads spread over all banks.
@@ -31,9 +31,7 @@ namespace vm {
 
 namespace {
 
-constexpr int W2 = 4;             // waves per workgroup, one per SIMD
-constexpr int Q2 = 2;             // 32-query tiles per wave
-constexpr int BQ2 = 32 * Q2 * W2;  // query rows per workgroup
+constexpr int W2 = 4;             // waves per workgroup
 // No running row maximum is kept.  A row's reference comes from the maximum of its first 32 logits, and any reference gives the
 // same results: the sums and the accumulators carry the common factor 2^-reference, the weights are formed in fp32 and rounded
 // to bf16, which has fp32's exponent range, so a stale reference costs the outputs no precision until 2^t nears overflow.  What
@@ -78,7 +76,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 #define F2_MFMA_RESULT_WAIT() asm volatile("s_nop 7\n\ts_nop 3" ::: "memory")
 
 // ENT: c_L not wanted (0), online (1) or in the identity form (2)
-template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT>
+// Q2: 32-query tiles per wave; W2 Q2 of them are the workgroup's query block
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2>
 __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   using G = RowGeo<D>;
   constexpr int ROW_BYTES = G::ROW_BYTES;
@@ -91,7 +90,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   constexpr int NX = (OUT_K ? 1 : 0) + (OUT_V ? 1 : 0);  // accumulator sets: [R K][R V]
   constexpr int XV = OUT_K ? 1 : 0;                       // index of the R V set
   static_assert(OUT_K || OUT_V, "at least one product");
-  static_assert(Q2 == 2, "the schedule below is written for two query tiles");
+  constexpr int BQ2 = 32 * Q2 * W2;  // query rows per workgroup
   auto swz = [](int row) { return G::swz(row); };
   extern __shared__ __attribute__((aligned(16))) char smem[];  // [K|V][NSLOT][64 rows][2 D bytes]
 
@@ -120,16 +119,6 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   const int nkeys = kend - kbeg;
   const int ntiles = (nkeys + BK - 1) / BK;
   const int last_left = nkeys - (ntiles - 1) * BK;  // 1..64 keys in the last tile
-  // The key loop can visit the tiles in rotated order, tile (i + first) mod ntiles at loop position i: any order
-  // gives the same sums, and with queries and keys from the same rows (the R-update) the query block's own
-  // tiles hold, for video tokens, the largest logits of its rows, so the references settle at once.  The
-  // launcher decides (P.own_tile_first); the rotation costs the blocks of a frame their common L2 lines.
-  const int first_tile = P.own_tile_first ? min(qb * (BQ2 / BK), ntiles - 1) : 0;
-  auto tile_at = [&](int i) __attribute__((always_inline)) -> int {
-    const int t = i + first_tile;
-    return t >= ntiles ? t - ntiles : t;
-  };
-
   const long long qrow0 = (long long)prob * P.q_rows_per_problem;
   const char* kbase = reinterpret_cast<const char*>(P.k + ((long long)prob * P.k_rows_per_problem + kbeg) * D);
   const char* vbase = OUT_V ? reinterpret_cast<const char*>(P.v + ((long long)prob * P.k_rows_per_problem + kbeg) * D) : nullptr;
@@ -156,9 +145,8 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
 #pragma unroll
   for (int r = 0; r < NR; ++r) goff[r] = (unsigned)((RPI * W2 * r + st_key) * ROW_BYTES + st_lc * 16);
   const unsigned lds_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)smem;
-  auto issue_tile = [&](int i) __attribute__((always_inline)) {  // loop position i: slot i & 3, tile tile_at(i)
-    const int t = tile_at(i);
-    const unsigned kb = lds_base + (i & (NSLOT - 1)) * TILE_BYTES;
+  auto issue_tile = [&](int t) __attribute__((always_inline)) {  // into slot t & 3
+    const unsigned kb = lds_base + (t & (NSLOT - 1)) * TILE_BYTES;
     const char* ksrc = kbase + (long long)t * TILE_BYTES;
     const char* vsrc = OUT_V ? vbase + (long long)t * TILE_BYTES : nullptr;
     const bool ragged = t == ntiles - 1 && last_left < BK;
@@ -191,20 +179,15 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     }
   }
 
-  // ---- queries: B operand of S^T = K Q^T, kept in registers -------------------------------
-  bf16x8 qreg[Q2][KS];
-  float sc[Q2];
-#pragma unroll
-  for (int qt = 0; qt < Q2; ++qt) {
-    const int r = qb * BQ2 + wave * (32 * Q2) + qt * 32 + ql;
+  // Row r of the problem as the B operand of S^T = K Q^T; returns its logit scale (log2 units).
+  auto load_query = [&](int r, bf16x8 (&x)[KS]) __attribute__((always_inline)) -> float {
     const int row = r < P.nq ? r : P.nq - 1;
     const bf16_t* qp = P.q + (qrow0 + row) * D + 8 * g;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qreg[qt][ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
-    float c = P.cR ? P.cR[qrow0 + row] : 1.0f;
-    c = fmaxf(c, P.cr_min);
-    sc[qt] = P.row_scale * LOG2E / c;
-  }
+    for (int ks = 0; ks < KS; ++ks) x[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
+    const float c = P.cR ? P.cR[qrow0 + row] : 1.0f;
+    return P.row_scale * LOG2E / fmaxf(c, P.cr_min);
+  };
 
   // LDS read addresses, one register each, everything else of an address is an instruction immediate.
   // Row reads (A of S^T): key row = 32 st + ql, logical chunk 2 ks + g.
@@ -243,6 +226,29 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_b64_ptr)(unsigned long long)addr);
   };
 
+  // ---- the MFMAs, as inline assembly ---------------------------------------------------------
+  // With more than 256 registers per wave the compiler gives every MFMA it selects itself an
+  // accumulation-register result, which plain vector instructions cannot read; here the logits must land in
+  // ordinary registers (the softmax consumes them element by element) and the products in accumulation
+  // registers.  Consecutive MFMAs that accumulate into exactly the registers the previous one wrote need
+  // no wait; a vector instruction that reads a result does (F2_MFMA_RESULT_WAIT, or enough MFMAs issued in
+  // between: each one waits for the pipe, 8 passes).
+  auto mfma_first = [&](f32x16& acc, const bf16x8& a, const bf16x8& b) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+  };
+  auto mfma_v = [&](f32x16& acc, const bf16x8& a, const bf16x8& b) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+  };
+  auto mfma_a = [&](f32x16& acc, const bf16x8& a, const bf16x8& b) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+  };
+
+  // ---- queries: B operand of S^T = K Q^T, kept in registers -------------------------------
+  bf16x8 qreg[Q2][KS];
+  float sc[Q2];
+#pragma unroll
+  for (int qt = 0; qt < Q2; ++qt) sc[qt] = load_query(qb * BQ2 + wave * (32 * Q2) + qt * 32 + ql, qreg[qt]);
+
   // ---- accumulators and statistics ---------------------------------------------------------
   // The products accumulate in accumulation registers (constraint "a" below): with the two query tiles,
   // the logits and the queries in the 256 ordinary registers, 2 x 2 x CT tiles of 16 live there.
@@ -264,28 +270,11 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     hsum[qt] = 0.f;
   }
 
-  // ---- the MFMAs, as inline assembly ---------------------------------------------------------
-  // With more than 256 registers per wave the compiler gives every MFMA it selects itself an
-  // accumulation-register result, which plain vector instructions cannot read; here the logits must land in
-  // ordinary registers (the softmax consumes them element by element) and the products in accumulation
-  // registers.  Consecutive MFMAs that accumulate into exactly the registers the previous one wrote need
-  // no wait; a vector instruction that reads a result does (F2_MFMA_RESULT_WAIT, or enough MFMAs issued in
-  // between: each one waits for the pipe, 8 passes).
-  auto mfma_first = [&](f32x16& acc, const bf16x8& a, const bf16x8& b) __attribute__((always_inline)) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
-  };
-  auto mfma_v = [&](f32x16& acc, const bf16x8& a, const bf16x8& b) __attribute__((always_inline)) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
-  };
-  auto mfma_a = [&](f32x16& acc, const bf16x8& a, const bf16x8& b) __attribute__((always_inline)) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-  };
-
   // ---- one step = one 32-key sub-tile, as a fixed sequence of groups ------------------------
   // Software pipeline over sub-tiles n = 0, 1, ...  Step n carries, in the one wave,
   //   matrix:  S^T of sub-tile n+1 (both query tiles), then O^T += X^T P^T of sub-tile n-1;
   //   vector:  p = 2^t, sums and bf16 P^T of sub-tile n, whose sums then say whether its references held.
-  // A group is the two MFMAs (query tile 0, query tile 1) that share one A operand from LDS: KS groups of
+  // A group is the MFMAs (one per query tile) that share one A operand from LDS: KS groups of
   // logits, then 2 CT NX groups of products in the order (16-key half c, channel tile ct, product x).  The
   // operand of group i + PF is requested while group i runs (a ring of four operand registers; NG is a
   // multiple of four, so ring positions repeat from step to step and the requests run on across steps,
@@ -293,7 +282,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   // slot carries more than an MFMA's worth of it when there is enough matrix work to hide it.
   constexpr int NPV = 2 * CT * NX;
   constexpr int NG = KS + NPV;
-  constexpr int NSL = 2 * NG;  // MFMA slots per step
+  constexpr int NSL = Q2 * NG;  // MFMA slots per step
   constexpr int PF = 2;        // groups between an operand's request and its use
   static_assert(NG % 4 == 0, "ring positions repeat from step to step");
   bf16x8 ring[4];
@@ -341,9 +330,9 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   float tq[2][2], pq[2][2];  // in flight between the stages, by parity of the pair
   float ltstep[Q2], lstep[Q2], hstep[Q2];  // this step's part of the sums
   auto score_scale = [&](auto kc, f32x16 (&scur)[Q2]) __attribute__((always_inline)) {
-    constexpr int K = decltype(kc)::value;  // 0 .. 15
-    constexpr int qt = K & 1;
-    constexpr int j = K >> 1;
+    constexpr int K = decltype(kc)::value;  // 0 .. 8 Q2 - 1
+    constexpr int qt = K % Q2;
+    constexpr int j = K / Q2;
     tq[K & 1][0] = __builtin_fmaf(scur[qt][2 * j], sc[qt], -msc[qt]);
     tq[K & 1][1] = __builtin_fmaf(scur[qt][2 * j + 1], sc[qt], -msc[qt]);
   };
@@ -354,8 +343,8 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   };
   auto score_sums = [&](auto kc, bf16x8 (&pbcur)[Q2][2]) __attribute__((always_inline)) {
     constexpr int K = decltype(kc)::value;
-    constexpr int qt = K & 1;
-    constexpr int j = K >> 1;
+    constexpr int qt = K % Q2;
+    constexpr int j = K / Q2;
     bf16x2 pr;
     pr[0] = (__bf16)pq[K & 1][0];  // round to nearest even; the pair is one v_cvt_pk_bf16_f32
     pr[1] = (__bf16)pq[K & 1][1];
@@ -371,10 +360,6 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     pbcur[qt][j >> 2][2 * (j & 3) + 1] = pr[1];
     asm volatile("" : "+v"(ltstep[qt]));
     if (ENT == 1) asm volatile("" : "+v"(lstep[qt]), "+v"(hstep[qt]));
-  };
-  auto row_max = [&](auto qc, f32x16 (&snext)[Q2]) __attribute__((always_inline)) -> float {
-    constexpr int qt = decltype(qc)::value;
-    return subtile_max(snext[qt]) * sc[qt];
   };
   // rows keys_left .. 31 of the last sub-tile are copies of the last valid row: push their logits far down so that they get
   // probability zero
@@ -392,47 +377,48 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
       constexpr int ks = decltype(kc)::value;
       const bf16x8 a = rd_row(a_off[ks] + off);
       if constexpr (ks == 0) {
-        mfma_first(s[0], a, qreg[0][ks]);
-        mfma_first(s[1], a, qreg[1][ks]);
+#pragma unroll
+        for (int qt = 0; qt < Q2; ++qt) mfma_first(s[qt], a, qreg[qt][ks]);
       } else {
-        mfma_v(s[0], a, qreg[0][ks]);
-        mfma_v(s[1], a, qreg[1][ks]);
+#pragma unroll
+        for (int qt = 0; qt < Q2; ++qt) mfma_v(s[qt], a, qreg[qt][ks]);
       }
     });
     F2_MFMA_RESULT_WAIT();
     F2_FENCE();
   };
+  // Query tile qt takes a reference of HEADROOM2 above `cand`; everything so far is rescaled (App. B: h <- a h + a log(a) l).
+  auto move_reference = [&](int qt, float cand) __attribute__((always_inline)) {
+    const float m = fmaxf(msc[qt], cand + HEADROOM2);
+    const float dl = msc[qt] - m;  // log2 of the rescale factor, <= 0
+    const float alpha = __builtin_amdgcn_exp2f(dl);
+    if (ENT == 1) {
+      hsum[qt] = alpha * (hsum[qt] + dl * lsum[qt]);
+      lsum[qt] *= alpha;
+    }
+    ltil[qt] *= alpha;
+    msc[qt] = m;
+#pragma unroll
+    for (int x = 0; x < NX; ++x)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        // one tile at a time (the empty statements tie the tile's copies out of and back into the
+        // accumulation registers to this place, so they do not pile up beside the loop's registers)
+        asm volatile("" : "+a"(oacc[x][qt][ct]));
+        scale_acc(oacc[x][qt][ct], alpha);
+        asm volatile("" : "+a"(oacc[x][qt][ct]));
+        F2_FENCE();
+      }
+  };
   // A reference has to move: the sub-tile just finished (keys at byte offset `off`; its products are not issued yet) is formed
-  // again against new references, everything before it is rescaled (App. B: h <- a h + a log(a) l).
+  // again against new references.
   auto redo = [&](int off, bf16x8 (&pbcur)[Q2][2], int keys_left) __attribute__((always_inline)) {
     f32x16 s[Q2];
     plain_logits(off, s);
     if (keys_left < 32) mask_tail(s, keys_left);
 #pragma unroll
-    for (int qt = 0; qt < Q2; ++qt) {
-      const float cand = qt == 0 ? row_max(std::integral_constant<int, 0>{}, s) : row_max(std::integral_constant<int, 1>{}, s);
-      const float m = fmaxf(msc[qt], cand + HEADROOM2);
-      const float dl = msc[qt] - m;  // log2 of the rescale factor, <= 0
-      const float alpha = __builtin_amdgcn_exp2f(dl);
-      if (ENT == 1) {
-        hsum[qt] = alpha * (hsum[qt] + dl * lsum[qt]);
-        lsum[qt] *= alpha;
-      }
-      ltil[qt] *= alpha;
-      msc[qt] = m;
-#pragma unroll
-      for (int x = 0; x < NX; ++x)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          // one tile at a time (the empty statements tie the tile's copies out of and back into the
-          // accumulation registers to this place, so they do not pile up beside the loop's registers)
-          asm volatile("" : "+a"(oacc[x][qt][ct]));
-          scale_acc(oacc[x][qt][ct], alpha);
-          asm volatile("" : "+a"(oacc[x][qt][ct]));
-          F2_FENCE();
-        }
-    }
-    static_for<0, 16>([&](auto kc) {
+    for (int qt = 0; qt < Q2; ++qt) move_reference(qt, subtile_max(s[qt]) * sc[qt]);
+    static_for<0, 8 * Q2>([&](auto kc) {
       score_scale(kc, s);
       score_exp(kc);
       score_sums(kc, pbcur);
@@ -457,16 +443,16 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
       } else {
         request(std::integral_constant<int, GI + PF - NG>{}, NS_OFF, NPV_OFF);
       }
-      static_for<0, 2>([&](auto qc) {
-        constexpr int SL = 2 * GI + decltype(qc)::value;
+      static_for<0, Q2>([&](auto qc) {
+        constexpr int SL = Q2 * GI + decltype(qc)::value;
         issue(gc, qc, snext, pbprev);
         // score pairs dealt evenly over the slots: pair k starts in slot floor(k NSL / 16), its exponents follow one
         // slot later and its sums two slots later (both clamped to the step's last slot).  Pairs in ascending
         // order, stages in their own order: a pair's stages that meet in one slot stay in sequence, and the sums
         // of pair k come before pair k + 2 reuses its buffers (it starts at least two slots after pair k).
-        static_for<0, 16>([&](auto kc) {
+        static_for<0, 8 * Q2>([&](auto kc) {
           constexpr int K = decltype(kc)::value;
-          constexpr int S0 = (K * NSL) / 16;
+          constexpr int S0 = (K * NSL) / (8 * Q2);
           constexpr int S1 = S0 + 1 < NSL ? S0 + 1 : NSL - 1;
           constexpr int S2 = S0 + 2 < NSL ? S0 + 2 : NSL - 1;
           if constexpr (S0 == SL) score_scale(kc, scur);
@@ -478,7 +464,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     });
 #pragma unroll
     for (int qt = 0; qt < Q2; ++qt) asm volatile("" : "+v"(pbcur[qt][0]), "+v"(pbcur[qt][1]));
-    if (__any(ltstep[0] > STEP_MAX2 || ltstep[1] > STEP_MAX2)) redo(NPV_OFF, pbcur, keys_left);
+    if (__any(ltstep[0] > STEP_MAX2 || ltstep[Q2 - 1] > STEP_MAX2)) redo(NPV_OFF, pbcur, keys_left);
 #pragma unroll
     for (int qt = 0; qt < Q2; ++qt) {
       ltil[qt] += ltstep[qt];
@@ -509,8 +495,8 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     if (active) {
       // logits of sub-tile 0, plain form; their row maxima are the first references
       plain_logits(0, sA);
-      msc[0] = fmaxf(msc[0], row_max(std::integral_constant<int, 0>{}, sA) + HEADROOM2);
-      msc[1] = fmaxf(msc[1], row_max(std::integral_constant<int, 1>{}, sA) + HEADROOM2);
+#pragma unroll
+      for (int qt = 0; qt < Q2; ++qt) msc[qt] = fmaxf(msc[qt], subtile_max(sA[qt]) * sc[qt] + HEADROOM2);
       // operands of the first groups of the first step (sub-tile 1 of slot 0; products against slot 3)
       static_for<0, PF>([&](auto gc) { request(gc, 32 * ROW_BYTES, 3 * TILE_BYTES + 32 * ROW_BYTES); });
     }
@@ -526,7 +512,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
       constexpr int kt = SLOT * TILE_BYTES;
       constexpr int kn = ((SLOT + 1) & 3) * TILE_BYTES;
       constexpr int HALF = 32 * ROW_BYTES;  // second sub-tile of a tile
-      const int left0 = tile_at(t) == ntiles - 1 ? last_left : 64;
+      const int left0 = t == ntiles - 1 ? last_left : 64;
       if (active) {
         // logits of (t, 1), products of (t-1, 1) [at t = 0: P^T = 0 against the cleared slot 3], softmax of (t, 0);
         // the step after it: logits of (t+1, 0), products of (t, 0)
@@ -555,8 +541,8 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
             const bf16x4 lo = rd_tr(t_off[x][ct][0] + pv_off + c * 16 * ROW_BYTES);
             const bf16x4 hi = rd_tr(t_off[x][ct][1] + pv_off + c * 16 * ROW_BYTES);
             const bf16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            mfma_a(oacc[x][0][ct], a, pbB[0][c]);
-            mfma_a(oacc[x][1][ct], a, pbB[1][c]);
+#pragma unroll
+            for (int qt = 0; qt < Q2; ++qt) mfma_a(oacc[x][qt][ct], a, pbB[qt][c]);
           }
     }
   }
@@ -663,11 +649,17 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   }
 }
 
-template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT>
-hipError_t launch_flash2(const FlashParams& P, hipStream_t st) {
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2>
+hipError_t launch_flash2(FlashParams P, long long problems, hipStream_t st) {
+  constexpr int ROWS = 32 * Q2;  // per wave
   // four K slots always (the logits need them), four V slots when values are multiplied: 128 KB at d = 128
   constexpr int LDS_BYTES = (OUT_V ? 2 : 1) * NSLOT * BK * D * 2;
-  auto kern = flash2_kernel<D, OUT_K, OUT_V, ENT, SPLIT>;
+  P.nqb = (P.nq + W2 * ROWS - 1) / (W2 * ROWS);
+  const long long total = problems * P.nqb * P.nsplit;
+  if (total > 0x3fffffffLL) return hipErrorInvalidValue;
+  P.total_blocks = (int)total;
+  P.blocks_per_xcd = (P.total_blocks + 7) / 8;
+  auto kern = flash2_kernel<D, OUT_K, OUT_V, ENT, SPLIT, Q2>;
   static bool configured = false;  // the attribute is per function, set once per process
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
@@ -683,12 +675,11 @@ hipError_t launch_flash2(const FlashParams& P, hipStream_t st) {
 
 }  // namespace
 
-int flash2_query_block() { return BQ2; }
-
 // Exact attention of a contiguous run of nrows query rows per head over all keys (Sec. 3.3) on this kernel, the keys
 // cut into `ns` ranges of keys_per_split (a multiple of the tile) whose partial results go to part_o / part_lse
-// for the merge (ns == 1: straight to out / lse).  Same 256-row query blocks and partial-result layout as the
+// for the merge (ns == 1: straight to out / lse).  Same query blocks and partial-result layout as the
 // one-tile kernel's pass.
+template <int D>
 hipError_t launch_first_frame_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse,
                                      float* part_o, float* part_lse, const Dims& dm, int nrows, int ns,
                                      int keys_per_split, hipStream_t st) {
@@ -697,49 +688,63 @@ hipError_t launch_first_frame_flash2(const bf16_t* q, const bf16_t* k, const bf1
   P.q_rows_per_problem = dm.N; P.k_rows_per_problem = dm.N;
   P.nq = nrows;
   P.nk = (int)dm.N;
-  P.nqb = (nrows + BQ2 - 1) / BQ2;
   P.nsplit = ns;
   P.keys_per_split = keys_per_split;
-  const long long total = (long long)dm.BH * P.nqb * ns;
-  if (total > 0x3fffffffLL) return hipErrorInvalidValue;
-  P.total_blocks = (int)total;
-  P.blocks_per_xcd = (P.total_blocks + 7) / 8;
-  P.row_scale = 1.0f / sqrtf((float)dm.d);
+  P.row_scale = 1.0f / sqrtf((float)D);
   P.cr_min = 0.f;
-  const bool split = ns > 1;
-  if (dm.d == 128) return split ? launch_flash2<128, false, true, 0, true>(P, st) : launch_flash2<128, false, true, 0, false>(P, st);
-  return split ? launch_flash2<64, false, true, 0, true>(P, st) : launch_flash2<64, false, true, 0, false>(P, st);
+  return ns > 1 ? launch_flash2<D, false, true, 0, true, 2>(P, dm.BH, st) : launch_flash2<D, false, true, 0, false, 2>(P, dm.BH, st);
 }
 
-// One R-update on the one-wave-per-SIMD kernel: alpha_L, c_L (and lse if not null), plus y when v is given.
+// Fitting update: query blocks of 128 rows (one query tile per wave) or of 256?  Of the short ones three share a compute unit at
+// d = 64, two at d = 128; of the long ones two and one.  The short ones hide each other's start and end and waste less on a ragged
+// last block or round; the long ones read an operand from LDS for two products, which counts where the launch is long and the
+// device's power is the limit.  A unit works through its blocks in groups as large as it holds, so the two launches' times
+// follow from the blocks per unit, with the time of a group of 1, 2, 3 blocks against the long blocks' largest group measured on 10 launch
+// sizes (4 .. 972 frames) x 12 frame sizes (130 .. 3600 tokens).  Short against long, us: d = 64: 16 frames of 1000 16.8 / 24.6, 130 of 300
+// 11.1 / 16.5, 80 of 1280 52.2 / 46.7, 252 of 2048 308 / 289; d = 128: 130 of 300 15.0 / 29.5, 130 of 1456 158 / 176, 252 of 2048 532 / 509.
+// (With values d = 64 always takes the short blocks: the long ones leave room for one wave per SIMD there, 252 frames of 512 .. 3600
+// 1 .. 10 % slower; d = 128 the long ones: the tiles leave LDS for one workgroup either way.)
+template <int D>
+bool short_blocks_faster(long long problems, int b) {
+  auto units = [&](int rows) -> long long { return (problems * ((b + rows - 1) / rows) + 255) / 256; };  // blocks per compute unit
+  const long long n1 = units(128), n2 = units(256);
+  if constexpr (D == 64) {
+    const double rest1[3] = {0.0, 0.43, 0.64};
+    return 0.87 * (double)(n1 / 3) + rest1[n1 % 3] < (double)(n2 / 2) + 0.64 * (double)(n2 % 2);
+  } else {
+    const double pair = b > 1024 ? 1.06 : 0.95;
+    return pair * (double)(n1 / 2) + 0.66 * (double)(n1 % 2) < (double)n2;
+  }
+}
+
+// One R-update: alpha_L, c_L (and lse if not null), plus y when v is given.
+template <int D>
 hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL,
                                   float* cL, bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min,
                                   int entropy_mode, hipStream_t st) {
-  if (!(dm.d == 128 || dm.d == 64) || (v == nullptr) != (y == nullptr)) return hipErrorInvalidValue;
+  if (dm.d != D || (v == nullptr) != (y == nullptr)) return hipErrorInvalidValue;
   FlashParams P = {};
   P.q = aR; P.cR = cR; P.k = k; P.v = v; P.outk = aL; P.outv = y; P.cl = cL; P.lse = lse;
   P.q_rows_per_problem = dm.b; P.k_rows_per_problem = dm.b;
   P.nq = dm.b; P.nk = dm.b;
-  P.nqb = (dm.b + BQ2 - 1) / BQ2;
   P.nsplit = 1;
   P.keys_per_split = ((dm.b + BK - 1) / BK) * BK;
-  const long long total = (long long)dm.BH * dm.T * P.nqb;
-  if (total > 0x3fffffffLL) return hipErrorInvalidValue;
-  P.total_blocks = (int)total;
-  P.blocks_per_xcd = (P.total_blocks + 7) / 8;
   P.row_scale = row_scale; P.cr_min = cr_min;
-  // 0: every query block of a frame walks the key tiles in the same order, so that the blocks resident on one XCD ask
-  // for the same tile at about the same time and all but the first request hit its L2 (starting each block at its own
-  // tile instead measured 1.9x the algorithmic HBM reads at the same speed)
-  P.own_tile_first = 0;
+  const long long problems = (long long)dm.BH * dm.T;
   const bool ident = entropy_mode == VMONARCH_ENTROPY_IDENTITY;
-  const bool d128 = dm.d == 128;
-  if (v != nullptr) {
-    if (ident) return d128 ? launch_flash2<128, true, true, 2, false>(P, st) : launch_flash2<64, true, true, 2, false>(P, st);
-    return d128 ? launch_flash2<128, true, true, 1, false>(P, st) : launch_flash2<64, true, true, 1, false>(P, st);
-  }
-  if (ident) return d128 ? launch_flash2<128, true, false, 2, false>(P, st) : launch_flash2<64, true, false, 2, false>(P, st);
-  return d128 ? launch_flash2<128, true, false, 1, false>(P, st) : launch_flash2<64, true, false, 1, false>(P, st);
+  constexpr int QV = D == 64 ? 1 : 2;  // see short_blocks_faster
+  if (v != nullptr)
+    return ident ? launch_flash2<D, true, true, 2, false, QV>(P, problems, st)
+                 : launch_flash2<D, true, true, 1, false, QV>(P, problems, st);
+  if (ident) return launch_flash2<D, true, false, 2, false, 1>(P, problems, st);
+  return short_blocks_faster<D>(problems, dm.b) ? launch_flash2<D, true, false, 1, false, 1>(P, problems, st)
+                                                : launch_flash2<D, true, false, 1, false, 2>(P, problems, st);
 }
+
+// This file is compiled once per head dimension.
+template hipError_t launch_first_frame_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*, float*,
+                                                           float*, const Dims&, int, int, int, hipStream_t);
+template hipError_t launch_r_update_flash2<VM_FLASH2_D>(const bf16_t*, const float*, const bf16_t*, const bf16_t*, bf16_t*, float*,
+                                                        bf16_t*, float*, const Dims&, float, float, int, hipStream_t);
 
 }  // namespace vm

@@ -62,7 +62,6 @@ struct FlashParams {
   const int* q_index;   // query row r of a problem is row q_index[r] of it (null: row r); entries
                         // outside [0, q_index_limit) are skipped
   int q_index_limit;
-  int own_tile_first;   // flash2: queries and keys are the same rows (R-update): start the key loop at the query block's own tile
 };
 
 __device__ __forceinline__ bf16x8 lds_read_b128(const char* p) { return *reinterpret_cast<const bf16x8*>(p); }
