@@ -374,7 +374,7 @@ def main() -> int:
         """The short-frame kernel that takes an R-update of this workload, or None (the library's rule for variant 2)."""
         if not bf16 or d not in (64, 128) or variant != 2 or not online or (with_v and not binding.get_fused_apply()):
             return None
-        return "frame_kernel" if b <= ((224 if d == 64 else 192) if with_v else 160) else None
+        return "frame_kernel" if b <= ((224 if d == 64 else 192 if BH * T <= 256 else 128) if with_v else 160) else None
     if "r_update_last" in phases:
         # dominant kernel (the longest single launch of a call): the R-update of the last sweep, which forms
         # the logits, R K (alpha_L), c_L and R V (y) in one launch: three b x b x d products per frame.

@@ -105,7 +105,7 @@ int vmonarch_get_manual_control(int* cr_control, int* cl_control, float* cl_valu
 /* Which bf16 MFMA kernel runs an R-update: 0 the kernels with two waves per SIMD and one 32-query
  * tile per wave; 1 the kernel whose waves take one or two 32-query tiles by the size of the launch
  * and whose accumulators live in accumulation registers; 2 (default) each update on the kernel
- * measured faster for it: short frames (up to 160 .. 224 tokens; online entropy and fused apply only)
+ * measured faster for it: short frames (up to 128 .. 224 tokens; online entropy and fused apply only)
  * on the kernel that takes a whole frame per workgroup; else that of 1, but for updates with values of
  * at most 128 tokens, which take that of 0. Exact attention of a contiguous row range
  * (first frame, vmonarch_recompute_rows) runs on the kernel of 1 unless the variant is 0; a row

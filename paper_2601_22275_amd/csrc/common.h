@@ -139,7 +139,7 @@ template <int D>
 hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL,
                                   float* cL, bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min,
                                   int entropy_mode, hipStream_t st);
-// frame.hip : the same updates for short frames (b <= 160 .. 224; d == 64 or 128), one workgroup per frame
+// frame.hip : the same updates for short frames (b <= 128 .. 224; d == 64 or 128), one workgroup per frame
 bool frame_supported(const Dims& dm, bool with_v);
 hipError_t launch_r_update_frame(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL,
                                  bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min, hipStream_t st);

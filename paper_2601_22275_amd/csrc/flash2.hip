@@ -75,13 +75,21 @@ __device__ __forceinline__ void static_for(F&& f) {
 // handling cannot see, so wherever vector code follows an MFMA closely this wait is written out.
 #define F2_MFMA_RESULT_WAIT() asm volatile("s_nop 7\n\ts_nop 3" ::: "memory")
 
+// Key rows per LDS tile: 64, or 32 where two workgroups are to share a compute unit and the tiles of keys and values would leave LDS
+// for one.
+template <int D, bool OUT_V, int Q2>
+constexpr int tile_rows() {
+  return D == 128 && OUT_V && Q2 == 1 ? 32 : 64;
+}
+
 // ENT: c_L not wanted (0), online (1) or in the identity form (2)
 // Q2: 32-query tiles per wave; W2 Q2 of them are the workgroup's query block
 template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2>
-__global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
+__global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1 ? 2 : 1) flash2_kernel(FlashParams P) {
   using G = RowGeo<D>;
   constexpr int ROW_BYTES = G::ROW_BYTES;
-  constexpr int TILE_BYTES = BK * ROW_BYTES;  // 16 KB (d = 128) or 8 KB (d = 64)
+  constexpr int BT = tile_rows<D, OUT_V, Q2>();
+  constexpr int TILE_BYTES = BT * ROW_BYTES;
   constexpr int KS = G::KS;                   // k-steps of S^T = K Q^T
   constexpr int CT = G::CT;                   // 32-channel tiles of an output row
   constexpr int CH = G::CH;                   // 16-byte chunks per row
@@ -90,6 +98,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   constexpr int NX = (OUT_K ? 1 : 0) + (OUT_V ? 1 : 0);  // accumulator sets: [R K][R V]
   constexpr int XV = OUT_K ? 1 : 0;                       // index of the R V set
   static_assert(OUT_K || OUT_V, "at least one product");
+  constexpr bool TIGHT = D == 128 && NX == 2 && Q2 == 1;  // two workgroups on a unit: 128 + 128 registers are just enough
   constexpr int BQ2 = 32 * Q2 * W2;  // query rows per workgroup
   auto swz = [](int row) { return G::swz(row); };
   extern __shared__ __attribute__((aligned(16))) char smem[];  // [K|V][NSLOT][64 rows][2 D bytes]
@@ -117,8 +126,8 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   const int kbeg = split * P.keys_per_split;
   const int kend = min(P.nk, kbeg + P.keys_per_split);
   const int nkeys = kend - kbeg;
-  const int ntiles = (nkeys + BK - 1) / BK;
-  const int last_left = nkeys - (ntiles - 1) * BK;  // 1..64 keys in the last tile
+  const int ntiles = (nkeys + BT - 1) / BT;
+  const int last_left = nkeys - (ntiles - 1) * BT;  // 1 .. BT keys in the last tile
   const long long qrow0 = (long long)prob * P.q_rows_per_problem;
   const char* kbase = reinterpret_cast<const char*>(P.k + ((long long)prob * P.k_rows_per_problem + kbeg) * D);
   const char* vbase = OUT_V ? reinterpret_cast<const char*>(P.v + ((long long)prob * P.k_rows_per_problem + kbeg) * D) : nullptr;
@@ -136,8 +145,8 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   // the next LDS read, a few instructions after they were issued.  The loop below waits for them
   // itself, before the barrier that publishes a tile.  Loads the compiler does not know about
   // only make its own vmcnt waits longer, never shorter: the counter retires in order.
-  constexpr int NR = BK / (RPI * W2);
-  static_assert(BK % (RPI * W2) == 0, "every wave issues the same number of loads per tile");
+  constexpr int NR = BT / (RPI * W2);
+  static_assert(BT % (RPI * W2) == 0, "every wave issues the same number of loads per tile");
   static_assert((RPI * W2) % 16 == 0, "the rows of one lane share a swizzle");
   const int st_key = RPI * wave + lane / CH;  // + RPI W2 r
   const int st_lc = (lane % CH) ^ swz(st_key);
@@ -149,7 +158,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     const unsigned kb = lds_base + (t & (NSLOT - 1)) * TILE_BYTES;
     const char* ksrc = kbase + (long long)t * TILE_BYTES;
     const char* vsrc = OUT_V ? vbase + (long long)t * TILE_BYTES : nullptr;
-    const bool ragged = t == ntiles - 1 && last_left < BK;
+    const bool ragged = t == ntiles - 1 && last_left < BT;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       unsigned off = goff[r];
@@ -197,7 +206,9 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   // Transpose reads (A of O^T += X^T P^T): 16-lane group u = lane / 16 -> g = u / 2, channel
   // half u & 1; lane r' of the group supplies key (r' / 4) and channels 4 (r' & 3) .. + 3.  The V slots
   // lie beyond the reach of the 16-bit offset field, hence a second set of registers for them.
-  unsigned t_off[NX][CT][2];
+  constexpr int NTO = NX == 2 && 2 * NSLOT * TILE_BYTES > 65536 ? 2 : 1;  // the 16-bit offset field reaches 64 KB
+  constexpr int V_IMM = NX == 2 && NTO == 1 ? V_OFF : 0;
+  unsigned t_off[NTO][CT][2];
   {
     const int rp = lane & 15;
     const int chh = (lane >> 4) & 1;
@@ -209,19 +220,21 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
         const int lc = 4 * ct + 2 * chh + ((rp >> 1) & 1);
         const unsigned o = lds_base + key * ROW_BYTES + ((lc ^ swz(key)) << 4) + ((rp & 1) << 3);
         if (OUT_K) t_off[0][ct][hh] = o;
-        if (OUT_V) t_off[XV][ct][hh] = o + V_OFF;
+        if (OUT_V && (!OUT_K || NTO == 2)) t_off[NTO - 1][ct][hh] = o + V_OFF;
       }
   }
   // keep the compiler from re-deriving these from one another inside the loop
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(a_off[ks]));
 #pragma unroll
-  for (int x = 0; x < NX; ++x)
+  for (int x = 0; x < NTO; ++x)
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) asm volatile("" : "+v"(t_off[x][ct][0]), "+v"(t_off[x][ct][1]));
   typedef __attribute__((address_space(3))) const bf16x8* lds_b128_ptr;
   typedef __attribute__((address_space(3))) bf16x4* lds_b64_ptr;
-  auto rd_row = [&](unsigned addr) __attribute__((always_inline)) -> bf16x8 { return *(lds_b128_ptr)(unsigned long long)addr; };
+  auto rd_row = [&](auto kc, int off) __attribute__((always_inline)) -> bf16x8 {  // A of k-step kc, keys at byte offset off
+    return *(lds_b128_ptr)(unsigned long long)(a_off[decltype(kc)::value] + off);
+  };
   auto rd_tr = [&](unsigned addr) __attribute__((always_inline)) -> bf16x4 {
     return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_b64_ptr)(unsigned long long)addr);
   };
@@ -283,38 +296,39 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   constexpr int NPV = 2 * CT * NX;
   constexpr int NG = KS + NPV;
   constexpr int NSL = Q2 * NG;  // MFMA slots per step
-  constexpr int PF = 2;        // groups between an operand's request and its use
-  static_assert(NG % 4 == 0, "ring positions repeat from step to step");
-  bf16x8 ring[4];
+  constexpr int PF = TIGHT ? 1 : 2;  // groups between an operand's request and its use
+  constexpr int RING = TIGHT ? 2 : 4;
+  static_assert(NG % RING == 0 && RING > PF, "ring positions repeat from step to step");
+  bf16x8 ring[RING];
   // request the A operand of group `gi` of a step whose logits come from byte offset s_off (slot and
   // sub-tile of the K tile) and whose products read byte offset pv_off (slot and sub-tile, K and V alike)
   auto request = [&](auto gc, int s_off, int pv_off) __attribute__((always_inline)) {
     constexpr int GI = decltype(gc)::value;
     if constexpr (GI < KS) {
-      ring[GI & 3] = rd_row(a_off[GI] + s_off);
+      ring[GI % RING] = rd_row(gc, s_off);
     } else {
       constexpr int h = GI - KS;
       constexpr int c = h / (CT * NX);
       constexpr int ct = (h % (CT * NX)) / NX;
       constexpr int x = h % NX;
-      const bf16x4 lo = rd_tr(t_off[x][ct][0] + pv_off + c * 16 * ROW_BYTES);
-      const bf16x4 hi = rd_tr(t_off[x][ct][1] + pv_off + c * 16 * ROW_BYTES);
-      ring[GI & 3] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      const bf16x4 lo = rd_tr(t_off[NTO == 2 ? x : 0][ct][0] + pv_off + (c * 16 * ROW_BYTES + (x == 1 ? V_IMM : 0)));
+      const bf16x4 hi = rd_tr(t_off[NTO == 2 ? x : 0][ct][1] + pv_off + (c * 16 * ROW_BYTES + (x == 1 ? V_IMM : 0)));
+      ring[GI % RING] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     }
   };
   auto issue = [&](auto gc, auto qc, f32x16 (&snext)[Q2], bf16x8 (&pbprev)[Q2][2]) __attribute__((always_inline)) {
     constexpr int GI = decltype(gc)::value;
     constexpr int qt = decltype(qc)::value;
     if constexpr (GI == 0) {
-      mfma_first(snext[qt], ring[GI & 3], qreg[qt][GI]);
+      mfma_first(snext[qt], ring[GI % RING], qreg[qt][GI]);
     } else if constexpr (GI < KS) {
-      mfma_v(snext[qt], ring[GI & 3], qreg[qt][GI]);
+      mfma_v(snext[qt], ring[GI % RING], qreg[qt][GI]);
     } else {
       constexpr int h = GI - KS;
       constexpr int c = h / (CT * NX);
       constexpr int ct = (h % (CT * NX)) / NX;
       constexpr int x = h % NX;
-      mfma_a(oacc[x][qt][ct], ring[GI & 3], pbprev[qt][c]);
+      mfma_a(oacc[x][qt][ct], ring[GI % RING], pbprev[qt][c]);
     }
   };
 
@@ -364,9 +378,12 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   // rows keys_left .. 31 of the last sub-tile are copies of the last valid row: push their logits far down so that they get
   // probability zero
   auto mask_tail = [&](f32x16 (&s)[Q2], int keys_left) __attribute__((always_inline)) {
+    // register r is key 8 (r / 4) + 4 g + r % 4; compared as below the lane keeps one limit, not sixteen key numbers across the loop
+    int limit = keys_left - 4 * g;
+    asm volatile("" : "+v"(limit));
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float off = (8 * (r >> 2) + 4 * g + (r & 3)) >= keys_left ? -1.0e9f : 0.f;
+      const float off = 8 * (r >> 2) + (r & 3) >= limit ? -1.0e9f : 0.f;
 #pragma unroll
       for (int qt = 0; qt < Q2; ++qt) s[qt][r] += off;
     }
@@ -375,7 +392,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
   auto plain_logits = [&](int off, f32x16 (&s)[Q2]) __attribute__((always_inline)) {
     static_for<0, KS>([&](auto kc) {
       constexpr int ks = decltype(kc)::value;
-      const bf16x8 a = rd_row(a_off[ks] + off);
+      const bf16x8 a = rd_row(kc, off);
       if constexpr (ks == 0) {
 #pragma unroll
         for (int qt = 0; qt < Q2; ++qt) mfma_first(s[qt], a, qreg[qt][ks]);
@@ -418,6 +435,8 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     if (keys_left < 32) mask_tail(s, keys_left);
 #pragma unroll
     for (int qt = 0; qt < Q2; ++qt) move_reference(qt, subtile_max(s[qt]) * sc[qt]);
+    plain_logits(off, s);  // again: kept meanwhile they would sit beside the copies of the accumulators
+    if (keys_left < 32) mask_tail(s, keys_left);
     static_for<0, 8 * Q2>([&](auto kc) {
       score_scale(kc, s);
       score_exp(kc);
@@ -435,12 +454,14 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     constexpr int NS_OFF = decltype(ns_c)::value, NPV_OFF = decltype(npv_c)::value;
     if (keys_left < 32) mask_tail(scur, keys_left);
     F2_FENCE();
+    // (with one sub-tile per tile the next step's logits are those of a tile that may still be travelling when this one ends)
+    if constexpr (BT == 32) static_for<0, PF>([&](auto gc) { request(gc, S_OFF, PV_OFF); });
     static_for<0, NG>([&](auto gc) {
       constexpr int GI = decltype(gc)::value;
       // request the operand of group GI + PF (of the next step beyond the end of this one)
       if constexpr (GI + PF < NG) {
         request(std::integral_constant<int, GI + PF>{}, S_OFF, PV_OFF);
-      } else {
+      } else if constexpr (BT == 64) {
         request(std::integral_constant<int, GI + PF - NG>{}, NS_OFF, NPV_OFF);
       }
       static_for<0, Q2>([&](auto qc) {
@@ -498,7 +519,7 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
 #pragma unroll
       for (int qt = 0; qt < Q2; ++qt) msc[qt] = fmaxf(msc[qt], subtile_max(sA[qt]) * sc[qt] + HEADROOM2);
       // operands of the first groups of the first step (sub-tile 1 of slot 0; products against slot 3)
-      static_for<0, PF>([&](auto gc) { request(gc, 32 * ROW_BYTES, 3 * TILE_BYTES + 32 * ROW_BYTES); });
+      if constexpr (BT == 64) static_for<0, PF>([&](auto gc) { request(gc, 32 * ROW_BYTES, 3 * TILE_BYTES + 32 * ROW_BYTES); });
     }
     // Four tiles per trip so that every LDS slot offset is an instruction immediate.
     auto tile_iteration = [&](auto slot_c, int t) __attribute__((always_inline)) {
@@ -512,8 +533,13 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
       constexpr int kt = SLOT * TILE_BYTES;
       constexpr int kn = ((SLOT + 1) & 3) * TILE_BYTES;
       constexpr int HALF = 32 * ROW_BYTES;  // second sub-tile of a tile
-      const int left0 = t == ntiles - 1 ? last_left : 64;
-      if (active) {
+      const int left0 = t == ntiles - 1 ? last_left : BT;
+      if (active && BT == 32) {
+        // one sub-tile per tile: logits of t+1, products of t-1 [at t = 0: P^T = 0 against the cleared slot 3], softmax of t
+        constexpr int k2 = ((SLOT + 2) & 3) * TILE_BYTES;
+        step(std::integral_constant<int, kn>{}, std::integral_constant<int, kp>{}, std::integral_constant<int, k2>{},
+             std::integral_constant<int, kt>{}, SLOT % 2 ? sB : sA, SLOT % 2 ? sA : sB, SLOT % 2 ? pbA : pbB, SLOT % 2 ? pbB : pbA, left0);
+      } else if (active) {
         // logits of (t, 1), products of (t-1, 1) [at t = 0: P^T = 0 against the cleared slot 3], softmax of (t, 0);
         // the step after it: logits of (t+1, 0), products of (t, 0)
         step(std::integral_constant<int, kt + HALF>{}, std::integral_constant<int, kp + HALF>{},
@@ -531,15 +557,24 @@ __global__ void __launch_bounds__(64 * W2) flash2_kernel(FlashParams P) {
     }
     if (active) {
       // drain: the products of the last sub-tile, (ntiles-1, 1), plain form
-      const int pv_off = ((ntiles - 1) & 3) * TILE_BYTES + 32 * ROW_BYTES;
+      const int pv_off = ((ntiles - 1) & 3) * TILE_BYTES + (BT - 32) * ROW_BYTES;
+      // softmax weights of the last sub-tile: the second of a tile, or the only one, whose set goes by the slot
+      if (BT == 32 && (ntiles & 1)) {
+#pragma unroll
+        for (int qt = 0; qt < Q2; ++qt) {
+          pbB[qt][0] = pbA[qt][0];
+          pbB[qt][1] = pbA[qt][1];
+        }
+        asm volatile("s_nop 1" ::: "memory");
+      }
 #pragma unroll
       for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
           for (int x = 0; x < NX; ++x) {
-            const bf16x4 lo = rd_tr(t_off[x][ct][0] + pv_off + c * 16 * ROW_BYTES);
-            const bf16x4 hi = rd_tr(t_off[x][ct][1] + pv_off + c * 16 * ROW_BYTES);
+            const bf16x4 lo = rd_tr(t_off[NTO == 2 ? x : 0][ct][0] + pv_off + (c * 16 * ROW_BYTES + (x == 1 ? V_IMM : 0)));
+            const bf16x4 hi = rd_tr(t_off[NTO == 2 ? x : 0][ct][1] + pv_off + (c * 16 * ROW_BYTES + (x == 1 ? V_IMM : 0)));
             const bf16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
             for (int qt = 0; qt < Q2; ++qt) mfma_a(oacc[x][qt][ct], a, pbB[qt][c]);
@@ -653,7 +688,7 @@ template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2>
 hipError_t launch_flash2(FlashParams P, long long problems, hipStream_t st) {
   constexpr int ROWS = 32 * Q2;  // per wave
   // four K slots always (the logits need them), four V slots when values are multiplied: 128 KB at d = 128
-  constexpr int LDS_BYTES = (OUT_V ? 2 : 1) * NSLOT * BK * D * 2;
+  constexpr int LDS_BYTES = (OUT_V ? 2 : 1) * NSLOT * tile_rows<D, OUT_V, Q2>() * D * 2;
   P.nqb = (P.nq + W2 * ROWS - 1) / (W2 * ROWS);
   const long long total = problems * P.nqb * P.nsplit;
   if (total > 0x3fffffffLL) return hipErrorInvalidValue;
@@ -695,15 +730,15 @@ hipError_t launch_first_frame_flash2(const bf16_t* q, const bf16_t* k, const bf1
   return ns > 1 ? launch_flash2<D, false, true, 0, true, 2>(P, dm.BH, st) : launch_flash2<D, false, true, 0, false, 2>(P, dm.BH, st);
 }
 
-// Fitting update: query blocks of 128 rows (one query tile per wave) or of 256?  Of the short ones three share a compute unit at
-// d = 64, two at d = 128; of the long ones two and one.  The short ones hide each other's start and end and waste less on a ragged
-// last block or round; the long ones read an operand from LDS for two products, which counts where the launch is long and the
-// device's power is the limit.  A unit works through its blocks in groups as large as it holds, so the two launches' times
-// follow from the blocks per unit, with the time of a group of 1, 2, 3 blocks against the long blocks' largest group measured on 10 launch
-// sizes (4 .. 972 frames) x 12 frame sizes (130 .. 3600 tokens).  Short against long, us: d = 64: 16 frames of 1000 16.8 / 24.6, 130 of 300
-// 11.1 / 16.5, 80 of 1280 52.2 / 46.7, 252 of 2048 308 / 289; d = 128: 130 of 300 15.0 / 29.5, 130 of 1456 158 / 176, 252 of 2048 532 / 509.
-// (With values d = 64 always takes the short blocks: the long ones leave room for one wave per SIMD there, 252 frames of 512 .. 3600
-// 1 .. 10 % slower; d = 128 the long ones: the tiles leave LDS for one workgroup either way.)
+// Query blocks of 128 rows (one query tile per wave) or of 256?  Of the short ones three share a compute unit at
+// d = 64 (two with values), two at d = 128; of the long ones two and one.  The short ones hide each other's start and end and waste
+// less on a ragged last block or round; the long ones read an operand from LDS for two products, which counts where the launch is long
+// and the device's power is the limit.  A unit works through its blocks in groups as large as it holds, so the two launches'
+// times follow from the blocks per unit, with the time of a group of 1, 2, 3 blocks against the long blocks' largest group measured on
+// 10 launch sizes (4 .. 972 frames) x 12 frame sizes (130 .. 3600 tokens).  Short against long, us: d = 64: 16 frames of 1000 16.8 / 24.6,
+// 130 of 300 11.1 / 16.5, 80 of 1280 52.2 / 46.7, 252 of 2048 308 / 289; d = 128: 130 of 300 15.0 / 29.5, 130 of 1456 158 / 176, 252
+// of 2048 532 / 509, with values 20.8 / 42.1, 230 / 257, 793 / 741.  With values d = 64 always takes the short blocks: the long
+// ones leave room for one wave per SIMD there (252 frames of 512 .. 3600 1 .. 10 % slower).
 template <int D>
 bool short_blocks_faster(long long problems, int b) {
   auto units = [&](int rows) -> long long { return (problems * ((b + rows - 1) / rows) + 255) / 256; };  // blocks per compute unit
@@ -712,7 +747,7 @@ bool short_blocks_faster(long long problems, int b) {
     const double rest1[3] = {0.0, 0.43, 0.64};
     return 0.87 * (double)(n1 / 3) + rest1[n1 % 3] < (double)(n2 / 2) + 0.64 * (double)(n2 % 2);
   } else {
-    const double pair = b > 1024 ? 1.06 : 0.95;
+    const double pair = b > 900 ? 1.06 : 0.95;
     return pair * (double)(n1 / 2) + 0.66 * (double)(n1 % 2) < (double)n2;
   }
 }
@@ -731,14 +766,16 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
   P.keys_per_split = ((dm.b + BK - 1) / BK) * BK;
   P.row_scale = row_scale; P.cr_min = cr_min;
   const long long problems = (long long)dm.BH * dm.T;
-  const bool ident = entropy_mode == VMONARCH_ENTROPY_IDENTITY;
-  constexpr int QV = D == 64 ? 1 : 2;  // see short_blocks_faster
-  if (v != nullptr)
-    return ident ? launch_flash2<D, true, true, 2, false, QV>(P, problems, st)
-                 : launch_flash2<D, true, true, 1, false, QV>(P, problems, st);
-  if (ident) return launch_flash2<D, true, false, 2, false, 1>(P, problems, st);
-  return short_blocks_faster<D>(problems, dm.b) ? launch_flash2<D, true, false, 1, false, 1>(P, problems, st)
-                                                : launch_flash2<D, true, false, 1, false, 2>(P, problems, st);
+  const bool short_blocks = short_blocks_faster<D>(problems, dm.b);
+  auto launch = [&](auto ent) -> hipError_t {
+    constexpr int ENT = decltype(ent)::value;
+    if (v == nullptr)
+      return short_blocks ? launch_flash2<D, true, false, ENT, false, 1>(P, problems, st) : launch_flash2<D, true, false, ENT, false, 2>(P, problems, st);
+    if constexpr (D == 128)
+      if (!short_blocks) return launch_flash2<D, true, true, ENT, false, 2>(P, problems, st);
+    return launch_flash2<D, true, true, ENT, false, 1>(P, problems, st);
+  };
+  return entropy_mode == VMONARCH_ENTROPY_IDENTITY ? launch(std::integral_constant<int, 2>{}) : launch(std::integral_constant<int, 1>{});
 }
 
 // This file is compiled once per head dimension.

@@ -121,17 +121,18 @@ def test_many_frames_and_no_row_scale(env, d):
             assert U.rel_l2(y[h][rows], np.matmul(R, v3)[0]) <= 4e-3
 
 
-@pytest.mark.parametrize("d,b,frames", [(64, 256, 512), (64, 260, 16), (64, 449, 256), (128, 161, 8), (128, 1290, 256), (128, 1281, 16)])
-def test_query_blocks_of_the_streaming_kernel(env, d, b, frames):
-    """Updates without values take query blocks of 128 or of 256 rows by the size of the launch: the same two frames, repeated
+@pytest.mark.parametrize("d,b,frames", [(64, 256, 512), (64, 260, 16), (64, 449, 256), (128, 161, 8), (128, 193, 300), (128, 1290, 256), (128, 1281, 16)])
+@pytest.mark.parametrize("with_v", [False, True])
+def test_query_blocks_of_the_streaming_kernel(env, d, b, frames, with_v):
+    """Updates take query blocks of 128 or of 256 rows by the size of the launch: the same two frames, repeated
     as often as it takes to reach either, against the oracle (bounds as above), every repeat bit-identical."""
     torch, binding, dev = env
     s = 1.0 / math.sqrt(d)
-    aR, K, _, cR = _inputs(1, b, d, 11 * b + d)
-    tq, tk = (U.to_device(x, torch, dev).reshape(1, 2, b, d).repeat(1, frames // 2, 1, 1).view(1, 1, -1, d) for x in (aR, K))
+    aR, K, V, cR = _inputs(1, b, d, 11 * b + d)
+    tq, tk, tv = (U.to_device(x, torch, dev).reshape(1, 2, b, d).repeat(1, frames // 2, 1, 1).view(1, 1, -1, d) for x in (aR, K, V))
     tc = torch.from_numpy(cR).to(dev).view(1, 2, b).repeat(1, frames // 2, 1).view(1, 1, -1)
-    aL, cL, y, lse = binding.r_update_lse(tq, tc, tk, None, frames, 1, b, s, 0.1)
-    got = [x.view(frames // 2, -1) for x in (aL, cL, lse)]
+    aL, cL, y, lse = binding.r_update_lse(tq, tc, tk, tv if with_v else None, frames, 1, b, s, 0.1)
+    got = [x.view(frames // 2, -1) for x in ((aL, cL, lse, y) if with_v else (aL, cL, lse))]
     for x in got:
         assert bool((x == x[0]).all())
     gaL = U.from_device(got[0][0].view(1, 1, 2 * b, d))[0].reshape(2, b, d)
@@ -139,6 +140,9 @@ def test_query_blocks_of_the_streaming_kernel(env, d, b, frames):
     for h in range(2):
         c = np.maximum(cR[h].reshape(1, b).astype(np.float64), 0.1)
         q3, k3 = (U.to_f64(x[h]).reshape(1, b, d) for x in (aR, K))
-        oaL, ocL, _ = O.r_update(q3 * s, c, k3, 0.1)
+        oaL, ocL, R = O.r_update(q3 * s, c, k3, 0.1)
         assert U.rel_l2(gaL[h], oaL[:, 0]) <= 4e-3
+        if with_v:
+            gy = U.from_device(got[3][0].view(1, 1, 2 * b, d))[0].reshape(2, b, d)[h]
+            assert U.rel_l2(gy, R[0] @ U.to_f64(V[h]).reshape(b, d)) <= 4e-3
         assert U.max_abs(gcL[h], ocL.reshape(-1)) <= 2.0 ** -8
