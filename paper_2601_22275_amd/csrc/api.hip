@@ -320,9 +320,9 @@ int first_frame_any<bf16_t>(const bf16_t* q, const bf16_t* k, const bf16_t* v, b
 }
 
 template <typename E>
-int sink_average_any(const E* q, const E* k, const E* v, E* out, const Dims& dm, hipStream_t st);
+int sink_average_any(const E* q, const E* k, const E* v, E* out, const Dims& dm, int flash_variant, hipStream_t st);
 template <>
-int sink_average_any<float>(const float* q, const float* k, const float* v, float* out, const Dims& dm, hipStream_t st) {
+int sink_average_any<float>(const float* q, const float* k, const float* v, float* out, const Dims& dm, int, hipStream_t st) {
   hipError_t e = f32_attend_supported(dm, true, dm.BH, dm.N, dm.b, {q, k, v, out})
                      ? launch_sink_average_f32(q, k, v, out, dm, st)
                      : launch_sink_average_generic<float>(q, k, v, out, dm, st);
@@ -330,8 +330,8 @@ int sink_average_any<float>(const float* q, const float* k, const float* v, floa
 }
 template <>
 int sink_average_any<bf16_t>(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const Dims& dm,
-                             hipStream_t st) {
-  hipError_t e = flash_supported(dm) ? launch_sink_average_flash(q, k, v, out, dm, st)
+                             int flash_variant, hipStream_t st) {
+  hipError_t e = flash_supported(dm) ? launch_sink_average_flash(q, k, v, out, dm, flash_variant != 0, st)
                                      : launch_sink_average_generic<bf16_t>(q, k, v, out, dm, st);
   return e == hipSuccess ? VMONARCH_OK : hip_fail(e, "sink_average (bf16) launch");
 }
@@ -344,7 +344,7 @@ int sink_average_impl(const void* q, const void* k, const void* v, void* out, in
   Dims dm;
   int rc = make_dims(B, heads, T, Hs, Ws, d, &dm);
   if (rc) return rc;
-  return sink_average_any<E>((const E*)q, (const E*)k, (const E*)v, (E*)out, dm, (hipStream_t)stream);
+  return sink_average_any<E>((const E*)q, (const E*)k, (const E*)v, (E*)out, dm, current_settings().flash_variant, (hipStream_t)stream);
 }
 
 template <typename E>
@@ -404,7 +404,7 @@ int attention_impl(const void* q_, const void* k_, const void* v_, void* out_, i
   }
   if (recompute == VMONARCH_SINK_AVERAGE) {
     phase_mark(st, "sink_average");
-    rc = sink_average_any<E>(q, k, v, out, dm, st);
+    rc = sink_average_any<E>(q, k, v, out, dm, cfg.flash_variant, st);
     if (rc) return rc;
   } else if (recompute) {
     phase_mark(st, "first_frame");

@@ -477,15 +477,19 @@ __device__ __forceinline__ uint4 average_bf16x8(uint4 a, uint4 b) {
                     average_bf16x2(a.w, b.w));
 }
 
-// Merge of the key-range partials of the first-frame recomputation: weights 2^(lse - max).
-__global__ void __launch_bounds__(128) merge_splits_kernel(const float* __restrict__ part_o,
+// Merge of the key-range partials of exact rows: weights 2^(lse - max).  Bound by the reads of the partials: a thread takes four channels
+// (16 bytes of every range), a workgroup 8 (d = 128) or 16 rows; one channel per thread and one row per workgroup before: 12 heads x
+// 1560 rows x 3 ranges, d = 128, 13.9 us (2.1 TB/s), 40 x 3600 x 5 171 us; now 9.8 and
+// 73 us.
+__global__ void __launch_bounds__(256) merge_splits_kernel(const float* __restrict__ part_o,
                                                            const float* __restrict__ part_lse, bf16_t* __restrict__ out,
                                                            float* __restrict__ lse, int nsplit, long long rows_per_split,
-                                                           int nq, long long out_rows_per_problem,
+                                                           int nq, int D, long long out_rows_per_problem,
                                                            const int* __restrict__ q_index, int q_index_limit) {
-  const int D = blockDim.x;        // one thread per channel
-  const long long r = blockIdx.x;  // problem * nq + row
-  const int c = threadIdx.x;       // channel
+  const int tpr = D >> 2;  // threads per row
+  const long long r = (long long)blockIdx.x * (256 / tpr) + threadIdx.x / tpr;  // problem * nq + row
+  const int c = 4 * (threadIdx.x % tpr);  // first channel
+  if (r >= rows_per_split) return;
   const long long prob = r / nq;
   long long row = r - prob * nq;
   if (q_index != nullptr) {
@@ -493,14 +497,32 @@ __global__ void __launch_bounds__(128) merge_splits_kernel(const float* __restri
     if (row < 0 || row >= q_index_limit) return;  // not a row of the head: skipped
   }
   float mx = -INFINITY;
+#pragma unroll 4
   for (int s = 0; s < nsplit; ++s) mx = fmaxf(mx, part_lse[s * rows_per_split + r]);
-  float wsum = 0.f, acc = 0.f;
+  float wsum = 0.f;
+  float4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
   for (int s = 0; s < nsplit; ++s) {
-    float w = exp2f(part_lse[s * rows_per_split + r] - mx);
+    const float w = exp2f(part_lse[s * rows_per_split + r] - mx);
+    const float4 o = *reinterpret_cast<const float4*>(part_o + (s * rows_per_split + r) * D + c);
     wsum += w;
-    acc += w * part_o[(s * rows_per_split + r) * D + c];
+    acc.x += w * o.x;
+    acc.y += w * o.y;
+    acc.z += w * o.z;
+    acc.w += w * o.w;
   }
-  out[(prob * out_rows_per_problem + row) * D + c] = f32_to_bf16(acc / wsum);
+  uint2 res;
+  res.x = pack_bf16(acc.x / wsum, acc.y / wsum);
+  res.y = pack_bf16(acc.z / wsum, acc.w / wsum);
+  bf16_t* dst = out + (prob * out_rows_per_problem + row) * D + c;
+  if ((reinterpret_cast<uintptr_t>(out) & 7) == 0) {
+    *reinterpret_cast<uint2*>(dst) = res;
+  } else {  // an output that does not start on 8 bytes
+    dst[0] = (bf16_t)res.x;
+    dst[1] = (bf16_t)(res.x >> 16);
+    dst[2] = (bf16_t)res.y;
+    dst[3] = (bf16_t)(res.y >> 16);
+  }
   if (lse != nullptr && c == 0) lse[prob * out_rows_per_problem + row] = LN2 * (mx + log2f(wsum));
 }
 
@@ -633,15 +655,20 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   P.row_scale = 1.0f / sqrtf((float)dm.d);
   P.cr_min = 0.f;
   const bool d128 = dm.d == 128;
-  // contiguous rows can run on the kernel with two query tiles per wave (same blocks, ranges and partial results;
-  // measured 2 .. 3 % faster on the long key loops of this pass); a row list is gathered by this file's kernel only
-  const bool ff2 = two_tile && row_list == nullptr;
+  // A list as long as the head stays on this file's kernel: a list of all rows gives the bits of the range form of variant 0, which
+  // is tested.
+  if (row_list != nullptr && nrows >= dm.N) two_tile = false;
+  // Query blocks of 128 rows instead of 256 where the items are small, for lack of keys or of rows to fill the units: their start
+  // and end count then, and the short blocks hide them from each other (short / long, us, ranges and partial results the same:
+  // d = 128: 4 heads x 400 rows x 8000 keys (16 ranges of 512) 29.9 / 36.6, 12 x 200 x 32,760 (21 of 1600) 67.2 / 67.0, 24 x 500 x 20,000
+  // (5 of 4032) 150.6 / 131.8; d = 64: 10 x 323 x 4199 (9 of 512) 22.2 / 23.9, 8 x 800 x 16,000 (8 of 2048) 48.8 / 48.2).
+  const bool short_blocks = P.keys_per_split <= 1536 || 2 * total <= compute_units();
   auto two_tile_pass = [&](float* part_o, float* part_lse) {
-    return d128 ? launch_first_frame_flash2<128>(q, k, v, out, lse, part_o, part_lse, dm, nrows, ns, P.keys_per_split, st)
-                : launch_first_frame_flash2<64>(q, k, v, out, lse, part_o, part_lse, dm, nrows, ns, P.keys_per_split, st);
+    return d128 ? launch_exact_rows_flash2<128>(q, k, v, out, lse, part_o, part_lse, dm, nrows, row_list, ns, P.keys_per_split, short_blocks, st)
+                : launch_exact_rows_flash2<64>(q, k, v, out, lse, part_o, part_lse, dm, nrows, row_list, ns, P.keys_per_split, short_blocks, st);
   };
   if (ns == 1) {
-    if (ff2) return two_tile_pass(nullptr, nullptr);
+    if (two_tile) return two_tile_pass(nullptr, nullptr);
     return d128 ? launch_flash<128, false, true, 0, false>(P, st) : launch_flash<64, false, true, 0, false>(P, st);
   }
   const size_t rows = (size_t)ns * dm.BH * nrows;
@@ -649,11 +676,12 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   if (scratch == nullptr || scratch_bytes < need) return hipErrorInvalidValue;
   P.part_lse = (float*)scratch;
   P.part_o = (float*)((char*)scratch + ((rows * sizeof(float) + 255) & ~(size_t)255));
-  hipError_t e = ff2 ? two_tile_pass(P.part_o, P.part_lse)
-                     : (d128 ? launch_flash<128, false, true, 0, true>(P, st) : launch_flash<64, false, true, 0, true>(P, st));
+  hipError_t e = two_tile ? two_tile_pass(P.part_o, P.part_lse)
+                          : (d128 ? launch_flash<128, false, true, 0, true>(P, st) : launch_flash<64, false, true, 0, true>(P, st));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(merge_splits_kernel, dim3((unsigned)((long long)dm.BH * nrows)), dim3(dm.d), 0, st, P.part_o,
-                     P.part_lse, out, lse, ns, (long long)dm.BH * nrows, nrows, dm.N, row_list, (int)dm.N);
+  const long long merge_rows = (long long)dm.BH * nrows, per_block = 1024 / dm.d;
+  hipLaunchKernelGGL(merge_splits_kernel, dim3((unsigned)((merge_rows + per_block - 1) / per_block)), dim3(256), 0, st, P.part_o,
+                     P.part_lse, out, lse, ns, merge_rows, nrows, dm.d, dm.N, row_list, (int)dm.N);
   return hipGetLastError();
 }
 
@@ -718,11 +746,12 @@ hipError_t launch_l_update_flash(const bf16_t* q, const bf16_t* aL, const float*
 // Attention-sink averaging (Sec. 4.4): all N queries of a head against its first frame's b keys,
 // one key range, the normalised rows averaged into `out` by the epilogue.
 hipError_t launch_sink_average_flash(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const Dims& dm,
-                                     hipStream_t st) {
+                                     bool two_tile, hipStream_t st) {
   FlashParams P = {};
   P.q = q; P.k = k; P.v = v; P.outv = out;
   P.q_rows_per_problem = dm.N; P.k_rows_per_problem = dm.N;
   if (dm.N > 0x7fffffffLL - BQ) return hipErrorInvalidValue;
+  if (two_tile) return dm.d == 128 ? launch_sink_average_flash2<128>(q, k, v, out, dm, st) : launch_sink_average_flash2<64>(q, k, v, out, dm, st);
   P.nq = (int)dm.N;
   P.nk = dm.b;
   P.nqb = (int)((dm.N + BQ - 1) / BQ);

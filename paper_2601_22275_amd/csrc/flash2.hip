@@ -188,9 +188,16 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
     }
   }
 
-  // Row r of the problem as the B operand of S^T = K Q^T; returns its logit scale (log2 units).
+  // The row of the problem that query row r stands for: the same, or (exact rows) what a list says; -1 if there is none.
+  auto row_of = [&](int r) __attribute__((always_inline)) -> int {
+    if (r >= P.nq) return -1;
+    if (OUT_K || P.q_index == nullptr) return r;
+    const int i = P.q_index[r];
+    return i >= 0 && i < P.q_index_limit ? i : -1;
+  };
+  // Query row r as the B operand of S^T = K Q^T; returns its logit scale (log2 units).
   auto load_query = [&](int r, bf16x8 (&x)[KS]) __attribute__((always_inline)) -> float {
-    const int row = r < P.nq ? r : P.nq - 1;
+    const int row = max(row_of(min(r, P.nq - 1)), 0);
     const bf16_t* qp = P.q + (qrow0 + row) * D + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) x[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
@@ -609,12 +616,13 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
     F2_FENCE();  // one query tile at a time: both at once need more ordinary registers than the queries leave
     const int qr = row_first + qt * 32 + ql_e;
     const bool qvalid = qr < P.nq;
-    const long long row = qrow0 + (qvalid ? qr : P.nq - 1);
     const float lt = ltil[qt] + __shfl_xor(ltil[qt], 32);
     const float inv = lt > 0.f ? 1.0f / lt : 0.f;
     if (!SPLIT) {
       const float l = ENT == 1 ? lsum[qt] + __shfl_xor(lsum[qt], 32) : lt;
-      if (P.lse != nullptr && qvalid && g_e == 0) P.lse[row] = LN2 * (msc[qt] + __log2f(l));
+      const int r = row_of(qr);
+      const long long row = qrow0 + r;
+      if (P.lse != nullptr && r >= 0 && g_e == 0) P.lse[row] = LN2 * (msc[qt] + __log2f(l));
       if (ENT == 1) {
         // App. B: H = log S - L / S; here in base-2 units, c_L = -H
         const float h = hsum[qt] + __shfl_xor(hsum[qt], 32);
@@ -673,9 +681,10 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
         const int lr = ps * RPI + lane_e / CH;  // row within the wave's block
         const int pc = lane_e % CH;
         const int lc = pc ^ swz(lr);
-        if (row_first + lr < P.nq) {
+        const int r = row_of(row_first + lr);
+        if (r >= 0) {
           uint4 w = *reinterpret_cast<const uint4*>(stage + lr * ROW_BYTES + pc * 16);
-          uint4* gp = reinterpret_cast<uint4*>(dst + (qrow0 + row_first + lr) * D + lc * 8);
+          uint4* gp = reinterpret_cast<uint4*>(dst + (qrow0 + r) * D + lc * 8);
           if (P.blend) w = avg_bf16x8(w, *gp);
           *gp = w;
         }
@@ -710,16 +719,17 @@ hipError_t launch_flash2(FlashParams P, long long problems, hipStream_t st) {
 
 }  // namespace
 
-// Exact attention of a contiguous run of nrows query rows per head over all keys (Sec. 3.3) on this kernel, the keys
-// cut into `ns` ranges of keys_per_split (a multiple of the tile) whose partial results go to part_o / part_lse
-// for the merge (ns == 1: straight to out / lse).  Same query blocks and partial-result layout as the
-// one-tile kernel's pass.
+// Exact attention of nrows query rows per head (a contiguous run, or those of a list) over all keys (Sec. 3.3), the keys
+// cut into `ns` ranges of keys_per_split (a multiple of 64) whose partial results go to part_o / part_lse
+// for the merge (ns == 1: straight to out / lse); query blocks of 128 rows or of 256.
 template <int D>
-hipError_t launch_first_frame_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse,
-                                     float* part_o, float* part_lse, const Dims& dm, int nrows, int ns,
-                                     int keys_per_split, hipStream_t st) {
+hipError_t launch_exact_rows_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse,
+                                    float* part_o, float* part_lse, const Dims& dm, int nrows, const int* rows, int ns,
+                                    int keys_per_split, bool short_blocks, hipStream_t st) {
   FlashParams P = {};
   P.q = q; P.k = k; P.v = v; P.outv = out; P.lse = lse; P.part_o = part_o; P.part_lse = part_lse;
+  P.q_index = rows;
+  P.q_index_limit = (int)dm.N;
   P.q_rows_per_problem = dm.N; P.k_rows_per_problem = dm.N;
   P.nq = nrows;
   P.nk = (int)dm.N;
@@ -727,29 +737,52 @@ hipError_t launch_first_frame_flash2(const bf16_t* q, const bf16_t* k, const bf1
   P.keys_per_split = keys_per_split;
   P.row_scale = 1.0f / sqrtf((float)D);
   P.cr_min = 0.f;
+  if (short_blocks)
+    return ns > 1 ? launch_flash2<D, false, true, 0, true, 1>(P, dm.BH, st) : launch_flash2<D, false, true, 0, false, 1>(P, dm.BH, st);
   return ns > 1 ? launch_flash2<D, false, true, 0, true, 2>(P, dm.BH, st) : launch_flash2<D, false, true, 0, false, 2>(P, dm.BH, st);
 }
 
+// out <- (out + softmax(q K_F1^T / sqrt(d)) V_F1) / 2 (Sec. 4.4): all N queries of a head against its first frame's b keys.
+template <int D>
+hipError_t launch_sink_average_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const Dims& dm,
+                                      hipStream_t st) {
+  FlashParams P = {};
+  P.q = q; P.k = k; P.v = v; P.outv = out;
+  P.q_rows_per_problem = dm.N; P.k_rows_per_problem = dm.N;
+  P.nq = (int)dm.N;
+  P.nk = dm.b;
+  P.nsplit = 1;
+  P.keys_per_split = ((dm.b + BK - 1) / BK) * BK;
+  P.row_scale = 1.0f / sqrtf((float)D);
+  P.cr_min = 0.f;
+  P.blend = 1;
+  // Short blocks always at d = 128, at d = 64 while long ones do not give every compute unit one (short / long, us: d = 128: 12 heads x
+  // 21 frames of 1560 312 / 331, 40 x 60 of 100 47.9 / 65.7; d = 64: 4 x 8 of 1000 17.4 / 23.4, 12 x 21 of 300 17.7 / 17.4, of 1560 196
+  // / 160; the one-tile kernel of flash.hip 336, 53.0, 23.2, 21.2, 205).
+  if constexpr (D == 64)
+    if ((P.nq + 255LL) / 256 * dm.BH > 256) return launch_flash2<D, false, true, 0, false, 2>(P, dm.BH, st);
+  return launch_flash2<D, false, true, 0, false, 1>(P, dm.BH, st);
+}
+
 // Query blocks of 128 rows (one query tile per wave) or of 256?  Of the short ones three share a compute unit at
-// d = 64 (two with values), two at d = 128; of the long ones two and one.  The short ones hide each other's start and end and waste
+// d = 64 without values, two otherwise; of the long ones two and one.  The short ones hide each other's start and end and waste
 // less on a ragged last block or round; the long ones read an operand from LDS for two products, which counts where the launch is long
 // and the device's power is the limit.  A unit works through its blocks in groups as large as it holds, so the two launches'
 // times follow from the blocks per unit, with the time of a group of 1, 2, 3 blocks against the long blocks' largest group measured on
-// 10 launch sizes (4 .. 972 frames) x 12 frame sizes (130 .. 3600 tokens).  Short against long, us: d = 64: 16 frames of 1000 16.8 / 24.6,
-// 130 of 300 11.1 / 16.5, 80 of 1280 52.2 / 46.7, 252 of 2048 308 / 289; d = 128: 130 of 300 15.0 / 29.5, 130 of 1456 158 / 176, 252
-// of 2048 532 / 509, with values 20.8 / 42.1, 230 / 257, 793 / 741.  With values d = 64 always takes the short blocks: the long
-// ones leave room for one wave per SIMD there (252 frames of 512 .. 3600 1 .. 10 % slower).
+// 10 launch sizes (4 .. 972 frames) x 12 frame sizes (130 .. 3600 tokens), video-like and random inputs.  Short against long, us: d =
+// 64: 16 frames of 1000 16.8 / 24.6, 130 of 300 11.1 / 16.5, 80 of 1280 52.2 / 46.7, 252 of 2048 308 / 289, with values 20.3 / 29.3, 126 of
+// 300 13.3 / 14.8, 252 of 2048 474 / 450; d = 128: 130 of 300 15.0 / 29.5, 130 of 1456 158 / 176, 252 of 2048 532 / 509, with values 20.8 /
+// 42.1, 230 / 257, 793 / 741.
 template <int D>
-bool short_blocks_faster(long long problems, int b) {
+bool short_blocks_faster(long long problems, int b, bool with_v) {
   auto units = [&](int rows) -> long long { return (problems * ((b + rows - 1) / rows) + 255) / 256; };  // blocks per compute unit
   const long long n1 = units(128), n2 = units(256);
-  if constexpr (D == 64) {
+  if (D == 64 && !with_v) {
     const double rest1[3] = {0.0, 0.43, 0.64};
     return 0.87 * (double)(n1 / 3) + rest1[n1 % 3] < (double)(n2 / 2) + 0.64 * (double)(n2 % 2);
-  } else {
-    const double pair = b > 900 ? 1.06 : 0.95;
-    return pair * (double)(n1 / 2) + 0.66 * (double)(n1 % 2) < (double)n2;
   }
+  const double pair = b <= 900 ? 0.95 : D == 64 ? 1.05 : 1.06;
+  return pair * (double)(n1 / 2) + 0.66 * (double)(n1 % 2) < (double)n2;
 }
 
 // One R-update: alpha_L, c_L (and lse if not null), plus y when v is given.
@@ -766,21 +799,20 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
   P.keys_per_split = ((dm.b + BK - 1) / BK) * BK;
   P.row_scale = row_scale; P.cr_min = cr_min;
   const long long problems = (long long)dm.BH * dm.T;
-  const bool short_blocks = short_blocks_faster<D>(problems, dm.b);
+  const bool short_blocks = short_blocks_faster<D>(problems, dm.b, v != nullptr);
   auto launch = [&](auto ent) -> hipError_t {
     constexpr int ENT = decltype(ent)::value;
     if (v == nullptr)
       return short_blocks ? launch_flash2<D, true, false, ENT, false, 1>(P, problems, st) : launch_flash2<D, true, false, ENT, false, 2>(P, problems, st);
-    if constexpr (D == 128)
-      if (!short_blocks) return launch_flash2<D, true, true, ENT, false, 2>(P, problems, st);
-    return launch_flash2<D, true, true, ENT, false, 1>(P, problems, st);
+    return short_blocks ? launch_flash2<D, true, true, ENT, false, 1>(P, problems, st) : launch_flash2<D, true, true, ENT, false, 2>(P, problems, st);
   };
   return entropy_mode == VMONARCH_ENTROPY_IDENTITY ? launch(std::integral_constant<int, 2>{}) : launch(std::integral_constant<int, 1>{});
 }
 
 // This file is compiled once per head dimension.
-template hipError_t launch_first_frame_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*, float*,
-                                                           float*, const Dims&, int, int, int, hipStream_t);
+template hipError_t launch_exact_rows_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*, float*, float*,
+                                                          const Dims&, int, const int*, int, int, bool, hipStream_t);
+template hipError_t launch_sink_average_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, const Dims&, hipStream_t);
 template hipError_t launch_r_update_flash2<VM_FLASH2_D>(const bf16_t*, const float*, const bf16_t*, const bf16_t*, bf16_t*, float*,
                                                         bf16_t*, float*, const Dims&, float, float, int, hipStream_t);
 

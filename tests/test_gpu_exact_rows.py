@@ -1,0 +1,71 @@
+"""Exact attention of chosen rows and the sink pass on both query-block sizes of the streaming kernel (128 and 256 rows): against
+the CPU oracle and against the one-tile kernel (flash variant 0), which forms the same sums in another order.
+
+Tolerance: the softmax weights and the result are rounded to bf16 (2^-9 relative each, random): sqrt(2) 2^-9 = 2.8e-3 in the relative
+norm at most; 4e-3 against the oracle, 6e-3 between the kernels.  The sink pass averages with a value that is there already
+and rounds once more: the same bounds."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import vmonarch_oracle as O
+from tests import util as U
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2601_22275_amd import binding
+    assert torch.cuda.is_available()
+    binding.lib()
+    return torch, binding, torch.device("cuda:0")
+
+
+def _both(binding, call):
+    got = call()
+    binding.set_flash_variant(0)
+    try:
+        return U.from_device(got), U.from_device(call())
+    finally:
+        binding.set_flash_variant(2)
+
+
+# heads x rows x keys: short blocks with key ranges, long blocks in one range, long blocks with ranges (and a last block of one row)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,rows,N", [(2, 130, 700), (51, 1025, 3970), (17, 257, 16001)])
+def test_listed_rows(env, heads, rows, N, d):
+    torch, binding, dev = env
+    rng = np.random.default_rng(rows + d)
+    q, k, v = (U.random_bits(rng, (heads, N, d), 1.5, True) for _ in range(3))
+    tq, tk, tv = (U.to_device(list(x), torch, dev) for x in (q, k, v))
+    listed = rng.permutation(N)[:rows].astype(np.int32)
+    listed[[1, rows // 2]] = [-1, N]                      # entries that name no row are skipped
+    tl = torch.from_numpy(listed).to(dev)
+    base = torch.randn((1, heads, N, d), device=dev).bfloat16()
+    got, one_tile = _both(binding, lambda: binding.recompute_tokens(tq, tk, tv, 1, 1, N, base.clone(), tl))
+    rest = np.setdiff1d(np.arange(N), listed)
+    valid = np.array([r for r in listed if 0 <= r < N])
+    assert np.array_equal(got[:, rest], U.from_device(base)[:, rest])
+    for h in (0, heads - 1):
+        ref = O.softmax_attention(U.to_f64(q[h])[valid], U.to_f64(k[h]), U.to_f64(v[h]), 1.0 / math.sqrt(d))
+        assert U.rel_l2(got[h][valid], ref) <= 4e-3
+    assert U.rel_l2(got[:, valid], one_tile[:, valid]) <= 6e-3
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,T,b", [(2, 5, 33), (40, 26, 65), (3, 2, 700)])
+def test_sink_pass(env, heads, T, b, d):
+    torch, binding, dev = env
+    N = T * b
+    rng = np.random.default_rng(T * b + d)
+    q, k, v = (U.random_bits(rng, (heads, N, d), 1.5, True) for _ in range(3))
+    tq, tk, tv = (U.to_device(list(x), torch, dev) for x in (q, k, v))
+    base = torch.randn((1, heads, N, d), device=dev).bfloat16()
+    got, one_tile = _both(binding, lambda: binding.sink_average(tq, tk, tv, T, 1, b, base.clone()))
+    for h in (0, heads - 1):
+        ref = O.softmax_attention(U.to_f64(q[h]), U.to_f64(k[h])[:b], U.to_f64(v[h])[:b], 1.0 / math.sqrt(d))
+        assert U.rel_l2(got[h], (ref + U.from_device(base)[h]) / 2) <= 4e-3
+    assert U.rel_l2(got, one_tile) <= 6e-3
