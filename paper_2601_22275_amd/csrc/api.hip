@@ -289,7 +289,8 @@ int l_update_any<bf16_t>(const bf16_t* q, const bf16_t* aL, const float* cL, con
   if (lpass_supported(dm)) {
     e = launch_l_update_mfma(q, aL, cL, y, aR, cR, out, dm, q_scale, st);
   } else if (temporal_flash_supported(dm)) {
-    e = launch_l_update_flash(q, aL, cL, y, aR, cR, out, lse_scratch, dm, q_scale, st);
+    e = dm.d == 128 ? launch_l_update_flash2<128>(q, aL, cL, y, aR, cR, out, lse_scratch, dm, q_scale, st)
+                    : launch_l_update_flash2<64>(q, aL, cL, y, aR, cR, out, lse_scratch, dm, q_scale, st);
   } else {
     e = launch_l_update_generic<bf16_t>(q, aL, cL, y, aR, cR, out, lse_scratch, dm, q_scale, st);
   }

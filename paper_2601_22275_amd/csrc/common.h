@@ -156,14 +156,14 @@ template <int D>
 hipError_t launch_exact_rows_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse,
                                     float* part_o, float* part_lse, const Dims& dm, int nrows, const int* rows, int ns,
                                     int keys_per_split, bool short_blocks, hipStream_t st);
+// flash2.hip : the temporal factor for any T <= 8128 on that kernel; lse_scratch: BH * N floats, fitting sweep only
+bool temporal_flash_supported(const Dims& dm);
+template <int D>
+hipError_t launch_l_update_flash2(const bf16_t* q, const bf16_t* aL, const float* cL, const bf16_t* y, bf16_t* aR, float* cR,
+                                  bf16_t* out, float* lse_scratch, const Dims& dm, float q_scale, hipStream_t st);
 template <int D>
 hipError_t launch_sink_average_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const Dims& dm,
                                       hipStream_t st);
-
-// the temporal factor for any T <= 8128 through the same kernel (see flash.hip); lse_scratch: BH * N floats, fitting sweep only
-bool temporal_flash_supported(const Dims& dm);
-hipError_t launch_l_update_flash(const bf16_t* q, const bf16_t* aL, const float* cL, const bf16_t* y, bf16_t* aR, float* cR,
-                                 bf16_t* out, float* lse_scratch, const Dims& dm, float q_scale, hipStream_t st);
 
 hipError_t launch_sink_average_flash(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const Dims& dm,
                                      bool two_tile, hipStream_t st);

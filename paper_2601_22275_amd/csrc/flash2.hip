@@ -77,27 +77,33 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // Key rows per LDS tile: 64, or 32 where two workgroups are to share a compute unit and the tiles of keys and values would leave LDS
 // for one.
-template <int D, bool OUT_V, int Q2>
+template <int D, bool OUT_V, int Q2, int BIAS>
 constexpr int tile_rows() {
-  return D == 128 && OUT_V && Q2 == 1 ? 32 : 64;
+  return (D == 128 || BIAS != 0) && OUT_V && Q2 == 1 ? 32 : 64;
 }
 
 // ENT: c_L not wanted (0), online (1) or in the identity form (2)
 // Q2: 32-query tiles per wave; W2 Q2 of them are the workgroup's query block
-template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2>
+// BIAS: the temporal factor's passes (launch_l_update_flash2): the logit of (query r, key l) is sc (q . k) + kb_scale kbias[key row l]
+// (kbias indexed like the key rows), and rows of a problem need not be adjacent.  1: with OUT_K only the rows' log-sum-exp is
+// wanted and no product formed, with OUT_V the products with the values.  2: the reference of query r is given, qb_scale qbias[query row r],
+// the sums stay unnormalised and the sum of the weights goes to `cl`.
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2, int BIAS>
 __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1 ? 2 : 1) flash2_kernel(FlashParams P) {
   using G = RowGeo<D>;
   constexpr int ROW_BYTES = G::ROW_BYTES;
-  constexpr int BT = tile_rows<D, OUT_V, Q2>();
+  constexpr int BT = tile_rows<D, OUT_V, Q2, BIAS>();
   constexpr int TILE_BYTES = BT * ROW_BYTES;
   constexpr int KS = G::KS;                   // k-steps of S^T = K Q^T
   constexpr int CT = G::CT;                   // 32-channel tiles of an output row
   constexpr int CH = G::CH;                   // 16-byte chunks per row
   constexpr int RPI = G::RPI;                 // rows filled by one 64-lane global -> LDS load
   constexpr int V_OFF = NSLOT * TILE_BYTES;   // the V slots follow the K slots
-  constexpr int NX = (OUT_K ? 1 : 0) + (OUT_V ? 1 : 0);  // accumulator sets: [R K][R V]
+  constexpr bool LSE_ONLY = BIAS == 1 && OUT_K;
+  constexpr int NX = LSE_ONLY ? 0 : (OUT_K ? 1 : 0) + (OUT_V ? 1 : 0);  // accumulator sets: [R K][R V]
   constexpr int XV = OUT_K ? 1 : 0;                       // index of the R V set
   static_assert(OUT_K || OUT_V, "at least one product");
+  static_assert(BIAS == 0 || (!SPLIT && ENT == 0 && OUT_K != OUT_V), "the biased modes are whole-range passes without entropy");
   constexpr bool TIGHT = D == 128 && NX == 2 && Q2 == 1;  // two workgroups on a unit: 128 + 128 registers are just enough
   constexpr int BQ2 = 32 * Q2 * W2;  // query rows per workgroup
   auto swz = [](int row) { return G::swz(row); };
@@ -128,9 +134,12 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   const int nkeys = kend - kbeg;
   const int ntiles = (nkeys + BT - 1) / BT;
   const int last_left = nkeys - (ntiles - 1) * BT;  // 1 .. BT keys in the last tile
-  const long long qrow0 = (long long)prob * P.q_rows_per_problem;
-  const char* kbase = reinterpret_cast<const char*>(P.k + ((long long)prob * P.k_rows_per_problem + kbeg) * D);
-  const char* vbase = OUT_V ? reinterpret_cast<const char*>(P.v + ((long long)prob * P.k_rows_per_problem + kbeg) * D) : nullptr;
+  const long long rs = BIAS != 0 ? P.row_stride : 1;  // distance between consecutive rows of a problem
+  const int p_out = BIAS != 0 ? prob / P.inner : prob, p_in = BIAS != 0 ? prob - p_out * P.inner : 0;
+  const long long qrow0 = (long long)p_out * P.q_rows_per_problem + p_in;
+  const long long krow0 = (long long)p_out * P.k_rows_per_problem + p_in + kbeg * rs;
+  const char* kbase = reinterpret_cast<const char*>(P.k + krow0 * D);
+  const char* vbase = OUT_V ? reinterpret_cast<const char*>(P.v + krow0 * D) : nullptr;
 
   // ---- global -> LDS staging (global_load_lds_dwordx4) --------------------------------------
   // One wave instruction fills 64 consecutive 16-byte slots (RPI key rows); slot = key * CH +
@@ -156,8 +165,8 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   const unsigned lds_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)smem;
   auto issue_tile = [&](int t) __attribute__((always_inline)) {  // into slot t & 3
     const unsigned kb = lds_base + (t & (NSLOT - 1)) * TILE_BYTES;
-    const char* ksrc = kbase + (long long)t * TILE_BYTES;
-    const char* vsrc = OUT_V ? vbase + (long long)t * TILE_BYTES : nullptr;
+    const char* ksrc = kbase + t * rs * TILE_BYTES;
+    const char* vsrc = OUT_V ? vbase + t * rs * TILE_BYTES : nullptr;
     const bool ragged = t == ntiles - 1 && last_left < BT;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
@@ -165,6 +174,17 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
       if (ragged) off = (unsigned)(min(RPI * W2 * r + st_key, last_left - 1) * ROW_BYTES + st_lc * 16);
       // wave-uniform LDS byte address in M0; lane lands at + 16 * lane
       const unsigned dst = __builtin_amdgcn_readfirstlane(kb + (RPI * W2 * r + RPI * wave) * ROW_BYTES);
+      if (BIAS != 0) {  // rows far apart: 64-bit lane addresses
+        int row = RPI * W2 * r + st_key;
+        if (ragged) row = min(row, last_left - 1);
+        const long long far = row * rs * ROW_BYTES + st_lc * 16;
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(ksrc + far), "s"(dst) : "memory", "m0");
+        if (OUT_V) {
+          const unsigned vdst = dst + V_OFF;
+          asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(vsrc + far), "s"(vdst) : "memory", "m0");
+        }
+        continue;
+      }
       asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(ksrc), "s"(dst) : "memory", "m0");
       if (OUT_V) {
         const unsigned vdst = dst + V_OFF;
@@ -188,6 +208,15 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
     }
   }
 
+  // Biased modes: the keys' terms behind the tile slots, in units of the raw product (divided by the scale of a logit), so that they can be
+  // the value a logit's accumulation starts from.  One sub-tile past the end is read (and its logits dropped).
+  constexpr int KB_OFF = (OUT_V ? 2 : 1) * NSLOT * TILE_BYTES;
+  if (BIAS != 0) {
+    float* kb_lds = reinterpret_cast<float*>(smem + KB_OFF);
+    const float f = P.kb_scale / (P.row_scale * LOG2E);
+    for (int l = tid; l < ntiles * BT + 32; l += 64 * W2) kb_lds[l] = l < nkeys ? f * P.kbias[krow0 + l * rs] : 0.f;
+  }
+
   // The row of the problem that query row r stands for: the same, or (exact rows) what a list says; -1 if there is none.
   auto row_of = [&](int r) __attribute__((always_inline)) -> int {
     if (r >= P.nq) return -1;
@@ -198,10 +227,11 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   // Query row r as the B operand of S^T = K Q^T; returns its logit scale (log2 units).
   auto load_query = [&](int r, bf16x8 (&x)[KS]) __attribute__((always_inline)) -> float {
     const int row = max(row_of(min(r, P.nq - 1)), 0);
-    const bf16_t* qp = P.q + (qrow0 + row) * D + 8 * g;
+    const bf16_t* qp = P.q + (qrow0 + row * rs) * D + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) x[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
-    const float c = P.cR ? P.cR[qrow0 + row] : 1.0f;
+    const float c = BIAS == 0 && P.cR ? P.cR[qrow0 + row] : 1.0f;
+    if (BIAS != 0) return P.row_scale * LOG2E;
     return P.row_scale * LOG2E / fmaxf(c, P.cr_min);
   };
 
@@ -256,6 +286,11 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   auto mfma_first = [&](f32x16& acc, const bf16x8& a, const bf16x8& b) __attribute__((always_inline)) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
   };
+  // acc = c + a b into registers of its own: a starting value put into acc itself could get there by plain moves right before the
+  // MFMA, which it would not wait for
+  auto mfma_from = [&](f32x16& acc, const bf16x8& a, const bf16x8& b, const f32x16& c) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(acc) : "v"(a), "v"(b), "v"(c));
+  };
   auto mfma_v = [&](f32x16& acc, const bf16x8& a, const bf16x8& b) __attribute__((always_inline)) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
   };
@@ -272,7 +307,7 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   // ---- accumulators and statistics ---------------------------------------------------------
   // The products accumulate in accumulation registers (constraint "a" below): with the two query tiles,
   // the logits and the queries in the 256 ordinary registers, 2 x 2 x CT tiles of 16 live there.
-  f32x16 oacc[NX][Q2][CT];
+  f32x16 oacc[NX > 0 ? NX : 1][Q2][CT];
 #pragma unroll
   for (int x = 0; x < NX; ++x)
 #pragma unroll
@@ -288,6 +323,7 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
     ltil[qt] = 0.f;
     lsum[qt] = 0.f;
     hsum[qt] = 0.f;
+    if (BIAS == 2) msc[qt] = P.qb_scale * P.qbias[qrow0 + min(qb * BQ2 + wave * (32 * Q2) + qt * 32 + ql, P.nq - 1) * rs];
   }
 
   // ---- one step = one 32-key sub-tile, as a fixed sequence of groups ------------------------
@@ -313,7 +349,7 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
     constexpr int GI = decltype(gc)::value;
     if constexpr (GI < KS) {
       ring[GI % RING] = rd_row(gc, s_off);
-    } else {
+    } else if constexpr (NX > 0) {
       constexpr int h = GI - KS;
       constexpr int c = h / (CT * NX);
       constexpr int ct = (h % (CT * NX)) / NX;
@@ -323,14 +359,29 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
       ring[GI % RING] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     }
   };
+  // Biased modes: the terms of the keys of sub-tile `sub` (32 sub .. 32 sub + 31), which their logits start from
+  const unsigned kb_base = lds_base + KB_OFF + 16 * g;
+  typedef __attribute__((address_space(3))) const f32x4* lds_f32x4_ptr;
+  f32x16 kterm;
+  auto load_kterm = [&](int sub) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const f32x4 kb = *(lds_f32x4_ptr)(unsigned long long)(kb_base + 128 * sub + 32 * c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) kterm[4 * c + e] = kb[e];
+    }
+  };
+
   auto issue = [&](auto gc, auto qc, f32x16 (&snext)[Q2], bf16x8 (&pbprev)[Q2][2]) __attribute__((always_inline)) {
     constexpr int GI = decltype(gc)::value;
     constexpr int qt = decltype(qc)::value;
-    if constexpr (GI == 0) {
+    if constexpr (GI == 0 && BIAS != 0) {
+      mfma_from(snext[qt], ring[GI % RING], qreg[qt][GI], kterm);
+    } else if constexpr (GI == 0) {
       mfma_first(snext[qt], ring[GI % RING], qreg[qt][GI]);
     } else if constexpr (GI < KS) {
       mfma_v(snext[qt], ring[GI % RING], qreg[qt][GI]);
-    } else {
+    } else if constexpr (NX > 0) {
       constexpr int h = GI - KS;
       constexpr int c = h / (CT * NX);
       constexpr int ct = (h % (CT * NX)) / NX;
@@ -366,6 +417,11 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
     constexpr int K = decltype(kc)::value;
     constexpr int qt = K % Q2;
     constexpr int j = K / Q2;
+    if (LSE_ONLY) {  // no weights: the sum of the unrounded ones
+      ltstep[qt] = (j == 0 ? pq[K & 1][0] : ltstep[qt] + pq[K & 1][0]) + pq[K & 1][1];
+      asm volatile("" : "+v"(ltstep[qt]));
+      return;
+    }
     bf16x2 pr;
     pr[0] = (__bf16)pq[K & 1][0];  // round to nearest even; the pair is one v_cvt_pk_bf16_f32
     pr[1] = (__bf16)pq[K & 1][1];
@@ -396,13 +452,17 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
     }
   };
   // logits of the 32 keys at byte offset `off` (slot and sub-tile), plain form, ready to be read
-  auto plain_logits = [&](int off, f32x16 (&s)[Q2]) __attribute__((always_inline)) {
+  auto plain_logits = [&](int off, f32x16 (&s)[Q2], int sub) __attribute__((always_inline)) {
+    if (BIAS != 0) load_kterm(sub);
     static_for<0, KS>([&](auto kc) {
       constexpr int ks = decltype(kc)::value;
       const bf16x8 a = rd_row(kc, off);
       if constexpr (ks == 0) {
 #pragma unroll
-        for (int qt = 0; qt < Q2; ++qt) mfma_first(s[qt], a, qreg[qt][ks]);
+        for (int qt = 0; qt < Q2; ++qt) {
+          if constexpr (BIAS != 0) mfma_from(s[qt], a, qreg[qt][ks], kterm);
+          else mfma_first(s[qt], a, qreg[qt][ks]);
+        }
       } else {
 #pragma unroll
         for (int qt = 0; qt < Q2; ++qt) mfma_v(s[qt], a, qreg[qt][ks]);
@@ -436,13 +496,13 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   };
   // A reference has to move: the sub-tile just finished (keys at byte offset `off`; its products are not issued yet) is formed
   // again against new references.
-  auto redo = [&](int off, bf16x8 (&pbcur)[Q2][2], int keys_left) __attribute__((always_inline)) {
+  auto redo = [&](int off, bf16x8 (&pbcur)[Q2][2], int keys_left, int sub) __attribute__((always_inline)) {
     f32x16 s[Q2];
-    plain_logits(off, s);
+    plain_logits(off, s, sub);
     if (keys_left < 32) mask_tail(s, keys_left);
 #pragma unroll
     for (int qt = 0; qt < Q2; ++qt) move_reference(qt, subtile_max(s[qt]) * sc[qt]);
-    plain_logits(off, s);  // again: kept meanwhile they would sit beside the copies of the accumulators
+    plain_logits(off, s, sub);  // again: kept meanwhile they would sit beside the copies of the accumulators
     if (keys_left < 32) mask_tail(s, keys_left);
     static_for<0, 8 * Q2>([&](auto kc) {
       score_scale(kc, s);
@@ -456,10 +516,13 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   // S_OFF / PV_OFF: byte offsets (slot and sub-tile) this step's logits and products read;
   // NS_OFF / NPV_OFF: the same for the step that follows (its first operands are requested here).
   auto step = [&](auto s_c, auto pv_c, auto ns_c, auto npv_c, f32x16 (&scur)[Q2], f32x16 (&snext)[Q2], bf16x8 (&pbprev)[Q2][2],
-                  bf16x8 (&pbcur)[Q2][2], int keys_left) __attribute__((always_inline)) {
+                  bf16x8 (&pbcur)[Q2][2], int keys_left, int sub) __attribute__((always_inline)) {
     constexpr int S_OFF = decltype(s_c)::value, PV_OFF = decltype(pv_c)::value;
     constexpr int NS_OFF = decltype(ns_c)::value, NPV_OFF = decltype(npv_c)::value;
+    if constexpr (NX == 0) F2_MFMA_RESULT_WAIT();  // no products between the logits' last MFMA and here
+    F2_FENCE();
     if (keys_left < 32) mask_tail(scur, keys_left);
+    if (BIAS != 0) load_kterm(sub + 1);
     F2_FENCE();
     // (with one sub-tile per tile the next step's logits are those of a tile that may still be travelling when this one ends)
     if constexpr (BT == 32) static_for<0, PF>([&](auto gc) { request(gc, S_OFF, PV_OFF); });
@@ -491,8 +554,9 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
       });
     });
 #pragma unroll
-    for (int qt = 0; qt < Q2; ++qt) asm volatile("" : "+v"(pbcur[qt][0]), "+v"(pbcur[qt][1]));
-    if (__any(ltstep[0] > STEP_MAX2 || ltstep[Q2 - 1] > STEP_MAX2)) redo(NPV_OFF, pbcur, keys_left);
+    for (int qt = 0; qt < Q2; ++qt)
+      if (!LSE_ONLY) asm volatile("" : "+v"(pbcur[qt][0]), "+v"(pbcur[qt][1]));
+    if (BIAS != 2 && __any(ltstep[0] > STEP_MAX2 || ltstep[Q2 - 1] > STEP_MAX2)) redo(NPV_OFF, pbcur, keys_left, sub);
 #pragma unroll
     for (int qt = 0; qt < Q2; ++qt) {
       ltil[qt] += ltstep[qt];
@@ -522,9 +586,10 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
     const bool active = qb * BQ2 + wave * (32 * Q2) < P.nq;
     if (active) {
       // logits of sub-tile 0, plain form; their row maxima are the first references
-      plain_logits(0, sA);
+      plain_logits(0, sA, 0);
 #pragma unroll
-      for (int qt = 0; qt < Q2; ++qt) msc[qt] = fmaxf(msc[qt], subtile_max(sA[qt]) * sc[qt] + HEADROOM2);
+      for (int qt = 0; qt < Q2; ++qt)
+        if (BIAS != 2) msc[qt] = fmaxf(msc[qt], subtile_max(sA[qt]) * sc[qt] + HEADROOM2);
       // operands of the first groups of the first step (sub-tile 1 of slot 0; products against slot 3)
       if constexpr (BT == 64) static_for<0, PF>([&](auto gc) { request(gc, 32 * ROW_BYTES, 3 * TILE_BYTES + 32 * ROW_BYTES); });
     }
@@ -545,15 +610,15 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
         // one sub-tile per tile: logits of t+1, products of t-1 [at t = 0: P^T = 0 against the cleared slot 3], softmax of t
         constexpr int k2 = ((SLOT + 2) & 3) * TILE_BYTES;
         step(std::integral_constant<int, kn>{}, std::integral_constant<int, kp>{}, std::integral_constant<int, k2>{},
-             std::integral_constant<int, kt>{}, SLOT % 2 ? sB : sA, SLOT % 2 ? sA : sB, SLOT % 2 ? pbA : pbB, SLOT % 2 ? pbB : pbA, left0);
+             std::integral_constant<int, kt>{}, SLOT % 2 ? sB : sA, SLOT % 2 ? sA : sB, SLOT % 2 ? pbA : pbB, SLOT % 2 ? pbB : pbA, left0, t);
       } else if (active) {
         // logits of (t, 1), products of (t-1, 1) [at t = 0: P^T = 0 against the cleared slot 3], softmax of (t, 0);
         // the step after it: logits of (t+1, 0), products of (t, 0)
         step(std::integral_constant<int, kt + HALF>{}, std::integral_constant<int, kp + HALF>{},
-             std::integral_constant<int, kn>{}, std::integral_constant<int, kt>{}, sA, sB, pbB, pbA, left0);
+             std::integral_constant<int, kn>{}, std::integral_constant<int, kt>{}, sA, sB, pbB, pbA, left0, 2 * t);
         // logits of (t+1, 0), products of (t, 0), softmax of (t, 1); then logits of (t+1, 1), products of (t, 1)
         step(std::integral_constant<int, kn>{}, std::integral_constant<int, kt>{},
-             std::integral_constant<int, kn + HALF>{}, std::integral_constant<int, kt + HALF>{}, sB, sA, pbA, pbB, left0 - 32);
+             std::integral_constant<int, kn + HALF>{}, std::integral_constant<int, kt + HALF>{}, sB, sA, pbA, pbB, left0 - 32, 2 * t + 1);
       }
     };
     for (int t0_ = 0; t0_ < ntiles; t0_ += 4) {
@@ -617,12 +682,13 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
     const int qr = row_first + qt * 32 + ql_e;
     const bool qvalid = qr < P.nq;
     const float lt = ltil[qt] + __shfl_xor(ltil[qt], 32);
-    const float inv = lt > 0.f ? 1.0f / lt : 0.f;
+    const float inv = BIAS == 2 ? 1.0f : lt > 0.f ? 1.0f / lt : 0.f;
     if (!SPLIT) {
       const float l = ENT == 1 ? lsum[qt] + __shfl_xor(lsum[qt], 32) : lt;
       const int r = row_of(qr);
-      const long long row = qrow0 + r;
-      if (P.lse != nullptr && r >= 0 && g_e == 0) P.lse[row] = LN2 * (msc[qt] + __log2f(l));
+      const long long row = qrow0 + r * rs;
+      if (BIAS == 2 && r >= 0 && g_e == 0) P.cl[row] = lt;
+      if (BIAS != 2 && P.lse != nullptr && r >= 0 && g_e == 0) P.lse[row] = LN2 * (msc[qt] + __log2f(l));
       if (ENT == 1) {
         // App. B: H = log S - L / S; here in base-2 units, c_L = -H
         const float h = hsum[qt] + __shfl_xor(hsum[qt], 32);
@@ -684,7 +750,7 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
         const int r = row_of(row_first + lr);
         if (r >= 0) {
           uint4 w = *reinterpret_cast<const uint4*>(stage + lr * ROW_BYTES + pc * 16);
-          uint4* gp = reinterpret_cast<uint4*>(dst + (qrow0 + r) * D + lc * 8);
+          uint4* gp = reinterpret_cast<uint4*>(dst + (qrow0 + r * rs) * D + lc * 8);
           if (P.blend) w = avg_bf16x8(w, *gp);
           *gp = w;
         }
@@ -693,29 +759,53 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   }
 }
 
-template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2>
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2, int BIAS = 0>
 hipError_t launch_flash2(FlashParams P, long long problems, hipStream_t st) {
   constexpr int ROWS = 32 * Q2;  // per wave
   // four K slots always (the logits need them), four V slots when values are multiplied: 128 KB at d = 128
-  constexpr int LDS_BYTES = (OUT_V ? 2 : 1) * NSLOT * tile_rows<D, OUT_V, Q2>() * D * 2;
+  constexpr int BT = tile_rows<D, OUT_V, Q2, BIAS>();
+  constexpr int TILE_LDS = (OUT_V ? 2 : 1) * NSLOT * BT * D * 2;
+  constexpr int MAX_LDS = TILE_LDS + (BIAS != 0 ? (kMaxBiasedKeys + 64 + 32) * 4 : 0);
+  const int lds = TILE_LDS + (BIAS != 0 ? ((P.nk + BT - 1) / BT * BT + 32) * 4 : 0);
+  if (lds > MAX_LDS) return hipErrorInvalidValue;
   P.nqb = (P.nq + W2 * ROWS - 1) / (W2 * ROWS);
   const long long total = problems * P.nqb * P.nsplit;
   if (total > 0x3fffffffLL) return hipErrorInvalidValue;
   P.total_blocks = (int)total;
   P.blocks_per_xcd = (P.total_blocks + 7) / 8;
-  auto kern = flash2_kernel<D, OUT_K, OUT_V, ENT, SPLIT, Q2>;
+  auto kern = flash2_kernel<D, OUT_K, OUT_V, ENT, SPLIT, Q2, BIAS>;
   static bool configured = false;  // the attribute is per function, set once per process
   if (!configured) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  hipLaunchKernelGGL(kern, dim3(P.blocks_per_xcd * 8), dim3(64 * W2), LDS_BYTES, st, P);
+  hipLaunchKernelGGL(kern, dim3(P.blocks_per_xcd * 8), dim3(64 * W2), lds, st, P);
   return hipGetLastError();
 }
 
 #undef F2_FENCE
 #undef F2_MFMA_RESULT_WAIT
+
+// Query blocks of 128 rows (one query tile per wave) or of 256?  Of the short ones three share a compute unit at
+// d = 64 without values, two otherwise; of the long ones two and one.  The short ones hide each other's start and end and waste
+// less on a ragged last block or round; the long ones read an operand from LDS for two products, which counts where the launch is long
+// and the device's power is the limit.  A unit works through its blocks in groups as large as it holds, so the two launches'
+// times follow from the blocks per unit, with the time of a group of 1, 2, 3 blocks against the long blocks' largest group measured on
+// 10 launch sizes (4 .. 972 frames) x 12 frame sizes (130 .. 3600 tokens), video-like and random inputs.  Short against long, us: d =
+// 64: 16 frames of 1000 16.8 / 24.6, 130 of 300 11.1 / 16.5, 80 of 1280 52.2 / 46.7, 252 of 2048 308 / 289, with values 20.3 / 29.3, 126 of
+// 300 13.3 / 14.8, 252 of 2048 474 / 450; d = 128: 130 of 300 15.0 / 29.5, 130 of 1456 158 / 176, 252 of 2048 532 / 509, with values 20.8 /
+// 42.1, 230 / 257, 793 / 741.
+// long_pairs: two long blocks share a unit (three short ones); else one (two), a pair of short ones takes `pair` of a long one's time.
+bool short_blocks_faster(long long problems, int rows, bool long_pairs, double pair) {
+  auto units = [&](int block) -> long long { return (problems * ((rows + block - 1) / block) + 255) / 256; };  // blocks per compute unit
+  const long long n1 = units(128), n2 = units(256);
+  if (long_pairs) {
+    const double rest1[3] = {0.0, 0.43, 0.64};
+    return 0.87 * (double)(n1 / 3) + rest1[n1 % 3] < (double)(n2 / 2) + 0.64 * (double)(n2 % 2);
+  }
+  return pair * (double)(n1 / 2) + 0.66 * (double)(n1 % 2) < (double)n2;
+}
 
 }  // namespace
 
@@ -764,25 +854,52 @@ hipError_t launch_sink_average_flash2(const bf16_t* q, const bf16_t* k, const bf
   return launch_flash2<D, false, true, 0, false, 1>(P, dm.BH, st);
 }
 
-// Query blocks of 128 rows (one query tile per wave) or of 256?  Of the short ones three share a compute unit at
-// d = 64 without values, two otherwise; of the long ones two and one.  The short ones hide each other's start and end and waste
-// less on a ragged last block or round; the long ones read an operand from LDS for two products, which counts where the launch is long
-// and the device's power is the limit.  A unit works through its blocks in groups as large as it holds, so the two launches'
-// times follow from the blocks per unit, with the time of a group of 1, 2, 3 blocks against the long blocks' largest group measured on
-// 10 launch sizes (4 .. 972 frames) x 12 frame sizes (130 .. 3600 tokens), video-like and random inputs.  Short against long, us: d =
-// 64: 16 frames of 1000 16.8 / 24.6, 130 of 300 11.1 / 16.5, 80 of 1280 52.2 / 46.7, 252 of 2048 308 / 289, with values 20.3 / 29.3, 126 of
-// 300 13.3 / 14.8, 252 of 2048 474 / 450; d = 128: 130 of 300 15.0 / 29.5, 130 of 1456 158 / 176, 252 of 2048 532 / 509, with values 20.8 /
-// 42.1, 230 / 257, 793 / 741.
+// The temporal factor through this kernel, for any number of frames T (Eq. L with Eq. alpha_R / c_R, and
+// the apply-to-V of App. A).  A problem is one (head, position i); its rows are the T frames of that position, b rows
+// apart in the frame-major tensors.  With u[j,k] = q_scale (Q[j] . alpha_L[k]) - c_L[k]:
+//   last sweep     one pass, queries Q[j], keys alpha_L[k] with the additive term -c_L[k], values y[k]:
+//                  out[j] = sum_k softmax_k(u[j,:])[k] y[k];
+//   fitting sweep  pass 1, the same queries and keys without a product: lse[j] = log sum_k exp u[j,k];
+//                  pass 2 with the roles exchanged, queries alpha_L[k] (fixed reference c_L[k]), keys Q[j] with the
+//                  additive term -lse[j], values Q[j]: the weights exp(u[j,k] - lse[j]) = L[j,k] are final, so
+//                  alpha_R[k] = sum_j L[j,k] Q[j] and c_R[k] = sum_j L[j,k] are plain unnormalised sums.
+// lse_scratch: BH * N floats (fitting sweep only).
+// The pass for the log-sum-exps keeps no products, a key's term is the value its logits' accumulation starts from, and there is no running
+// maximum: vector work, which bounds these passes at d = 64 (0.69 .. 0.81 of the cycles), falls by a quarter.  12 x 64 problems of 512
+// frames, d = 64: fitting 128 -> 106 us, last 83 -> 71; 8 x 100 of 300 88 -> 66, 55 -> 44, d = 128 173 -> 112, 109 -> 75.  Block sizes as in
+// the fitting update at d = 64, whose long blocks come two to a unit as here; at d = 128 the products' tiles and registers leave room
+// for two short blocks or one long one, and the short ones win (12 x 64 of 512 fitting 207 / 218 us, 8 x 100 of 300 110 / 150).
 template <int D>
-bool short_blocks_faster(long long problems, int b, bool with_v) {
-  auto units = [&](int rows) -> long long { return (problems * ((b + rows - 1) / rows) + 255) / 256; };  // blocks per compute unit
-  const long long n1 = units(128), n2 = units(256);
-  if (D == 64 && !with_v) {
-    const double rest1[3] = {0.0, 0.43, 0.64};
-    return 0.87 * (double)(n1 / 3) + rest1[n1 % 3] < (double)(n2 / 2) + 0.64 * (double)(n2 % 2);
+hipError_t launch_l_update_flash2(const bf16_t* q, const bf16_t* aL, const float* cL, const bf16_t* y, bf16_t* aR, float* cR,
+                                  bf16_t* out, float* lse_scratch, const Dims& dm, float q_scale, hipStream_t st) {
+  if (dm.T > kMaxBiasedKeys) return hipErrorInvalidValue;
+  FlashParams P = {};
+  P.q_rows_per_problem = dm.N; P.k_rows_per_problem = dm.N;
+  P.inner = dm.b; P.row_stride = dm.b;
+  P.nq = dm.T; P.nk = dm.T;
+  P.nsplit = 1;
+  P.keys_per_split = ((dm.T + BK - 1) / BK) * BK;
+  P.row_scale = q_scale;
+  P.kb_scale = -LOG2E;
+  const long long problems = (long long)dm.BH * dm.b;
+  const bool short_blocks = short_blocks_faster(problems, dm.T, true, 0.0);
+  if (y != nullptr) {
+    P.q = q; P.k = aL; P.v = y; P.outv = out; P.kbias = cL;
+    if constexpr (D == 64)
+      if (!short_blocks) return launch_flash2<D, false, true, 0, false, 2, 1>(P, problems, st);
+    return launch_flash2<D, false, true, 0, false, 1, 1>(P, problems, st);
   }
-  const double pair = b <= 900 ? 0.95 : D == 64 ? 1.05 : 1.06;
-  return pair * (double)(n1 / 2) + 0.66 * (double)(n1 % 2) < (double)n2;
+  if (lse_scratch == nullptr) return hipErrorInvalidValue;
+  P.q = q; P.k = aL; P.lse = lse_scratch; P.kbias = cL;
+  hipError_t e = short_blocks ? launch_flash2<D, true, false, 0, false, 1, 1>(P, problems, st)
+                              : launch_flash2<D, true, false, 0, false, 2, 1>(P, problems, st);
+  if (e != hipSuccess) return e;
+  P.q = aL; P.k = q; P.outk = aR; P.cl = cR; P.lse = nullptr;
+  P.kbias = lse_scratch;          // natural log, like c_L: the same scale -log2(e) applies
+  P.qbias = cL; P.qb_scale = LOG2E;
+  if constexpr (D == 64)
+    if (!short_blocks) return launch_flash2<D, true, false, 0, false, 2, 2>(P, problems, st);
+  return launch_flash2<D, true, false, 0, false, 1, 2>(P, problems, st);
 }
 
 // One R-update: alpha_L, c_L (and lse if not null), plus y when v is given.
@@ -799,7 +916,7 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
   P.keys_per_split = ((dm.b + BK - 1) / BK) * BK;
   P.row_scale = row_scale; P.cr_min = cr_min;
   const long long problems = (long long)dm.BH * dm.T;
-  const bool short_blocks = short_blocks_faster<D>(problems, dm.b, v != nullptr);
+  const bool short_blocks = short_blocks_faster(problems, dm.b, D == 64 && v == nullptr, dm.b <= 900 ? 0.95 : D == 64 ? 1.05 : 1.06);
   auto launch = [&](auto ent) -> hipError_t {
     constexpr int ENT = decltype(ent)::value;
     if (v == nullptr)
@@ -813,6 +930,8 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
 template hipError_t launch_exact_rows_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*, float*, float*,
                                                           const Dims&, int, const int*, int, int, bool, hipStream_t);
 template hipError_t launch_sink_average_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, const Dims&, hipStream_t);
+template hipError_t launch_l_update_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const float*, const bf16_t*, bf16_t*, float*, bf16_t*,
+                                                        float*, const Dims&, float, hipStream_t);
 template hipError_t launch_r_update_flash2<VM_FLASH2_D>(const bf16_t*, const float*, const bf16_t*, const bf16_t*, bf16_t*, float*,
                                                         bf16_t*, float*, const Dims&, float, float, int, hipStream_t);
 

@@ -21,6 +21,7 @@ constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 constexpr float RESCALE_TH = 8.0f;  // rescale the accumulators only when a row max grows by 2^8
 constexpr float NEG_BIG = -1.0e30f;
+constexpr int kMaxBiasedKeys = 8192 - BK;  // biased modes keep one float per key behind the tile slots: 32 KB
 
 struct FlashParams {
   const bf16_t* q;      // query rows
@@ -45,20 +46,19 @@ struct FlashParams {
   float row_scale;
   float cr_min;
   int blend;            // outv <- (outv + result) / 2 instead of outv <- result
-  // flash_kernel only.  Rows of a problem need not be adjacent: row r of problem p is row
-  //   (p / inner) * rows_per_problem + (p % inner) * inner_rows + r * row_stride     (inner = 0 means 1)
-  // of its tensor, the same rule for queries and keys.  The temporal factor walks frame-major tensors this
-  // way: problem = (head, position), rows = frames, row_stride = b.  row_stride = 0 means 1.
+  // The rest is for flash2.hip's biased modes (template parameter BIAS != 0).  Rows of a problem are not adjacent there: row r of
+  // problem p is row (p / inner) * rows_per_problem + p % inner + r * row_stride of its tensor, the same rule for queries and keys.
+  // The temporal factor walks frame-major tensors this way: problem = (head, position), rows = frames, inner = row_stride = b.
   int inner;
-  long long inner_rows;
   long long row_stride;
-  // Biased modes (template parameter BIAS != 0): logit of (query r, key l) = sc (q . k) + kb_scale * kbias[key row l]
-  // (kbias indexed like the key rows); BIAS == 2 additionally fixes the reference of query r at
-  // qb_scale * qbias[query row r], keeps the sums unnormalised and stores the sum of the weights in `cl`.
+  // Logit of (query r, key l) = sc (q . k) + kb_scale * kbias[key row l] (kbias indexed like the key rows); BIAS == 2
+  // additionally fixes the reference of query r at qb_scale * qbias[query row r], keeps the sums unnormalised and stores the sum
+  // of the weights in `cl`.
   const float* kbias;
   const float* qbias;
   float kb_scale;
   float qb_scale;
+  // Exact rows (flash.hip, flash2.hip):
   const int* q_index;   // query row r of a problem is row q_index[r] of it (null: row r); entries
                         // outside [0, q_index_limit) are skipped
   int q_index_limit;

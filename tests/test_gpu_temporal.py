@@ -41,3 +41,30 @@ def test_large_launches(T):
         for got, ref in ((aR, few_aR), (out, few_out)):
             assert U.rel_l2(got[h], ref[h]) <= 6e-3
         assert U.rel_l2(cR[h], few_cR[h]) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T", [193, 256, 400])
+def test_long_query_blocks(T, d):
+    """Launches whose passes take query blocks of 256 rows (d = 128: the log-sum-exp pass), at the first, a middle and the last
+    position against the oracle and the launch of those positions alone, which takes blocks of 128.  Bounds as above."""
+    import torch
+    from paper_2601_22275_amd import binding
+    dev, b, heads, qs = torch.device("cuda:0"), 256, 2, d ** -0.5
+    rng = np.random.default_rng(T + d)
+    Q, aL, Y = ([U.random_bits(rng, (T * b, d), 1.5, True) for _ in range(heads)] for _ in range(3))
+    cL = (-3.0 * rng.random((heads, T * b))).astype(np.float32)
+    tq, taL, ty = (U.to_device(x, torch, dev) for x in (Q, aL, Y))
+    tc = torch.from_numpy(cL).to(dev).view(1, heads, -1)
+    pos = [0, 77, b - 1]
+    pick = lambda x: x.view(1, heads, T, b, *x.shape[3:])[:, :, :, pos].contiguous().view(1, heads, T * 3, *x.shape[3:])
+    large = (*binding.l_update(tq, taL, tc, None, T, 1, b, qs), binding.l_update(tq, taL, tc, ty, T, 1, b, qs))
+    small = (*binding.l_update(pick(tq), pick(taL), pick(tc), None, T, 1, 3, qs),
+             binding.l_update(pick(tq), pick(taL), pick(tc), pick(ty), T, 1, 3, qs))
+    at = lambda x, h: U.to_f64(x[h]).reshape(T, b, -1)[:, pos].transpose(1, 0, 2)
+    for (aR, cR, out) in ([U.from_device(pick(x)) for x in large], [U.from_device(x) for x in small]):
+        for h in range(heads):
+            oaR, ocR, L = O.l_update(at(aL, h), cL[h].reshape(T, b)[:, pos].T.astype(np.float64), at(Q, h) * qs)
+            assert U.rel_l2(aR[h] * qs, oaR.reshape(T * 3, d)) <= 4e-3
+            assert U.rel_l2(cR[h], ocR.reshape(T * 3)) <= 2.0 ** -8
+            assert U.rel_l2(out[h], np.matmul(L, at(Y, h)).transpose(1, 0, 2).reshape(T * 3, d)) <= 4e-3
