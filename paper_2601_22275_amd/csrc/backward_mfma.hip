@@ -35,13 +35,13 @@ namespace vm {
 
 namespace {
 
-constexpr int BK = 64;    // stream rows per LDS tile
-// Waves per workgroup, 32 owner rows each.  At d = 64 two workgroups of four waves fit a compute unit: the smaller blocks leave less
-// of the last round idle and hide each other's start and end (all gradients, eight -> four waves: 90 frames of 943 131 -> 114 us,
-// 252 of 1560 722 -> 667, 128 of 512 level).  At d = 128 the tiles leave LDS for one.
-template <int D>
-constexpr int waves() {
-  return D == 64 ? 4 : 8;
+// Workgroups are NW waves of 32 owner rows: 4 at d = 64, two or three of them on a compute unit, 4 or 8 at d = 128.  Smaller blocks leave less of the
+// last block and the last round idle and hide each other's start and end (all gradients, d = 64, eight -> four waves: 90 frames
+// of 943 131 -> 114 us, 252 of 1560 722 -> 667, 128 of 512 level).  At d = 128 two workgroups leave LDS for tiles of 32 stream rows, a
+// barrier for every 32 rows: which launch takes which, see launch_entropy_bwd_mfma.
+template <int D, int NW>
+constexpr int tile_rows() {  // stream rows per LDS tile
+  return D == 128 && NW == 4 ? 32 : 64;
 }
 constexpr int NSLOT = 3;
 constexpr float LOG2E = 1.4426950408889634f;
@@ -93,15 +93,16 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-template <int D, int MODE>
+template <int D, int MODE, int NW>
 constexpr int own_in_lds() {
-  return D == 128 && MODE == MODE_DKV ? 2 : 0;
+  return D != 128 || MODE == MODE_DQ ? 0 : MODE == MODE_DKV ? 2 : NW == 4 ? 4 : 0;
 }
 
-template <int D, int MODE>
-__global__ void __launch_bounds__(64 * waves<D>(), 2) bwd_kernel(BwdParams P) {
+template <int D, int MODE, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) bwd_kernel(BwdParams P) {
   using G = RowGeo<D>;
-  constexpr int NW = waves<D>();
+  constexpr int BK = tile_rows<D, NW>();
+  constexpr int SR = 64;                              // floats of a tile's array of statistics (a wave's load fills 64)
   constexpr int BO = 32 * NW;
   constexpr int ROW_BYTES = G::ROW_BYTES;
   constexpr int TILE_BYTES = BK * ROW_BYTES;
@@ -113,15 +114,16 @@ __global__ void __launch_bounds__(64 * waves<D>(), 2) bwd_kernel(BwdParams P) {
   constexpr bool DKV = MODE != MODE_DQ;               // stream rows are queries
   constexpr bool PLAIN = MODE == MODE_DKV_PLAIN;
   constexpr int NST = !DKV ? 0 : PLAIN ? 2 : 4;      // arrays of stream statistics: l2, a (, sc2, b)
-  constexpr int STATS_OFF = NSLOT * SLOT_BYTES;      // [NSLOT][NST][64] floats
-  constexpr int STATS_SLOT = NST * BK * 4;
+  constexpr int STATS_OFF = NSLOT * SLOT_BYTES;      // [NSLOT][NST][SR] floats
+  constexpr int STATS_SLOT = NST * SR * 4;
   constexpr int NACC = DKV ? 2 : 1;                   // accumulator sets: [dQ or dK][dV]
   constexpr bool TIGHT = DKV && D == 128;             // the registers are just enough
   constexpr int NG = 2 * KS;                          // MFMAs of G^T and dP^T
   // The dK, dV pass at d = 128 just fills a wave's 256 registers (64 of owner rows, 128 of accumulators, 32 of logits); with
-  // the general statistics in flight it is a few short, and the last NL k-steps of the second owner tensor wait in
-  // LDS, private to the wave.
-  constexpr int NL = own_in_lds<D, MODE>();
+  // the general statistics in flight, or tiles of 32 rows, it is a few short, and the last NL k-steps of the second owner
+  // tensor wait in LDS, private to the wave.  (One spilled operand instead waits, in order, behind the tile just requested:
+  // 252 frames of 1536 1035 us instead of 1011.)
+  constexpr int NL = own_in_lds<D, MODE, NW>();
   constexpr int OWN_OFF = STATS_OFF + NSLOT * STATS_SLOT;  // [NW][NL][64 lanes] 16 bytes
   auto swz = [](int row) { return G::swz(row); };
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -174,7 +176,7 @@ __global__ void __launch_bounds__(64 * waves<D>(), 2) bwd_kernel(BwdParams P) {
       // wave w fetches statistic w of the tile's 64 query rows, one float per lane
       const float* s3 = reinterpret_cast<const float*>(stats + (long long)t * BK) + (wave == 0 ? 1 : wave == 1 ? 2 : wave == 2 ? 0 : 3);
       const unsigned off = (unsigned)(min(lane_i, last) * 16);
-      const unsigned dst3 = __builtin_amdgcn_readfirstlane(lds_base + STATS_OFF + (t % NSLOT) * STATS_SLOT + wave * (BK * 4));
+      const unsigned dst3 = __builtin_amdgcn_readfirstlane(lds_base + STATS_OFF + (t % NSLOT) * STATS_SLOT + wave * (SR * 4));
       asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(off), "s"(s3), "s"(dst3) : "memory", "m0");
     }
   };
@@ -300,10 +302,10 @@ __global__ void __launch_bounds__(64 * waves<D>(), 2) bwd_kernel(BwdParams P) {
       if (DKV) {
         const unsigned sa = sslot + (32 * ST + 8 * r4) * 4;
         l2 = rd_stat(sa);
-        av = rd_stat(sa + BK * 4);
+        av = rd_stat(sa + SR * 4);
         if (!PLAIN) {
-          sc2 = rd_stat(sa + 2 * BK * 4);
-          bv = rd_stat(sa + 3 * BK * 4);
+          sc2 = rd_stat(sa + 2 * SR * 4);
+          bv = rd_stat(sa + 3 * SR * 4);
         }
       }
 #pragma unroll
@@ -350,7 +352,7 @@ __global__ void __launch_bounds__(64 * waves<D>(), 2) bwd_kernel(BwdParams P) {
       const unsigned sslot = lds_base + STATS_OFF + (t % NSLOT) * STATS_SLOT + 16 * g;
       const int left = n - t * BK;
       step(slot, sslot, std::integral_constant<int, 0>{}, left);
-      step(slot, sslot, std::integral_constant<int, 1>{}, left - 32);
+      if constexpr (BK == 64) step(slot, sslot, std::integral_constant<int, 1>{}, left - 32);
     }
   }
 
@@ -393,17 +395,22 @@ __global__ void __launch_bounds__(64 * waves<D>(), 2) bwd_kernel(BwdParams P) {
   }
 }
 
-template <int D, int MODE>
-hipError_t launch_bwd(const BwdParams& P, hipStream_t st) {
-  constexpr int LDS_BYTES = 2 * NSLOT * BK * D * 2 + NSLOT * BK * 16 + waves<D>() * own_in_lds<D, MODE>() * 1024;
-  auto kern = bwd_kernel<D, MODE>;
+template <int D, int MODE, int NW>
+hipError_t launch_bwd(BwdParams P, long long problems, hipStream_t st) {
+  constexpr int LDS_BYTES = 2 * NSLOT * tile_rows<D, NW>() * D * 2 + NSLOT * 64 * 16 + NW * own_in_lds<D, MODE, NW>() * 1024;
+  P.nob = (P.n + 32 * NW - 1) / (32 * NW);
+  const long long total = problems * P.nob;
+  if (total > 0x3fffffffLL) return hipErrorInvalidValue;
+  P.total_blocks = (int)total;
+  P.blocks_per_xcd = (P.total_blocks + 7) / 8;
+  auto kern = bwd_kernel<D, MODE, NW>;
   static bool configured = false;
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  hipLaunchKernelGGL(kern, dim3(P.blocks_per_xcd * 8), dim3(64 * waves<D>()), LDS_BYTES, st, P);
+  hipLaunchKernelGGL(kern, dim3(P.blocks_per_xcd * 8), dim3(64 * NW), LDS_BYTES, st, P);
   return hipGetLastError();
 }
 
@@ -423,23 +430,27 @@ hipError_t launch_entropy_bwd_mfma(const bf16_t* q, const float* cR, const bf16_
   P.o = o; P.cR = cR; P.lse = lse; P.H = H; P.dH = dH; P.stats = (float4*)scratch;
   P.row_scale = row_scale; P.cr_min = cr_min;
   P.n = dm.b;
-  const int owner_rows = 32 * (dm.d == 64 ? waves<64>() : waves<128>());
-  P.nob = (dm.b + owner_rows - 1) / owner_rows;
-  const long long total = (long long)dm.BH * dm.T * P.nob;
-  if (total > 0x3fffffffLL) return hipErrorInvalidValue;
-  P.total_blocks = (int)total;
-  P.blocks_per_xcd = (P.total_blocks + 7) / 8;
+  const long long problems = (long long)dm.BH * dm.T;
   const bool plain = cR == nullptr && dH == nullptr;
-  auto run = [&](auto dc) -> hipError_t {
-    constexpr int D = decltype(dc)::value;
+  auto run = [&](auto dc, auto wc) -> hipError_t {
+    constexpr int D = decltype(dc)::value, NW = decltype(wc)::value;
     P.out = dq;
-    hipError_t e2 = launch_bwd<D, MODE_DQ>(P, st);
+    hipError_t e2 = launch_bwd<D, MODE_DQ, NW>(P, problems, st);
     if (e2 != hipSuccess) return e2;
     P.out = dk;
     P.out_v = dv;
-    return plain ? launch_bwd<D, MODE_DKV_PLAIN>(P, st) : launch_bwd<D, MODE_DKV>(P, st);
+    return plain ? launch_bwd<D, MODE_DKV_PLAIN, NW>(P, problems, st) : launch_bwd<D, MODE_DKV, NW>(P, problems, st);
   };
-  return dm.d == 128 ? run(std::integral_constant<int, 128>{}) : run(std::integral_constant<int, 64>{});
+  using four = std::integral_constant<int, 4>;
+  if (dm.d == 64) return run(std::integral_constant<int, 64>{}, four{});
+  // d = 128: blocks of 128 rows, two on a compute unit, or of 256, one?  The times follow from the blocks per unit, with a pair of short
+  // blocks (0.96 .. 1.02) and a single one (0.80) measured against a long block.  All gradients, plain form, short against long, us: 130 frames
+  // of 300 44 / 79, 32 of 1000 74 / 91, 400 of 720 446 / 468, 252 of 512 134 / 142, of 1536 1011 / 996, of 1560 1091 / 1090.
+  auto units = [&](int rows) -> long long { return (problems * ((dm.b + rows - 1) / rows) + 255) / 256; };
+  const long long n1 = units(128), n2 = units(256);
+  const double pair = dm.b > 900 ? 1.02 : 0.96;
+  if (pair * (double)(n1 / 2) + 0.80 * (double)(n1 % 2) < (double)n2) return run(std::integral_constant<int, 128>{}, four{});
+  return run(std::integral_constant<int, 128>{}, std::integral_constant<int, 8>{});
 }
 
 }  // namespace vm

@@ -81,3 +81,31 @@ def test_more_blocks_than_the_card_holds(env, d, with_dh, with_cr):
         ref = O.entropy_attention_backward(q, k, v, y[h][rows], do, lse[h][rows], H[h][rows], dh, s / c)
         for name, g, r in zip(("dq", "dk", "dv"), got, ref):
             assert U.rel_l2(g[h][rows], r) <= 1e-2, name
+
+
+@pytest.mark.parametrize("with_dh,with_cr", [(False, False), (True, True)])
+def test_long_owner_blocks(env, with_dh, with_cr):
+    """d = 128, 256 frames of 1200 tokens: a launch that takes owner blocks of 256 rows (smaller ones take 128).  Two frames repeated;
+    every repeat bit-identical, one against the oracle."""
+    torch, binding, dev = env
+    b, d, frames, rng = 1200, 128, 256, np.random.default_rng(5)
+    Q, K, V, dO = (U.random_bits(rng, (2 * b, d), 1.0, True) for _ in range(4))
+    rep = lambda x: x.view(1, 1, 2, b, -1).repeat(1, 1, frames // 2, 1, 1).view(1, 1, frames * b, -1)
+    tq, tk, tv, tdo = (rep(U.to_device([x], torch, dev)) for x in (Q, K, V, dO))
+    cR = (0.3 + 1.5 * rng.random(2 * b)).astype(np.float32) if with_cr else None
+    dH = rng.normal(size=2 * b).astype(np.float32) if with_dh else None
+    tcr, tdh = (None if x is None else rep(torch.from_numpy(x).to(dev)).view(1, 1, -1) for x in (cR, dH))
+    s, cr_min = 1.0 / math.sqrt(d), 0.1
+    _, cL, y, lse = binding.r_update_lse(tq, tcr, tk, tv, frames, 1, b, s, cr_min)
+    H = (-cL).contiguous()
+    got = binding.entropy_attention_bwd(tq, tcr, tk, tv, y, tdo, lse, H, tdh, frames, 1, b, s, cr_min)
+    for x in got:
+        x = x.view(frames // 2, -1)
+        assert bool((x == x[0]).all())
+    got = [x.float().cpu().numpy().reshape(frames, b, d)[1] for x in got]
+    q, k, v, do = (U.to_f64(x).reshape(2, b, d)[1] for x in (Q, K, V, dO))
+    o, l64, h64 = (x.float().cpu().numpy().reshape(frames, b, -1)[1].astype(np.float64) for x in (y, lse, H))
+    c = np.ones(b) if cR is None else np.maximum(cR[b:].astype(np.float64), cr_min)
+    ref = O.entropy_attention_backward(q, k, v, o, do, l64[:, 0], h64[:, 0], None if dH is None else dH[b:].astype(np.float64), s / c)
+    for name, g, r in zip(("dq", "dk", "dv"), got, ref):
+        assert U.rel_l2(g, r) <= 1e-2, name
