@@ -380,11 +380,23 @@ int attention_impl(const void* q_, const void* k_, const void* v_, void* out_, i
   // App. A: aR = Q, cR = 1, then `iters` times (R-update; L-update); y = R V and O = L y
   // ride on the last sweep.  Q carries 1/sqrt(d) through row_scale / q_scale.
   if (g_timing) g_n_phases = 0;
+  bool ranges_done = false;  // the first frame's key ranges are in the scratch already
   for (int sweep = 0; sweep < iters; ++sweep) {
     const bool last = sweep == iters - 1;
     phase_mark(st, last ? "r_update_last" : "r_update");
-    rc = r_update_any<E>(sweep == 0 ? q : aR, sweep == 0 ? nullptr : cR, k, last ? v : nullptr, aL, cL,
-                         last ? y : nullptr, nullptr, dm, s, cr_min, cfg, st);
+    bool updated = false;
+    if constexpr (sizeof(E) == 2) {
+      // the first frame's exact rows need nothing of the sweeps: in a small call their key ranges go along with the first update
+      if (sweep == 0 && !last && recompute == VMONARCH_RECOMPUTE_FIRST_FRAME && cfg.flash_variant == 2 &&
+          cfg.entropy_mode == VMONARCH_ENTROPY_ONLINE) {
+        const hipError_t e = launch_update_and_first_frame(q, k, v, aL, cL, ws + w.ff, w.total - w.ff, dm, s, cr_min, &ranges_done, st);
+        if (e != hipSuccess) return hip_fail(e, "r_update + first_frame (bf16) launch");
+        updated = ranges_done;
+      }
+    }
+    if (!updated)
+      rc = r_update_any<E>(sweep == 0 ? q : aR, sweep == 0 ? nullptr : cR, k, last ? v : nullptr, aL, cL,
+                           last ? y : nullptr, nullptr, dm, s, cr_min, cfg, st);
     if (rc) return rc;
     // manual control (App. "Manual Control of Monarch Parameters"): overwrite the term just produced,
     // for key frame 0 (the head's first b entries) or for all frames
@@ -411,8 +423,13 @@ int attention_impl(const void* q_, const void* k_, const void* v_, void* out_, i
     phase_mark(st, "first_frame");
     // f32: the sweeps are done with alpha_L and y, whose room (adjacent) takes the partial sums of the key ranges
     const bool reuse = sizeof(E) == 4;
-    rc = first_frame_any<E>(q, k, v, out, nullptr, ws + (reuse ? w.aL : w.ff), reuse ? w.cL - w.aL : w.total - w.ff, dm,
-                            dm.b, nullptr, cfg.flash_variant, st);
+    if (ranges_done) {
+      const hipError_t e = merge_first_frame_flash((bf16_t*)out, ws + w.ff, dm, st);
+      if (e != hipSuccess) return hip_fail(e, "first_frame merge launch");
+    } else {
+      rc = first_frame_any<E>(q, k, v, out, nullptr, ws + (reuse ? w.aL : w.ff), reuse ? w.cL - w.aL : w.total - w.ff, dm,
+                              dm.b, nullptr, cfg.flash_variant, st);
+    }
     if (rc) return rc;
   }
   phase_mark(st, nullptr);

@@ -444,11 +444,11 @@ hipError_t launch_entropy_bwd_mfma(const bf16_t* q, const float* cR, const bf16_
   using four = std::integral_constant<int, 4>;
   if (dm.d == 64) return run(std::integral_constant<int, 64>{}, four{});
   // d = 128: blocks of 128 rows, two on a compute unit, or of 256, one?  The times follow from the blocks per unit, with a pair of short
-  // blocks (0.96 .. 1.02) and a single one (0.80) measured against a long block.  All gradients, plain form, short against long, us: 130 frames
+  // blocks (0.96 .. 1.04, by the frame) and a single one (0.80) measured against a long block.  All gradients, plain form, short against long, us: 130 frames
   // of 300 44 / 79, 32 of 1000 74 / 91, 400 of 720 446 / 468, 252 of 512 134 / 142, of 1536 1011 / 996, of 1560 1091 / 1090.
   auto units = [&](int rows) -> long long { return (problems * ((dm.b + rows - 1) / rows) + 255) / 256; };
   const long long n1 = units(128), n2 = units(256);
-  const double pair = dm.b > 900 ? 1.02 : 0.96;
+  const double pair = dm.b > 900 ? 1.04 : 0.96;
   if (pair * (double)(n1 / 2) + 0.80 * (double)(n1 % 2) < (double)n2) return run(std::integral_constant<int, 128>{}, four{});
   return run(std::integral_constant<int, 128>{}, std::integral_constant<int, 8>{});
 }

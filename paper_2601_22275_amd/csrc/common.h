@@ -150,6 +150,11 @@ size_t first_frame_flash_scratch_bytes(const Dims& dm, int nrows);
 hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse,
                                     void* scratch, size_t scratch_bytes, const Dims& dm, int nrows, const int* rows,
                                     bool two_tile, hipStream_t st);
+// A call's first fitting update together with the key ranges of its first frame, if both are small: *done says whether, then only
+// merge_first_frame_flash (same scratch) is left of the first frame
+hipError_t launch_update_and_first_frame(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL, void* scratch,
+                                         size_t scratch_bytes, const Dims& dm, float row_scale, float cr_min, bool* done, hipStream_t st);
+hipError_t merge_first_frame_flash(bf16_t* out, void* scratch, const Dims& dm, hipStream_t st);
 // flash2.hip : the same pass on that kernel; the caller has cut the keys into ns ranges of keys_per_split and owns the
 // partial-result buffers
 template <int D>
@@ -161,6 +166,13 @@ bool temporal_flash_supported(const Dims& dm);
 template <int D>
 hipError_t launch_l_update_flash2(const bf16_t* q, const bf16_t* aL, const float* cL, const bf16_t* y, bf16_t* aR, float* cR,
                                   bf16_t* out, float* lse_scratch, const Dims& dm, float q_scale, hipStream_t st);
+// flash2.hip : the first fitting update and the first frame's key ranges in one launch
+template <int D>
+bool update_and_first_frame_supported(const Dims& dm, int ns);
+template <int D>
+hipError_t launch_update_and_first_frame_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL, float* part_o,
+                                                float* part_lse, const Dims& dm, float row_scale, float cr_min, int ns,
+                                                int keys_per_split, hipStream_t st);
 template <int D>
 hipError_t launch_sink_average_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, const Dims& dm,
                                       hipStream_t st);

@@ -528,6 +528,24 @@ int first_frame_splits(const Dims& dm, int nrows) {
   return best;
 }
 
+// Where the partial results of `ns` key ranges lie in their scratch: log2-sum-exps, then rows
+struct Partials {
+  float* lse;
+  float* o;
+};
+Partials partials_in(void* scratch, const Dims& dm, int nrows, int ns) {
+  const size_t rows = (size_t)ns * dm.BH * nrows;
+  return {(float*)scratch, (float*)((char*)scratch + ((rows * sizeof(float) + 255) & ~(size_t)255))};
+}
+
+hipError_t launch_merge(const float* part_o, const float* part_lse, bf16_t* out, float* lse, int ns, const Dims& dm, int nrows,
+                        const int* row_list, hipStream_t st) {
+  const long long merge_rows = (long long)dm.BH * nrows, per_block = 1024 / dm.d;
+  hipLaunchKernelGGL(merge_splits_kernel, dim3((unsigned)((merge_rows + per_block - 1) / per_block)), dim3(256), 0, st, part_o,
+                     part_lse, out, lse, ns, merge_rows, nrows, dm.d, dm.N, row_list, (int)dm.N);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 bool temporal_flash_supported(const Dims& dm) { return (dm.d == 128 || dm.d == 64) && dm.T <= kMaxBiasedKeys; }
@@ -618,15 +636,35 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   const size_t rows = (size_t)ns * dm.BH * nrows;
   const size_t need = rows * dm.d * sizeof(float) + ((rows * sizeof(float) + 255) & ~(size_t)255);
   if (scratch == nullptr || scratch_bytes < need) return hipErrorInvalidValue;
-  P.part_lse = (float*)scratch;
-  P.part_o = (float*)((char*)scratch + ((rows * sizeof(float) + 255) & ~(size_t)255));
+  const Partials part = partials_in(scratch, dm, nrows, ns);
+  P.part_lse = part.lse;
+  P.part_o = part.o;
   hipError_t e = two_tile ? two_tile_pass(P.part_o, P.part_lse)
                           : (d128 ? launch_flash<128, false, true, 0, true>(P, st) : launch_flash<64, false, true, 0, true>(P, st));
   if (e != hipSuccess) return e;
-  const long long merge_rows = (long long)dm.BH * nrows, per_block = 1024 / dm.d;
-  hipLaunchKernelGGL(merge_splits_kernel, dim3((unsigned)((merge_rows + per_block - 1) / per_block)), dim3(256), 0, st, P.part_o,
-                     P.part_lse, out, lse, ns, merge_rows, nrows, dm.d, dm.N, row_list, (int)dm.N);
-  return hipGetLastError();
+  return launch_merge(P.part_o, P.part_lse, out, lse, ns, dm, nrows, row_list, st);
+}
+
+hipError_t launch_update_and_first_frame(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL, void* scratch,
+                                         size_t scratch_bytes, const Dims& dm, float row_scale, float cr_min, bool* done, hipStream_t st) {
+  *done = false;
+  if (!flash_supported(dm) || frame_supported(dm, false) || dm.N > 0x7fffffffLL - BK) return hipSuccess;
+  const int ns = first_frame_splits(dm, dm.b);
+  if (!(dm.d == 128 ? update_and_first_frame_supported<128>(dm, ns) : update_and_first_frame_supported<64>(dm, ns))) return hipSuccess;
+  if (scratch == nullptr || scratch_bytes < first_frame_flash_scratch_bytes(dm, dm.b)) return hipErrorInvalidValue;
+  const Partials part = partials_in(scratch, dm, dm.b, ns);
+  const long long tiles = (dm.N + BK - 1) / BK;
+  const int keys_per_split = (int)(((tiles + ns - 1) / ns) * BK);
+  const hipError_t e = dm.d == 128 ? launch_update_and_first_frame_flash2<128>(q, k, v, aL, cL, part.o, part.lse, dm, row_scale, cr_min, ns, keys_per_split, st)
+                                   : launch_update_and_first_frame_flash2<64>(q, k, v, aL, cL, part.o, part.lse, dm, row_scale, cr_min, ns, keys_per_split, st);
+  *done = e == hipSuccess;
+  return e;
+}
+
+hipError_t merge_first_frame_flash(bf16_t* out, void* scratch, const Dims& dm, hipStream_t st) {
+  const int ns = first_frame_splits(dm, dm.b);
+  const Partials part = partials_in(scratch, dm, dm.b, ns);
+  return launch_merge(part.o, part.lse, out, nullptr, ns, dm, dm.b, nullptr, st);
 }
 
 // Attention-sink averaging (Sec. 4.4): all N queries of a head against its first frame's b keys,

@@ -77,9 +77,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // Key rows per LDS tile: 64, or 32 where two workgroups are to share a compute unit and the tiles of keys and values would leave LDS
 // for one.
-template <int D, bool OUT_V, int Q2, int BIAS>
+template <int D, bool OUT_V, int Q2, int BIAS, bool PAIRED = false>
 constexpr int tile_rows() {
-  return (D == 128 || BIAS != 0) && OUT_V && Q2 == 1 ? 32 : 64;
+  return (D == 128 || BIAS != 0 || PAIRED) && OUT_V && Q2 == 1 ? 32 : 64;
 }
 
 // ENT: c_L not wanted (0), online (1) or in the identity form (2)
@@ -88,11 +88,12 @@ constexpr int tile_rows() {
 // (kbias indexed like the key rows), and rows of a problem need not be adjacent.  1: with OUT_K only the rows' log-sum-exp is
 // wanted and no product formed, with OUT_V the products with the values.  2: the reference of query r is given, qb_scale qbias[query row r],
 // the sums stay unnormalised and the sum of the weights goes to `cl`.
-template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2, int BIAS>
-__global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1 ? 2 : 1) flash2_kernel(FlashParams P) {
+// PAIRED: one of two kinds of blocks in a launch (flash2_pair_kernel).
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2, int BIAS, bool PAIRED = false>
+__device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid) {
   using G = RowGeo<D>;
   constexpr int ROW_BYTES = G::ROW_BYTES;
-  constexpr int BT = tile_rows<D, OUT_V, Q2, BIAS>();
+  constexpr int BT = tile_rows<D, OUT_V, Q2, BIAS, PAIRED>();
   constexpr int TILE_BYTES = BT * ROW_BYTES;
   constexpr int KS = G::KS;                   // k-steps of S^T = K Q^T
   constexpr int CT = G::CT;                   // 32-channel tiles of an output row
@@ -112,7 +113,6 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   // XCD-aware placement: hardware deals workgroups to the 8 XCDs round-robin, so give each
   // XCD one contiguous range of work items; the query blocks of one (head, frame) then share
   // that XCD's L2 copy of the frame's K and V.
-  const int bid = blockIdx.x;
   const int wid = (bid & 7) * P.blocks_per_xcd + (bid >> 3);
   if (wid >= P.total_blocks) return;
   const int per_problem = P.nqb * P.nsplit;
@@ -759,6 +759,28 @@ __global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1
   }
 }
 
+template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2, int BIAS>
+__global__ void __launch_bounds__(64 * W2, D == 128 && OUT_K && OUT_V && Q2 == 1 ? 2 : 1) flash2_kernel(FlashParams P) {
+  flash2_block<D, OUT_K, OUT_V, ENT, SPLIT, Q2, BIAS>(P, blockIdx.x);
+}
+
+// A fitting update without values (blocks 0 .. na - 1, na a multiple of 8) and the key ranges of exact rows in one launch.
+template <int D>
+__global__ void __launch_bounds__(64 * W2, 2) flash2_pair_kernel(FlashParams A, FlashParams B, int na) {
+  if ((int)blockIdx.x < na) flash2_block<D, true, false, 1, false, 1, 0, true>(A, blockIdx.x);
+  else flash2_block<D, false, true, 0, true, 1, 0, true>(B, blockIdx.x - na);
+}
+
+// Block counts of a launch of `problems` problems
+hipError_t count_blocks(FlashParams& P, long long problems, int block_rows) {
+  P.nqb = (P.nq + block_rows - 1) / block_rows;
+  const long long total = problems * P.nqb * P.nsplit;
+  if (total > 0x3fffffffLL) return hipErrorInvalidValue;
+  P.total_blocks = (int)total;
+  P.blocks_per_xcd = (P.total_blocks + 7) / 8;
+  return hipSuccess;
+}
+
 template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT, int Q2, int BIAS = 0>
 hipError_t launch_flash2(FlashParams P, long long problems, hipStream_t st) {
   constexpr int ROWS = 32 * Q2;  // per wave
@@ -768,11 +790,8 @@ hipError_t launch_flash2(FlashParams P, long long problems, hipStream_t st) {
   constexpr int MAX_LDS = TILE_LDS + (BIAS != 0 ? (kMaxBiasedKeys + 64 + 32) * 4 : 0);
   const int lds = TILE_LDS + (BIAS != 0 ? ((P.nk + BT - 1) / BT * BT + 32) * 4 : 0);
   if (lds > MAX_LDS) return hipErrorInvalidValue;
-  P.nqb = (P.nq + W2 * ROWS - 1) / (W2 * ROWS);
-  const long long total = problems * P.nqb * P.nsplit;
-  if (total > 0x3fffffffLL) return hipErrorInvalidValue;
-  P.total_blocks = (int)total;
-  P.blocks_per_xcd = (P.total_blocks + 7) / 8;
+  const hipError_t ec = count_blocks(P, problems, W2 * ROWS);
+  if (ec != hipSuccess) return ec;
   auto kern = flash2_kernel<D, OUT_K, OUT_V, ENT, SPLIT, Q2, BIAS>;
   static bool configured = false;  // the attribute is per function, set once per process
   if (!configured) {
@@ -809,13 +828,9 @@ bool short_blocks_faster(long long problems, int rows, bool long_pairs, double p
 
 }  // namespace
 
-// Exact attention of nrows query rows per head (a contiguous run, or those of a list) over all keys (Sec. 3.3), the keys
-// cut into `ns` ranges of keys_per_split (a multiple of 64) whose partial results go to part_o / part_lse
-// for the merge (ns == 1: straight to out / lse); query blocks of 128 rows or of 256.
-template <int D>
-hipError_t launch_exact_rows_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse,
-                                    float* part_o, float* part_lse, const Dims& dm, int nrows, const int* rows, int ns,
-                                    int keys_per_split, bool short_blocks, hipStream_t st) {
+namespace {
+FlashParams exact_rows_params(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse, float* part_o, float* part_lse,
+                              const Dims& dm, int nrows, const int* rows, int ns, int keys_per_split) {
   FlashParams P = {};
   P.q = q; P.k = k; P.v = v; P.outv = out; P.lse = lse; P.part_o = part_o; P.part_lse = part_lse;
   P.q_index = rows;
@@ -825,8 +840,31 @@ hipError_t launch_exact_rows_flash2(const bf16_t* q, const bf16_t* k, const bf16
   P.nk = (int)dm.N;
   P.nsplit = ns;
   P.keys_per_split = keys_per_split;
-  P.row_scale = 1.0f / sqrtf((float)D);
+  P.row_scale = 1.0f / sqrtf((float)dm.d);
   P.cr_min = 0.f;
+  return P;
+}
+FlashParams r_update_params(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL, bf16_t* y,
+                            float* lse, const Dims& dm, float row_scale, float cr_min) {
+  FlashParams P = {};
+  P.q = aR; P.cR = cR; P.k = k; P.v = v; P.outk = aL; P.outv = y; P.cl = cL; P.lse = lse;
+  P.q_rows_per_problem = dm.b; P.k_rows_per_problem = dm.b;
+  P.nq = dm.b; P.nk = dm.b;
+  P.nsplit = 1;
+  P.keys_per_split = ((dm.b + BK - 1) / BK) * BK;
+  P.row_scale = row_scale; P.cr_min = cr_min;
+  return P;
+}
+}  // namespace
+
+// Exact attention of nrows query rows per head (a contiguous run, or those of a list) over all keys (Sec. 3.3), the keys
+// cut into `ns` ranges of keys_per_split (a multiple of 64) whose partial results go to part_o / part_lse
+// for the merge (ns == 1: straight to out / lse); query blocks of 128 rows or of 256.
+template <int D>
+hipError_t launch_exact_rows_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse,
+                                    float* part_o, float* part_lse, const Dims& dm, int nrows, const int* rows, int ns,
+                                    int keys_per_split, bool short_blocks, hipStream_t st) {
+  const FlashParams P = exact_rows_params(q, k, v, out, lse, part_o, part_lse, dm, nrows, rows, ns, keys_per_split);
   if (short_blocks)
     return ns > 1 ? launch_flash2<D, false, true, 0, true, 1>(P, dm.BH, st) : launch_flash2<D, false, true, 0, false, 1>(P, dm.BH, st);
   return ns > 1 ? launch_flash2<D, false, true, 0, true, 2>(P, dm.BH, st) : launch_flash2<D, false, true, 0, false, 2>(P, dm.BH, st);
@@ -908,13 +946,7 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
                                   float* cL, bf16_t* y, float* lse, const Dims& dm, float row_scale, float cr_min,
                                   int entropy_mode, hipStream_t st) {
   if (dm.d != D || (v == nullptr) != (y == nullptr)) return hipErrorInvalidValue;
-  FlashParams P = {};
-  P.q = aR; P.cR = cR; P.k = k; P.v = v; P.outk = aL; P.outv = y; P.cl = cL; P.lse = lse;
-  P.q_rows_per_problem = dm.b; P.k_rows_per_problem = dm.b;
-  P.nq = dm.b; P.nk = dm.b;
-  P.nsplit = 1;
-  P.keys_per_split = ((dm.b + BK - 1) / BK) * BK;
-  P.row_scale = row_scale; P.cr_min = cr_min;
+  const FlashParams P = r_update_params(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min);
   const long long problems = (long long)dm.BH * dm.T;
   const bool short_blocks = short_blocks_faster(problems, dm.b, D == 64 && v == nullptr, dm.b <= 900 ? 0.95 : D == 64 ? 1.05 : 1.06);
   auto launch = [&](auto ent) -> hipError_t {
@@ -926,9 +958,46 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
   return entropy_mode == VMONARCH_ENTROPY_IDENTITY ? launch(std::integral_constant<int, 2>{}) : launch(std::integral_constant<int, 1>{});
 }
 
+// The first fitting update and the key ranges of the first frame's exact rows (ns > 1) in one launch, both in blocks of 128 rows.  The
+// exact rows need nothing of the sweeps.  In a call as small as this each of the two launches leaves places on the compute units empty and
+// takes one block's time all the same; together they take little more than one.  Whole calls of two sweeps, separate / together, us: 13 frames
+// of 323, 10 heads, d = 64 64.6 / 57.1; 13 of 400, 4 heads 52.6 / 44.8, d = 128 73.3 / 63.0; 13 of 300, 4 heads, d = 128 62.2 / 51.8.  Only where all
+// blocks of both run at once.
+template <int D>
+bool update_and_first_frame_supported(const Dims& dm, int ns) {
+  auto blocks = [&](long long n) -> long long { return n * ((dm.b + 127) / 128); };
+  return ns > 1 && blocks((long long)dm.BH * dm.T) + blocks((long long)dm.BH * ns) <= (D == 64 ? 3 : 2) * 256;
+}
+
+template <int D>
+hipError_t launch_update_and_first_frame_flash2(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL, float* part_o,
+                                                float* part_lse, const Dims& dm, float row_scale, float cr_min, int ns,
+                                                int keys_per_split, hipStream_t st) {
+  FlashParams A = r_update_params(q, nullptr, k, nullptr, aL, cL, nullptr, nullptr, dm, row_scale, cr_min);
+  FlashParams B = exact_rows_params(q, k, v, nullptr, nullptr, part_o, part_lse, dm, dm.b, nullptr, ns, keys_per_split);
+  hipError_t e = count_blocks(A, (long long)dm.BH * dm.T, 32 * W2);
+  if (e == hipSuccess) e = count_blocks(B, dm.BH, 32 * W2);
+  if (e != hipSuccess) return e;
+  constexpr int LDS_A = NSLOT * tile_rows<D, false, 1, 0, true>() * D * 2, LDS_B = 2 * NSLOT * tile_rows<D, true, 1, 0, true>() * D * 2;
+  constexpr int LDS_BYTES = LDS_A > LDS_B ? LDS_A : LDS_B;
+  auto kern = flash2_pair_kernel<D>;
+  static bool configured = false;  // the attribute is per function, set once per process
+  if (!configured) {
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  const int na = A.blocks_per_xcd * 8;
+  hipLaunchKernelGGL(kern, dim3(na + B.blocks_per_xcd * 8), dim3(64 * W2), LDS_BYTES, st, A, B, na);
+  return hipGetLastError();
+}
+
 // This file is compiled once per head dimension.
 template hipError_t launch_exact_rows_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*, float*, float*,
                                                           const Dims&, int, const int*, int, int, bool, hipStream_t);
+template bool update_and_first_frame_supported<VM_FLASH2_D>(const Dims&, int);
+template hipError_t launch_update_and_first_frame_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*, float*, float*,
+                                                                      const Dims&, float, float, int, int, hipStream_t);
 template hipError_t launch_sink_average_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, const Dims&, hipStream_t);
 template hipError_t launch_l_update_flash2<VM_FLASH2_D>(const bf16_t*, const bf16_t*, const float*, const bf16_t*, bf16_t*, float*, bf16_t*,
                                                         float*, const Dims&, float, hipStream_t);

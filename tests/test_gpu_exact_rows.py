@@ -69,3 +69,21 @@ def test_sink_pass(env, heads, T, b, d):
         ref = O.softmax_attention(U.to_f64(q[h]), U.to_f64(k[h])[:b], U.to_f64(v[h])[:b], 1.0 / math.sqrt(d))
         assert U.rel_l2(got[h], (ref + U.from_device(base)[h]) / 2) <= 4e-3
     assert U.rel_l2(got, one_tile) <= 6e-3
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,T,b", [(1, 5, 161), (2, 9, 257), (4, 13, 385), (12, 13, 300), (40, 30, 200)])
+def test_first_frame_of_small_calls(env, heads, T, b, d):
+    """A small call's first frame goes along with its first update (the last shape is too large for that): the other frames
+    keep the bits of the call without it, the first frame agrees with the entry point of its own."""
+    torch, binding, dev = env
+    rng = np.random.default_rng(T * b + d)
+    tq, tk, tv = (U.to_device(list(U.random_bits(rng, (heads, T * b, d), 1.5, True)), torch, dev) for _ in range(3))
+    got = binding.attention(tq, tk, tv, T, 1, b, iters=2, recompute=1)
+    rest = binding.attention(tq, tk, tv, T, 1, b, iters=2, recompute=0)
+    assert torch.equal(got[:, :, b:].view(torch.uint8), rest[:, :, b:].view(torch.uint8))
+    alone = binding.first_frame_attention(tq, tk, tv, T, 1, b, torch.zeros_like(tq))
+    assert U.rel_l2(U.from_device(got[:, :, :b]), U.from_device(alone[:, :, :b])) <= 6e-3
+    ref = O.softmax_attention(U.to_f64(tq[0, 0, :b].view(torch.uint16).cpu().numpy()), *(U.to_f64(x[0, 0].view(torch.uint16).cpu().numpy())
+                              for x in (tk, tv)), 1.0 / math.sqrt(d))
+    assert U.rel_l2(U.from_device(got)[0, :b], ref) <= 4e-3
