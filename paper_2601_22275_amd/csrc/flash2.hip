@@ -328,13 +328,12 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
 
   // ---- one step = one 32-key sub-tile, as a fixed sequence of groups ------------------------
   // Software pipeline over sub-tiles n = 0, 1, ...  Step n carries, in the one wave,
-  //   matrix:  S^T of sub-tile n+1 (both query tiles), then O^T += X^T P^T of sub-tile n-1;
+  //   matrix:  S^T of sub-tile n+1 (all query tiles), then O^T += X^T P^T of sub-tile n-1;
   //   vector:  p = 2^t, sums and bf16 P^T of sub-tile n, whose sums then say whether its references held.
   // A group is the MFMAs (one per query tile) that share one A operand from LDS: KS groups of
   // logits, then 2 CT NX groups of products in the order (16-key half c, channel tile ct, product x).  The
-  // operand of group i + PF is requested while group i runs (a ring of four operand registers; NG is a
-  // multiple of four, so ring positions repeat from step to step and the requests run on across steps,
-  // tiles and barriers).  The vector work is cut into pieces that are dealt to the MFMA slots so that no
+  // operand of group i + PF is requested while group i runs (a ring of operand registers whose length divides NG, so that
+  // ring positions repeat from step to step and, with two sub-tiles per tile, the requests run on across steps, tiles and barriers).  The vector work is cut into pieces that are dealt to the MFMA slots so that no
   // slot carries more than an MFMA's worth of it when there is enough matrix work to hide it.
   constexpr int NPV = 2 * CT * NX;
   constexpr int NG = KS + NPV;
@@ -537,10 +536,12 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
       static_for<0, Q2>([&](auto qc) {
         constexpr int SL = Q2 * GI + decltype(qc)::value;
         issue(gc, qc, snext, pbprev);
-        // score pairs dealt evenly over the slots: pair k starts in slot floor(k NSL / 16), its exponents follow one
+        // score pairs dealt evenly over the slots: pair k starts in slot floor(k NSL / (8 Q2)), its exponents follow one
         // slot later and its sums two slots later (both clamped to the step's last slot).  Pairs in ascending
         // order, stages in their own order: a pair's stages that meet in one slot stay in sequence, and the sums
-        // of pair k come before pair k + 2 reuses its buffers (it starts at least two slots after pair k).
+        // of pair k come before pair k + 2 reuses its buffers (it starts two slots after pair k; one in the pass without
+        // products, whose sums need no exponents).
+        static_assert(NSL >= 8 * Q2 || ENT != 1, "the sums of p t find their exponents");
         static_for<0, 8 * Q2>([&](auto kc) {
           constexpr int K = decltype(kc)::value;
           constexpr int S0 = (K * NSL) / (8 * Q2);
@@ -581,7 +582,7 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
 #pragma unroll
         for (int c = 0; c < 2; ++c) pbB[qt][c] = zero;  // step 0 has no predecessor: it adds P^T = 0
     }
-    // A wave whose 64 query rows all lie past the end of the problem (the tail of the last query
+    // A wave whose query rows all lie past the end of the problem (the tail of the last query
     // block) only helps to load the tiles.
     const bool active = qb * BQ2 + wave * (32 * Q2) < P.nq;
     if (active) {
@@ -662,7 +663,7 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
       for (int ct = 0; ct < CT; ++ct) asm volatile("" : "+a"(oacc[x][qt][ct]));  // ... and not before this line
   F2_FENCE();
   // ---- epilogue ------------------------------------------------------------------------------
-  // Normalised rows are staged in LDS (each wave owns the 64 rows it computed, swizzled like the
+  // Normalised rows are staged in LDS (each wave owns the rows it computed, swizzled like the
   // key tiles; the R K rows over the K slots, the R V rows over the V slots) and leave as whole
   // rows, 16 bytes per lane.  Lane-dependent values are derived again from the thread index,
   // behind an opaque copy, so that none of the epilogue's address arithmetic stays live across
