@@ -260,7 +260,7 @@ def main() -> int:
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--flash-variant", type=int, choices=[0, 1, 2], default=None,
                     help="bf16 MFMA R-update kernels: 0 two waves per SIMD, 1 up to two query tiles per "
-                         "wave, 2 the latter for the update with values only (default: the library's setting)")
+                         "wave, 2 each update on the kernel measured faster (default: the library's setting)")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run one token-permutation copy of known size (reference for HBM byte counters)")
     ap.add_argument("--backward", action="store_true",
