@@ -33,22 +33,40 @@ namespace {
 
 constexpr int W2 = 4;             // waves per workgroup
 // No running row maximum is kept.  A row's reference comes from the maximum of its first 32 logits, and any reference gives the
-// same results: the sums and the accumulators carry the common factor 2^-reference, the weights are formed in fp32 and rounded
+// same outputs: the sums and the accumulators carry the common factor 2^-reference, the weights are formed in fp32 and rounded
 // to bf16, which has fp32's exponent range, so a stale reference costs the outputs no precision until 2^t nears overflow.  What
 // would overflow shows in the sums: a sub-tile whose weights add up to more than this in any lane is formed again, before its
 // products, against references from its own row maxima (`redo`).  The maxima and their bookkeeping were 18 % of the vector
 // instructions, which bound the loop (busy 0.85 of the cycles at d = 64 without values).  Measured, R-update without / with
 // values: 12 x 32 frames of 2048, d = 64: 472 -> 441 / 713 -> 654 us (934, 945 TFLOP/s); 12 x 21 of 1536, d = 128: 317 -> 298 /
 // 453 -> 431 us (1021, 1060).
-// c_L needs one precaution: the sum h of p t and the sum l of p must weigh every key alike, or their mismatch (about 1e-3
+// c_L needs two precautions.  The sum h of p t and the sum l of p must weigh every key alike, or their mismatch (about 1e-3
 // relative when l holds the bf16-rounded p and h the unrounded ones) is multiplied by the mean of t, which a stale reference
-// lets grow to 32; both carry the UNROUNDED p here, beside the rounded sum that the outputs are divided by.
-constexpr float STEP_MAX2 = 4294967296.0f;  // 2^32
-// Where a reference is put: this far (log2 units) above the row maximum, the first one included.  The largest probability of a
-// row is then 2^-64 (keys more than 2^-62 below the row maximum flush to zero), and a new reference is needed only where the
-// maximum grows by 2^92 or more: moving one passes the accumulators through ordinary registers and forms a sub-tile twice, and
-// attention can be sharp (c_R raises logits up to tenfold; row maxima then jump by more than 2^32 from tile to tile).
-constexpr float HEADROOM2 = 64.0f;
+// lets grow; both carry the UNROUNDED p here, beside the rounded sum that the outputs are divided by.  And c_L = h / l - log2 l is a
+// difference of two numbers of the size of t at the keys that matter, so the reference belongs at the row's maximum: see
+// HEADROOM2.
+constexpr float STEP_MAX2 = 18446744073709551616.0f;  // 2^64: leaves the accumulators 2^47 of room at 2^17 keys
+// A reference is put at the row's maximum.  Only where attention is sharp it is put above it, by up to this much (log2 units), because
+// moving one passes the accumulators through ordinary registers and forms a sub-tile twice, and the maxima of such rows jump from
+// tile to tile (c_R raises logits up to tenfold): with first references and moves at the maximum itself 252 frames of 1560, d = 128, logits of
+// deviation 20 / 30 in natural units, take 394 / 513 us without values, with this headroom 347 / 362.  Sharp are rows whose first 32 logits
+// span more than 40 log2 units, and rows that have to move; the fp32 rounding of logits of that size costs c_L as much as the headroom does.
+// Every row 2^64 above its maximum instead cost c_L a digit: largest error for deviations 1 / 3 / 20, 2 x 1560 rows, d = 128: 1.9e-5 /
+// 3.5e-5 / 2.1e-5, now 1.3e-6 / 4.5e-6 / 8.4e-6; d = 64 2.0e-5 / 2.4e-5 / 1.9e-5, now 1.2e-6 / 4.9e-6 / 8.4e-6 (flash_kernel, at most 2^8
+// below the maximum: 2.7e-6 / 8.5e-6 / 4.4e-6).  It also drove products with values below 2^-62 under the smallest normal number.
+// STEP_MAX2 * 2^HEADROOM2 must stay below 2^102: the factor that a move rescales by is then normal wherever old sums still count.
+constexpr float HEADROOM2 = 32.0f;
+// A row that a wave's move finds this far above its reference (log2 units) is taken for sharp and moves along.
+constexpr float MOVE_ALONG2 = 8.0f;
+
+// The headroom of a row's first reference from its first 32 logits, which span `top` downwards.
+__device__ __forceinline__ float first_headroom(const f32x16& s, float sc, float top) {
+  f32x16 neg;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) neg[r] = -s[r];
+  const float bottom = fmaxf(-subtile_max(neg) * sc, NEG_BIG);
+  return fminf(fmaxf(0.8f * (top - bottom) - 32.0f, 0.f), HEADROOM2);
+}
 
 __device__ __forceinline__ uint32_t avg_bf16x2(uint32_t a, uint32_t b) {
   const float lo = 0.5f * (__uint_as_float(a << 16) + __uint_as_float(b << 16));
@@ -470,9 +488,10 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
     F2_MFMA_RESULT_WAIT();
     F2_FENCE();
   };
-  // Query tile qt takes a reference of HEADROOM2 above `cand`; everything so far is rescaled (App. B: h <- a h + a log(a) l).
+  // Rows of query tile qt that have outgrown their reference take one of HEADROOM2 above `cand`; everything so far is rescaled
+  // (App. B: h <- a h + a log(a) l).
   auto move_reference = [&](int qt, float cand) __attribute__((always_inline)) {
-    const float m = fmaxf(msc[qt], cand + HEADROOM2);
+    const float m = cand > msc[qt] + MOVE_ALONG2 ? cand + HEADROOM2 : msc[qt];
     const float dl = msc[qt] - m;  // log2 of the rescale factor, <= 0
     const float alpha = __builtin_amdgcn_exp2f(dl);
     if (ENT == 1) {
@@ -588,9 +607,29 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
     if (active) {
       // logits of sub-tile 0, plain form; their row maxima are the first references
       plain_logits(0, sA, 0);
+      if (BIAS != 2) {
+        float head[Q2];
+        bool sharp = false;
 #pragma unroll
-      for (int qt = 0; qt < Q2; ++qt)
-        if (BIAS != 2) msc[qt] = fmaxf(msc[qt], subtile_max(sA[qt]) * sc[qt] + HEADROOM2);
+        for (int qt = 0; qt < Q2; ++qt) {
+          msc[qt] = fmaxf(subtile_max(sA[qt]) * sc[qt], NEG_BIG);
+          head[qt] = first_headroom(sA[qt], sc[qt], msc[qt]);
+          sharp = sharp || head[qt] >= HEADROOM2;
+        }
+        // in sharp rows the first 32 logits say little of the rest: the maxima of all keys that are here (deviation 30: moves
+        // from 462 to 362 us where 340 need none)
+        if (__any(sharp)) {
+          const int subs = min(2, ntiles) * (BT / 32);
+#pragma unroll 1
+          for (int sub = 1; sub < subs; ++sub) {
+            plain_logits(sub * 32 * ROW_BYTES, sB, sub);
+#pragma unroll
+            for (int qt = 0; qt < Q2; ++qt) msc[qt] = fmaxf(msc[qt], subtile_max(sB[qt]) * sc[qt]);
+          }
+        }
+#pragma unroll
+        for (int qt = 0; qt < Q2; ++qt) msc[qt] += head[qt];
+      }
       // operands of the first groups of the first step (sub-tile 1 of slot 0; products against slot 3)
       if constexpr (BT == 64) static_for<0, PF>([&](auto gc) { request(gc, 32 * ROW_BYTES, 3 * TILE_BYTES + 32 * ROW_BYTES); });
     }
