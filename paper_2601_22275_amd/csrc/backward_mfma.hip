@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "flash_select.h"
 
 namespace vm {
 
@@ -38,7 +39,7 @@ namespace {
 // Workgroups are NW waves of 32 owner rows: 4 at d = 64, two or three of them on a compute unit, 4 or 8 at d = 128.  Smaller blocks leave less of the
 // last block and the last round idle and hide each other's start and end (all gradients, d = 64, eight -> four waves: 90 frames
 // of 943 131 -> 114 us, 252 of 1560 722 -> 667, 128 of 512 level).  At d = 128 two workgroups leave LDS for tiles of 32 stream rows, a
-// barrier for every 32 rows: which launch takes which, see launch_entropy_bwd_mfma.
+// barrier for every 32 rows: which launch takes which: flash_select.h.
 template <int D, int NW>
 constexpr int tile_rows() {  // stream rows per LDS tile
   return D == 128 && NW == 4 ? 32 : 64;
@@ -443,13 +444,7 @@ hipError_t launch_entropy_bwd_mfma(const bf16_t* q, const float* cR, const bf16_
   };
   using four = std::integral_constant<int, 4>;
   if (dm.d == 64) return run(std::integral_constant<int, 64>{}, four{});
-  // d = 128: blocks of 128 rows, two on a compute unit, or of 256, one?  The times follow from the blocks per unit, with a pair of short
-  // blocks (0.96 .. 1.04, by the frame) and a single one (0.80) measured against a long block.  All gradients, plain form, short against long, us: 130 frames
-  // of 300 44 / 79, 32 of 1000 74 / 91, 400 of 720 446 / 468, 252 of 512 134 / 142, of 1536 1011 / 996, of 1560 1091 / 1090.
-  auto units = [&](int rows) -> long long { return (problems * ((dm.b + rows - 1) / rows) + 255) / 256; };
-  const long long n1 = units(128), n2 = units(256);
-  const double pair = dm.b > 900 ? 1.04 : 0.96;
-  if (pair * (double)(n1 / 2) + 0.80 * (double)(n1 % 2) < (double)n2) return run(std::integral_constant<int, 128>{}, four{});
+  if (backward_short_blocks(problems, dm.b, compute_units())) return run(std::integral_constant<int, 128>{}, four{});
   return run(std::integral_constant<int, 128>{}, std::integral_constant<int, 8>{});
 }
 

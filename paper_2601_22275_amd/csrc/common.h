@@ -68,6 +68,9 @@ struct Dims {
   long long N;  // T * b
 };
 
+// compute units of the device (flash.hip)
+int compute_units();
+
 // ---- launchers (host) -------------------------------------------------------------
 // generic.hip : plain-ALU kernels, any T, b, d <= 256, element type float or bf16
 template <typename E>

@@ -23,6 +23,7 @@
 
 #include "common.h"
 #include "flash_device.h"
+#include "flash_select.h"
 
 namespace vm {
 
@@ -490,43 +491,7 @@ hipError_t launch_flash(const FlashParams& P, hipStream_t st) {
   return hipGetLastError();
 }
 
-int compute_units() {
-  static int cus = 0;  // one device per process is assumed for this tuning value only
-  if (cus == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-      cus = n;
-    else
-      cus = 256;
-  }
-  return cus;
-}
-
-// Key ranges for exact attention of `nrows` query rows per head over all N keys.  One workgroup
-// occupies a compute unit, and all work items take the same time, so the launch runs in
-// ceil(items / CUs) rounds: the split count is the one that wastes least of the last round,
-// after a charge of a few tiles' worth of time per item for its start-up and wind-down.
-int first_frame_splits(const Dims& dm, int nrows) {
-  const long long nqb = (nrows + BQ - 1) / BQ;
-  const long long tiles = (dm.N + BK - 1) / BK;
-  const long long cus = compute_units();
-  int best = 1;
-  double best_score = -1.0;
-  for (long long s = 1; s <= 64; ++s) {
-    const long long per = (tiles + s - 1) / s;  // tiles per key range
-    if (s > 1 && per < 8) break;
-    if ((tiles + per - 1) / per != s) continue;  // would leave an empty range: the same as a smaller count
-    const long long items = (long long)dm.BH * nqb * s;
-    const long long rounds = (items + cus - 1) / cus;
-    const double score = (double)items / (double)(rounds * cus) * (double)per / (double)(per + 6);
-    if (score > best_score * 1.005) {  // prefer fewer ranges (less merge traffic) unless clearly better
-      best_score = score;
-      best = (int)s;
-    }
-  }
-  return best;
-}
+int first_frame_splits(const Dims& dm, int nrows) { return exact_rows_ranges(dm.BH, nrows, dm.N, compute_units()); }
 
 // Where the partial results of `ns` key ranges lie in their scratch: log2-sum-exps, then rows
 struct Partials {
@@ -547,6 +512,15 @@ hipError_t launch_merge(const float* part_o, const float* part_lse, bf16_t* out,
 }
 
 }  // namespace
+
+int compute_units() {
+  // one device per process is assumed for this tuning value only
+  static const int units = [] {
+    int dev = 0, n = 0;
+    return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0 ? n : 256;
+  }();
+  return units;
+}
 
 bool temporal_flash_supported(const Dims& dm) { return (dm.d == 128 || dm.d == 64) && dm.T <= kMaxBiasedKeys; }
 
@@ -608,8 +582,7 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   P.nk = (int)dm.N;
   P.nqb = (nrows + BQ - 1) / BQ;
   P.nsplit = ns;
-  const long long tiles = (dm.N + BK - 1) / BK;
-  P.keys_per_split = (int)(((tiles + ns - 1) / ns) * BK);
+  P.keys_per_split = (int)exact_rows_range_keys(dm.N, ns);
   long long total = (long long)dm.BH * P.nqb * ns;
   if (total > 0x3fffffffLL) return hipErrorInvalidValue;
   P.total_blocks = (int)total;
@@ -620,11 +593,7 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   // A list as long as the head stays on this file's kernel: a list of all rows gives the bits of the range form of variant 0, which
   // is tested.
   if (row_list != nullptr && nrows >= dm.N) two_tile = false;
-  // Query blocks of 128 rows instead of 256 where the items are small, for lack of keys or of rows to fill the units: their start
-  // and end count then, and the short blocks hide them from each other (short / long, us, ranges and partial results the same:
-  // d = 128: 4 heads x 400 rows x 8000 keys (16 ranges of 512) 29.9 / 36.6, 12 x 200 x 32,760 (21 of 1600) 67.2 / 67.0, 24 x 500 x 20,000
-  // (5 of 4032) 150.6 / 131.8; d = 64: 10 x 323 x 4199 (9 of 512) 22.2 / 23.9, 8 x 800 x 16,000 (8 of 2048) 48.8 / 48.2).
-  const bool short_blocks = P.keys_per_split <= 1536 || 2 * total <= compute_units();
+  const bool short_blocks = exact_rows_short_blocks(dm.BH, nrows, dm.N, compute_units());
   auto two_tile_pass = [&](float* part_o, float* part_lse) {
     return d128 ? launch_exact_rows_flash2<128>(q, k, v, out, lse, part_o, part_lse, dm, nrows, row_list, ns, P.keys_per_split, short_blocks, st)
                 : launch_exact_rows_flash2<64>(q, k, v, out, lse, part_o, part_lse, dm, nrows, row_list, ns, P.keys_per_split, short_blocks, st);
@@ -653,8 +622,7 @@ hipError_t launch_update_and_first_frame(const bf16_t* q, const bf16_t* k, const
   if (!(dm.d == 128 ? update_and_first_frame_supported<128>(dm, ns) : update_and_first_frame_supported<64>(dm, ns))) return hipSuccess;
   if (scratch == nullptr || scratch_bytes < first_frame_flash_scratch_bytes(dm, dm.b)) return hipErrorInvalidValue;
   const Partials part = partials_in(scratch, dm, dm.b, ns);
-  const long long tiles = (dm.N + BK - 1) / BK;
-  const int keys_per_split = (int)(((tiles + ns - 1) / ns) * BK);
+  const int keys_per_split = (int)exact_rows_range_keys(dm.N, ns);
   const hipError_t e = dm.d == 128 ? launch_update_and_first_frame_flash2<128>(q, k, v, aL, cL, part.o, part.lse, dm, row_scale, cr_min, ns, keys_per_split, st)
                                    : launch_update_and_first_frame_flash2<64>(q, k, v, aL, cL, part.o, part.lse, dm, row_scale, cr_min, ns, keys_per_split, st);
   *done = e == hipSuccess;

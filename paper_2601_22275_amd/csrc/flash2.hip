@@ -8,7 +8,7 @@
 // One workgroup = 4 waves.  With two tiles a wave owns 64 query rows for the whole key loop and, at d = 128 with values, the
 // full register file of its SIMD (512 registers), which is what lets one wave hold both accumulator sets (R K and R V:
 // 2 x 2 x 4 tiles of 16 registers) beside its queries and logits.  With one tile (32 rows, 128 in a workgroup) two or three
-// workgroups share a compute unit; which launch takes which: short_blocks_faster.  Keys (and values) stream through LDS in 64-row tiles, four slots per
+// workgroups share a compute unit; which launch takes which: flash_select.h.  Keys (and values) stream through LDS in 64-row tiles, four slots per
 // tensor, loaded two tiles ahead.  Both contractions use v_mfma_f32_32x32x16_bf16:
 //
 //   S^T = K Q^T     A = K rows read from LDS (ds_read_b128), B = Q^T held in registers.  One A
@@ -26,6 +26,7 @@
 
 #include "common.h"
 #include "flash_device.h"
+#include "flash_select.h"
 
 namespace vm {
 
@@ -846,29 +847,6 @@ hipError_t launch_flash2(FlashParams P, long long problems, hipStream_t st) {
 #undef F2_FENCE
 #undef F2_MFMA_RESULT_WAIT
 
-// Query blocks of 128 rows (one query tile per wave) or of 256?  Of the short ones three share a compute unit at
-// d = 64 without values, two otherwise; of the long ones two and one.  The short ones hide each other's start and end and waste
-// less on a ragged last block or round; the long ones read an operand from LDS for two products, which counts where the launch is long
-// and the device's power is the limit.  A unit works through its blocks in groups as large as it holds, so the two launches'
-// times follow from the blocks per unit, with the time of a group of 1, 2, 3 blocks against the long blocks' largest group measured on
-// 10 launch sizes (4 .. 972 frames) x 12 frame sizes (130 .. 3600 tokens), video-like and random inputs.  Short against long, us: d =
-// 64: 16 frames of 1000 16.8 / 24.6, 130 of 300 11.1 / 16.5, 80 of 1280 52.2 / 46.7, 252 of 2048 308 / 289, with values 20.3 / 29.3, 126 of
-// 300 13.3 / 14.8, 252 of 2048 474 / 450; d = 128: 130 of 300 15.0 / 29.5, 130 of 1456 158 / 176, 252 of 2048 532 / 509, with values 20.8 /
-// 42.1, 230 / 257, 793 / 741.
-// long_pairs: two long blocks share a unit (three short ones); else one (two), a pair of short ones takes `pair` of a long one's time.
-bool short_blocks_faster(long long problems, int rows, bool long_pairs, double pair) {
-  auto units = [&](int block) -> long long { return (problems * ((rows + block - 1) / block) + 255) / 256; };  // blocks per compute unit
-  const long long n1 = units(128), n2 = units(256);
-  if (long_pairs) {
-    const double rest1[3] = {0.0, 0.43, 0.64};
-    return 0.87 * (double)(n1 / 3) + rest1[n1 % 3] < (double)(n2 / 2) + 0.64 * (double)(n2 % 2);
-  }
-  return pair * (double)(n1 / 2) + 0.66 * (double)(n1 % 2) < (double)n2;
-}
-
-}  // namespace
-
-namespace {
 FlashParams exact_rows_params(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* out, float* lse, float* part_o, float* part_lse,
                               const Dims& dm, int nrows, const int* rows, int ns, int keys_per_split) {
   FlashParams P = {};
@@ -928,7 +906,7 @@ hipError_t launch_sink_average_flash2(const bf16_t* q, const bf16_t* k, const bf
   // 21 frames of 1560 312 / 331, 40 x 60 of 100 47.9 / 65.7; d = 64: 4 x 8 of 1000 17.4 / 23.4, 12 x 21 of 300 17.7 / 17.4, of 1560 196
   // / 160; the one-tile kernel of flash.hip 336, 53.0, 23.2, 21.2, 205).
   if constexpr (D == 64)
-    if ((P.nq + 255LL) / 256 * dm.BH > 256) return launch_flash2<D, false, true, 0, false, 2>(P, dm.BH, st);
+    if ((P.nq + 255LL) / 256 * dm.BH > compute_units()) return launch_flash2<D, false, true, 0, false, 2>(P, dm.BH, st);
   return launch_flash2<D, false, true, 0, false, 1>(P, dm.BH, st);
 }
 
@@ -944,9 +922,7 @@ hipError_t launch_sink_average_flash2(const bf16_t* q, const bf16_t* k, const bf
 // lse_scratch: BH * N floats (fitting sweep only).
 // The pass for the log-sum-exps keeps no products, a key's term is the value its logits' accumulation starts from, and there is no running
 // maximum: vector work, which bounds these passes at d = 64 (0.69 .. 0.81 of the cycles), falls by a quarter.  12 x 64 problems of 512
-// frames, d = 64: fitting 128 -> 106 us, last 83 -> 71; 8 x 100 of 300 88 -> 66, 55 -> 44, d = 128 173 -> 112, 109 -> 75.  Block sizes as in
-// the fitting update at d = 64, whose long blocks come two to a unit as here; at d = 128 the products' tiles and registers leave room
-// for two short blocks or one long one, and the short ones win (12 x 64 of 512 fitting 207 / 218 us, 8 x 100 of 300 110 / 150).
+// frames, d = 64: fitting 128 -> 106 us, last 83 -> 71; 8 x 100 of 300 88 -> 66, 55 -> 44, d = 128 173 -> 112, 109 -> 75.
 template <int D>
 hipError_t launch_l_update_flash2(const bf16_t* q, const bf16_t* aL, const float* cL, const bf16_t* y, bf16_t* aR, float* cR,
                                   bf16_t* out, float* lse_scratch, const Dims& dm, float q_scale, hipStream_t st) {
@@ -960,23 +936,24 @@ hipError_t launch_l_update_flash2(const bf16_t* q, const bf16_t* aL, const float
   P.row_scale = q_scale;
   P.kb_scale = -LOG2E;
   const long long problems = (long long)dm.BH * dm.b;
-  const bool short_blocks = short_blocks_faster(problems, dm.T, true, 0.0);
+  const int units = compute_units();
+  const bool short_products = temporal_product_short_blocks(D, problems, dm.T, units);
   if (y != nullptr) {
     P.q = q; P.k = aL; P.v = y; P.outv = out; P.kbias = cL;
     if constexpr (D == 64)
-      if (!short_blocks) return launch_flash2<D, false, true, 0, false, 2, 1>(P, problems, st);
+      if (!short_products) return launch_flash2<D, false, true, 0, false, 2, 1>(P, problems, st);
     return launch_flash2<D, false, true, 0, false, 1, 1>(P, problems, st);
   }
   if (lse_scratch == nullptr) return hipErrorInvalidValue;
   P.q = q; P.k = aL; P.lse = lse_scratch; P.kbias = cL;
-  hipError_t e = short_blocks ? launch_flash2<D, true, false, 0, false, 1, 1>(P, problems, st)
-                              : launch_flash2<D, true, false, 0, false, 2, 1>(P, problems, st);
+  hipError_t e = temporal_lse_short_blocks(D, problems, dm.T, units) ? launch_flash2<D, true, false, 0, false, 1, 1>(P, problems, st)
+                                                                     : launch_flash2<D, true, false, 0, false, 2, 1>(P, problems, st);
   if (e != hipSuccess) return e;
   P.q = aL; P.k = q; P.outk = aR; P.cl = cR; P.lse = nullptr;
   P.kbias = lse_scratch;          // natural log, like c_L: the same scale -log2(e) applies
   P.qbias = cL; P.qb_scale = LOG2E;
   if constexpr (D == 64)
-    if (!short_blocks) return launch_flash2<D, true, false, 0, false, 2, 2>(P, problems, st);
+    if (!short_products) return launch_flash2<D, true, false, 0, false, 2, 2>(P, problems, st);
   return launch_flash2<D, true, false, 0, false, 1, 2>(P, problems, st);
 }
 
@@ -988,7 +965,7 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
   if (dm.d != D || (v == nullptr) != (y == nullptr)) return hipErrorInvalidValue;
   const FlashParams P = r_update_params(aR, cR, k, v, aL, cL, y, lse, dm, row_scale, cr_min);
   const long long problems = (long long)dm.BH * dm.T;
-  const bool short_blocks = short_blocks_faster(problems, dm.b, D == 64 && v == nullptr, dm.b <= 900 ? 0.95 : D == 64 ? 1.05 : 1.06);
+  const bool short_blocks = update_short_blocks(D, v != nullptr, problems, dm.b, compute_units());
   auto launch = [&](auto ent) -> hipError_t {
     constexpr int ENT = decltype(ent)::value;
     if (v == nullptr)
@@ -1006,7 +983,7 @@ hipError_t launch_r_update_flash2(const bf16_t* aR, const float* cR, const bf16_
 template <int D>
 bool update_and_first_frame_supported(const Dims& dm, int ns) {
   auto blocks = [&](long long n) -> long long { return n * ((dm.b + 127) / 128); };
-  return ns > 1 && blocks((long long)dm.BH * dm.T) + blocks((long long)dm.BH * ns) <= (D == 64 ? 3 : 2) * 256;
+  return ns > 1 && blocks((long long)dm.BH * dm.T) + blocks((long long)dm.BH * ns) <= (D == 64 ? 3 : 2) * compute_units();
 }
 
 template <int D>

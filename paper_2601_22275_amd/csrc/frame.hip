@@ -18,6 +18,7 @@
 // by the sum of the bf16-rounded weights.
 #include "common.h"
 #include "flash_device.h"
+#include "flash_select.h"
 
 namespace vm {
 
@@ -233,15 +234,10 @@ hipError_t launch_frames(const FrameParams& P, unsigned frames, hipStream_t st) 
 
 }  // namespace
 
-// Where this kernel is the faster one, by sweeps of b = 32 .. 256 with 16 .. 6000 frames against the streaming kernel's blocks of 128
-// rows (us for 2000 frames, this kernel / that one).  d = 64 without values up to 160 tokens: 20.7 / 22.9 at 128, 34.2 / 40.4 at 160, 50.8
-// / 41.0 at 192; with values up to 224: 79 / 88 there, 101.6 / 96.9 at 256.  d = 128 without values up to 160: 33.2 / 38.8 at 128, 70.9 /
-// 72.6 at 160, 94.5 / 81.0 at 192; with values up to 128: 63 / 72 there, 120.8 / 109.1 at 160, and up to 192 while all frames run at
-// once (130 frames of 192: 13.1 / 15.1; a seventh tile of logits spills).
 bool frame_supported(const Dims& dm, bool with_v) {
   if (dm.d != 64 && dm.d != 128) return false;
   const long long frames = (long long)dm.BH * dm.T;
-  return dm.b <= (!with_v ? 160 : dm.d == 64 ? 224 : frames <= 256 ? 192 : 128) && frames <= 0x7fffff;
+  return dm.b <= whole_frame_tokens(dm.d, with_v, frames, compute_units()) && frames <= 0x7fffff;
 }
 
 hipError_t launch_r_update_frame(const bf16_t* aR, const float* cR, const bf16_t* k, const bf16_t* v, bf16_t* aL, float* cL,
