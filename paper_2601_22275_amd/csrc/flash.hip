@@ -590,9 +590,6 @@ hipError_t launch_first_frame_flash(const bf16_t* q, const bf16_t* k, const bf16
   P.row_scale = 1.0f / sqrtf((float)dm.d);
   P.cr_min = 0.f;
   const bool d128 = dm.d == 128;
-  // A list as long as the head stays on this file's kernel: a list of all rows gives the bits of the range form of variant 0, which
-  // is tested.
-  if (row_list != nullptr && nrows >= dm.N) two_tile = false;
   const bool short_blocks = exact_rows_short_blocks(dm.BH, nrows, dm.N, compute_units());
   auto two_tile_pass = [&](float* part_o, float* part_lse) {
     return d128 ? launch_exact_rows_flash2<128>(q, k, v, out, lse, part_o, part_lse, dm, nrows, row_list, ns, P.keys_per_split, short_blocks, st)

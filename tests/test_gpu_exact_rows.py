@@ -56,6 +56,19 @@ def test_listed_rows(env, heads, rows, N, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+def test_list_of_every_row(env, d):
+    """A list as long as the head takes the kernel of one that is a row shorter: the rows both name get the same bits."""
+    torch, binding, dev = env
+    N, rng = 320, np.random.default_rng(d)
+    tq, tk, tv = (U.to_device(list(U.random_bits(rng, (2, N, d), 1.5, True)), torch, dev) for _ in range(3))
+    rows = torch.from_numpy(rng.permutation(N).astype(np.int32)).to(dev)
+    zero = torch.zeros_like(tq)
+    every, shorter = (binding.recompute_tokens(tq, tk, tv, 1, 1, N, zero.clone(), r) for r in (rows, rows[:-1].contiguous()))
+    both = rows[:-1].long()
+    assert torch.equal(every[:, :, both].view(torch.uint8), shorter[:, :, both].view(torch.uint8))
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("heads,T,b", [(2, 5, 33), (40, 26, 65), (3, 2, 700)])
 def test_sink_pass(env, heads, T, b, d):
     torch, binding, dev = env

@@ -440,16 +440,16 @@ def test_recompute_tokens_any_subset(env, T, Hs, Ws, d, dt, kind):
         assert U.rel_l2(got[h][rows], ref) <= rel_tol and U.max_abs(got[h][rows], ref) <= abs_tol
         assert np.array_equal(got[h][untouched], base_np[h][untouched])
     if kind in ("all", "all-reversed"):
-        # the same rows as one contiguous range: identical arithmetic per row, identical bits, when the range runs on
-        # the kernel that gathers a list (the contiguous range may otherwise take the kernel with two query tiles
-        # per wave, whose sums associate differently: then the two agree to rounding)
+        # the same rows as one contiguous range on the same kernel: identical arithmetic per row, identical bits.  By default list and range
+        # may take query blocks and key ranges of their own; both forms under variant 0 run on the one-tile kernel
         default = binding.get_flash_variant()
         binding.set_flash_variant(0)
         try:
             ranged = binding.recompute_rows(tq, tk, tv, T, Hs, Ws, base.clone(), 0, N)
+            gathered = binding.recompute_tokens(tq, tk, tv, T, Hs, Ws, base.clone(), trows)
         finally:
             binding.set_flash_variant(default)
-        assert torch.equal(ranged.view(torch.uint8), out.view(torch.uint8))
+        assert torch.equal(ranged.view(torch.uint8), gathered.view(torch.uint8))
         ranged2 = binding.recompute_rows(tq, tk, tv, T, Hs, Ws, base.clone(), 0, N)
         assert U.max_abs(U.from_device(ranged2), U.from_device(out)) <= (2 * abs_tol if dt == "bf16" else 1e-5)
     with pytest.raises(binding.VMonarchError):
