@@ -15,7 +15,9 @@ extern "C" {
 
 /* While enabled, vmonarch_attention[_f32] records a HIP event on the caller's
  * stream before each of its phases ("r_update", "l_update", "r_update_last", "l_update_last",
- * "first_frame" or "sink_average") and one at the end.  vmonarch_get_phase_timing waits for the last call's
+ * "first_frame" or "sink_average") and one at the end.  Where a small bf16 call computes the first frame's key ranges in the
+ * launch of its first update, that phase is "r_update+first_frame" and the last one, which only merges them,
+ * "first_frame_merge".  vmonarch_get_phase_timing waits for the last call's
  * final event and writes, for up to `cap` phases, the elapsed milliseconds to ms_host[i] and
  * the phase name to names_host + 32*i (HOST buffers of cap floats / cap*32 chars).  A phase
  * may span more than one kernel launch.  Not thread-safe; off by default. */

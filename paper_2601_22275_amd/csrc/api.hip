@@ -68,6 +68,11 @@ void phase_mark(hipStream_t st, const char* name_of_phase_that_starts) {
   ++g_n_phases;
 }
 
+// The phase that started last turned out to hold more than its name says.
+void phase_rename(const char* name) {
+  if (g_timing && g_n_phases > 0) snprintf(g_phase_name[g_n_phases - 1], sizeof(g_phase_name[0]), "%s", name);
+}
+
 int fail(int code, const char* fmt, ...) {
   va_list ap;
   va_start(ap, fmt);
@@ -392,6 +397,7 @@ int attention_impl(const void* q_, const void* k_, const void* v_, void* out_, i
         const hipError_t e = launch_update_and_first_frame(q, k, v, aL, cL, ws + w.ff, w.total - w.ff, dm, s, cr_min, &ranges_done, st);
         if (e != hipSuccess) return hip_fail(e, "r_update + first_frame (bf16) launch");
         updated = ranges_done;
+        if (updated) phase_rename("r_update+first_frame");
       }
     }
     if (!updated)
@@ -420,7 +426,7 @@ int attention_impl(const void* q_, const void* k_, const void* v_, void* out_, i
     rc = sink_average_any<E>(q, k, v, out, dm, cfg.flash_variant, st);
     if (rc) return rc;
   } else if (recompute) {
-    phase_mark(st, "first_frame");
+    phase_mark(st, ranges_done ? "first_frame_merge" : "first_frame");
     // f32: the sweeps are done with alpha_L and y, whose room (adjacent) takes the partial sums of the key ranges
     const bool reuse = sizeof(E) == 4;
     if (ranges_done) {
