@@ -35,7 +35,9 @@
  *   - Sizes.  d <= 256, B*heads <= 65535, T <= 65535, N < 2^31 for every entry point; no other
  *     shape is refused.  bf16 with d == 128 or d == 64 runs on the MFMA kernels (the temporal factor
  *     on a kernel of its own up to T = 128 and through the blocked-softmax kernel up to T = 8128);
- *     other shapes and every `_f32` entry point run on slower plain-ALU kernels with the same results.
+ *     float32 with d == 32, 64 or 128 runs the softmax passes on the fp32 matrix units (tensors on 16-byte
+ *     boundaries, temporal factor up to T = 32).  Other shapes run on slower plain-ALU kernels with the
+ *     same results.
  *   - (T, Hs, Ws) only enter as m = T blocks of b = Hs*Ws tokens: a general Monarch split
  *     (m, b) of a sequence that is no video is T = m, Hs = 1, Ws = b.
  */
@@ -107,10 +109,10 @@ int vmonarch_get_manual_control(int* cr_control, int* cl_control, float* cl_valu
  * and whose accumulators live in accumulation registers; 2 (default) each update on the kernel
  * measured faster for it: short frames (up to 128 .. 224 tokens; online entropy and fused apply only)
  * on the kernel that takes a whole frame per workgroup; else that of 1, but for updates with values of
- * at most 128 tokens, which take that of 0. Exact attention of a contiguous row range
- * (first frame, vmonarch_recompute_rows) runs on the kernel of 1 unless the variant is 0; a row
- * list (vmonarch_recompute_tokens) and the sink averaging always run on the kernels of 0.  Same
- * results up to rounding order.  Process-wide. */
+ * at most 128 tokens, which take that of 0.  Exact attention of rows (first frame, vmonarch_recompute_rows,
+ * vmonarch_recompute_tokens) and the sink averaging run on the kernel of 1 unless the variant is 0.  The
+ * backward and the L-update do not depend on the variant.  Same results up to rounding order.
+ * Process-wide. */
 int vmonarch_set_flash_variant(int variant);
 int vmonarch_get_flash_variant(void);
 
@@ -190,8 +192,9 @@ int vmonarch_r_update_f32(const void* aR, const float* cR, const void* k, const 
  * The same R-update, which also returns the log-sum-exp of every query row's logits, the
  * per-row statistic Alg. 1 hands to the backward pass (Alg. 2) beside the entropy:
  *     lse_out[k,i] = log sum_l exp z[l]        (natural log; float32 [B][heads][T][b])
- * The row entropy of Alg. 1 is H = -cL_out.  On the bf16 MFMA path the sum inside the
- * logarithm is taken over the bf16-rounded probabilities (absolute error about 1e-3).
+ * The row entropy of Alg. 1 is H = -cL_out.  On the bf16 MFMA path both come from fp32 sums of the
+ * unrounded probabilities; only the wave-pair kernel (flash variant 0 with values and fused apply)
+ * sums the bf16-rounded ones (absolute error about 1e-3).
  * lse_out must not be NULL.
  */
 int vmonarch_r_update_lse(const void* aR, const float* cR, const void* k, const void* v, void* aL_out,
@@ -233,7 +236,8 @@ int vmonarch_first_frame_attention_f32(const void* q, const void* k, const void*
 /*
  * The same recomputation, which also returns lse_out[0:b] = log sum_n exp(Q[i] . K[n] / sqrt(d))
  * over all N keys (natural log).  lse_out: float32 [B][heads][T][b] like every per-token scalar;
- * only the entries of frame 0 are written.  lse_out must not be NULL.
+ * only the entries of frame 0 are written.  lse_out must not be NULL.  On the bf16 MFMA path the
+ * sum inside the logarithm is taken over the bf16-rounded probabilities (absolute error up to 3e-3).
  */
 int vmonarch_first_frame_attention_lse(const void* q, const void* k, const void* v, void* out,
                                        float* lse_out, int B, int heads, int T, int Hs, int Ws, int d,
