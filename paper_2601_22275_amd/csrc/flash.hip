@@ -29,10 +29,6 @@ namespace vm {
 
 namespace {
 
-// element-wise (a + b) / 2 of eight bf16 values, in float, rounded once
-__device__ __forceinline__ uint32_t average_bf16x2(uint32_t a, uint32_t b);
-__device__ __forceinline__ uint4 average_bf16x8(uint4 a, uint4 b);
-
 // ENT: c_L not wanted (0), online (1) or in the identity form (2).
 template <int D, bool OUT_K, bool OUT_V, int ENT, bool SPLIT>
 __global__ void __launch_bounds__(64 * NW) flash_kernel(FlashParams P) {
@@ -416,16 +412,6 @@ __global__ void __launch_bounds__(64 * NW) flash_kernel(FlashParams P) {
       }
     }
   }
-}
-
-__device__ __forceinline__ uint32_t average_bf16x2(uint32_t a, uint32_t b) {
-  const float lo = 0.5f * (__uint_as_float(a << 16) + __uint_as_float(b << 16));
-  const float hi = 0.5f * (__uint_as_float(a & 0xffff0000u) + __uint_as_float(b & 0xffff0000u));
-  return pack_bf16(lo, hi);
-}
-__device__ __forceinline__ uint4 average_bf16x8(uint4 a, uint4 b) {
-  return make_uint4(average_bf16x2(a.x, b.x), average_bf16x2(a.y, b.y), average_bf16x2(a.z, b.z),
-                    average_bf16x2(a.w, b.w));
 }
 
 // Merge of the key-range partials of exact rows: weights 2^(lse - max).  Bound by the reads of the partials: a thread takes four channels

@@ -8,8 +8,8 @@
 // One workgroup = 4 waves.  With two tiles a wave owns 64 query rows for the whole key loop and, at d = 128 with values, the
 // full register file of its SIMD (512 registers), which is what lets one wave hold both accumulator sets (R K and R V:
 // 2 x 2 x 4 tiles of 16 registers) beside its queries and logits.  With one tile (32 rows, 128 in a workgroup) two or three
-// workgroups share a compute unit; which launch takes which: flash_select.h.  Keys (and values) stream through LDS in 64-row tiles, four slots per
-// tensor, loaded two tiles ahead.  Both contractions use v_mfma_f32_32x32x16_bf16:
+// workgroups share a compute unit; which launch takes which: flash_select.h.  Keys (and values) stream through LDS in tiles of 64 rows (32 where two
+// workgroups would not fit a unit otherwise: tile_rows), four slots per tensor, loaded two tiles ahead.  Both contractions use v_mfma_f32_32x32x16_bf16:
 //
 //   S^T = K Q^T     A = K rows read from LDS (ds_read_b128), B = Q^T held in registers.  One A
 //                   operand serves all query tiles of the wave: with two, half the
@@ -67,15 +67,6 @@ __device__ __forceinline__ float first_headroom(const f32x16& s, float sc, float
   for (int r = 0; r < 16; ++r) neg[r] = -s[r];
   const float bottom = fmaxf(-subtile_max(neg) * sc, NEG_BIG);
   return fminf(fmaxf(0.8f * (top - bottom) - 32.0f, 0.f), HEADROOM2);
-}
-
-__device__ __forceinline__ uint32_t avg_bf16x2(uint32_t a, uint32_t b) {
-  const float lo = 0.5f * (__uint_as_float(a << 16) + __uint_as_float(b << 16));
-  const float hi = 0.5f * (__uint_as_float(a & 0xffff0000u) + __uint_as_float(b & 0xffff0000u));
-  return pack_bf16(lo, hi);
-}
-__device__ __forceinline__ uint4 avg_bf16x8(uint4 a, uint4 b) {
-  return make_uint4(avg_bf16x2(a.x, b.x), avg_bf16x2(a.y, b.y), avg_bf16x2(a.z, b.z), avg_bf16x2(a.w, b.w));
 }
 
 template <int I, int N, typename F>
@@ -792,7 +783,7 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
         if (r >= 0) {
           uint4 w = *reinterpret_cast<const uint4*>(stage + lr * ROW_BYTES + pc * 16);
           uint4* gp = reinterpret_cast<uint4*>(dst + (qrow0 + r * rs) * D + lc * 8);
-          if (P.blend) w = avg_bf16x8(w, *gp);
+          if (P.blend) w = average_bf16x8(w, *gp);
           *gp = w;
         }
       }

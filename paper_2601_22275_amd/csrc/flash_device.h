@@ -82,6 +82,17 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return u;
 }
 
+// element-wise (a + b) / 2 of eight bf16 values, in float, rounded once
+__device__ __forceinline__ uint32_t average_bf16x2(uint32_t a, uint32_t b) {
+  const float lo = 0.5f * (__uint_as_float(a << 16) + __uint_as_float(b << 16));
+  const float hi = 0.5f * (__uint_as_float(a & 0xffff0000u) + __uint_as_float(b & 0xffff0000u));
+  return pack_bf16(lo, hi);
+}
+__device__ __forceinline__ uint4 average_bf16x8(uint4 a, uint4 b) {
+  return make_uint4(average_bf16x2(a.x, b.x), average_bf16x2(a.y, b.y), average_bf16x2(a.z, b.z),
+                    average_bf16x2(a.w, b.w));
+}
+
 // acc *= alpha for an MFMA accumulator tile.  This file is compiled with the MFMA results
 // in ordinary vector registers (-mllvm -amdgpu-mfma-vgpr-form=1): with two waves per SIMD
 // a wave owns 256 registers in total, the accumulators need only 64 of them, and keeping

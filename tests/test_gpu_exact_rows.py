@@ -69,6 +69,21 @@ def test_list_of_every_row(env, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+def test_merge_into_an_output_off_eight_bytes(env, d):
+    """Several key ranges, merged into a tensor that starts two bytes into its storage: the bits of the aligned one, nothing beside it."""
+    torch, binding, dev = env
+    N, rows, rng = 9000, 300, np.random.default_rng(d)
+    tq, tk, tv = (U.to_device(list(U.random_bits(rng, (2, N, d), 1.5, True)), torch, dev) for _ in range(3))
+    ref = binding.recompute_rows(tq, tk, tv, 1, 1, N, torch.zeros_like(tq), 7, rows)
+    storage = torch.full((tq.numel() + 8,), 3.0, dtype=tq.dtype, device=dev)
+    out = storage[1:1 + tq.numel()].view(tq.shape)
+    out.zero_()
+    binding.recompute_rows(tq, tk, tv, 1, 1, N, out, 7, rows)
+    assert out.data_ptr() % 8 == 2 and torch.equal(out, ref)
+    assert bool((storage[:1] == 3.0).all()) and bool((storage[1 + tq.numel():] == 3.0).all())
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("heads,T,b", [(2, 5, 33), (40, 26, 65), (3, 2, 700)])
 def test_sink_pass(env, heads, T, b, d):
     torch, binding, dev = env
