@@ -172,6 +172,16 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
   unsigned goff[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) goff[r] = (unsigned)((RPI * W2 * r + st_key) * ROW_BYTES + st_lc * 16);
+  // Biased modes, whose rows lie far apart: the same in 64 bits.  Formed anew for every tile, the products with the row distance were 93
+  // instructions of the one wave on a SIMD, 12 of them at a quarter of the rate.
+  long long far[NR];
+  if (BIAS != 0) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      far[r] = (RPI * W2 * r + st_key) * rs * ROW_BYTES + st_lc * 16;
+      asm volatile("" : "+v"(far[r]));
+    }
+  }
   const unsigned lds_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)smem;
   auto issue_tile = [&](int t) __attribute__((always_inline)) {  // into slot t & 3
     const unsigned kb = lds_base + (t & (NSLOT - 1)) * TILE_BYTES;
@@ -184,14 +194,13 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
       if (ragged) off = (unsigned)(min(RPI * W2 * r + st_key, last_left - 1) * ROW_BYTES + st_lc * 16);
       // wave-uniform LDS byte address in M0; lane lands at + 16 * lane
       const unsigned dst = __builtin_amdgcn_readfirstlane(kb + (RPI * W2 * r + RPI * wave) * ROW_BYTES);
-      if (BIAS != 0) {  // rows far apart: 64-bit lane addresses
-        int row = RPI * W2 * r + st_key;
-        if (ragged) row = min(row, last_left - 1);
-        const long long far = row * rs * ROW_BYTES + st_lc * 16;
-        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(ksrc + far), "s"(dst) : "memory", "m0");
+      if (BIAS != 0) {
+        long long at = far[r];
+        if (ragged) at = min(RPI * W2 * r + st_key, last_left - 1) * rs * ROW_BYTES + st_lc * 16;
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(ksrc + at), "s"(dst) : "memory", "m0");
         if (OUT_V) {
           const unsigned vdst = dst + V_OFF;
-          asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(vsrc + far), "s"(vdst) : "memory", "m0");
+          asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(vsrc + at), "s"(vdst) : "memory", "m0");
         }
         continue;
       }
@@ -819,7 +828,8 @@ hipError_t launch_flash2(FlashParams P, long long problems, hipStream_t st) {
   // four K slots always (the logits need them), four V slots when values are multiplied: 128 KB at d = 128
   constexpr int BT = tile_rows<D, OUT_V, Q2, BIAS>();
   constexpr int TILE_LDS = (OUT_V ? 2 : 1) * NSLOT * BT * D * 2;
-  constexpr int MAX_LDS = TILE_LDS + (BIAS != 0 ? (kMaxBiasedKeys + 64 + 32) * 4 : 0);
+  constexpr int MAX_LDS = TILE_LDS + (BIAS != 0 ? (kMaxBiasedKeys + 32) * 4 : 0);
+  static_assert(MAX_LDS <= 160 * 1024 && kMaxBiasedKeys % BT == 0, "a unit's LDS holds the tiles and the longest row of key terms");
   const int lds = TILE_LDS + (BIAS != 0 ? ((P.nk + BT - 1) / BT * BT + 32) * 4 : 0);
   if (lds > MAX_LDS) return hipErrorInvalidValue;
   const hipError_t ec = count_blocks(P, problems, W2 * ROWS);
@@ -928,12 +938,10 @@ hipError_t launch_l_update_flash2(const bf16_t* q, const bf16_t* aL, const float
   P.kb_scale = -LOG2E;
   const long long problems = (long long)dm.BH * dm.b;
   const int units = compute_units();
-  const bool short_products = temporal_product_short_blocks(D, problems, dm.T, units);
+  const bool short_products = temporal_product_short_blocks(D, y != nullptr, problems, dm.T, units);
   if (y != nullptr) {
     P.q = q; P.k = aL; P.v = y; P.outv = out; P.kbias = cL;
-    if constexpr (D == 64)
-      if (!short_products) return launch_flash2<D, false, true, 0, false, 2, 1>(P, problems, st);
-    return launch_flash2<D, false, true, 0, false, 1, 1>(P, problems, st);
+    return short_products ? launch_flash2<D, false, true, 0, false, 1, 1>(P, problems, st) : launch_flash2<D, false, true, 0, false, 2, 1>(P, problems, st);
   }
   if (lse_scratch == nullptr) return hipErrorInvalidValue;
   P.q = q; P.k = aL; P.lse = lse_scratch; P.kbias = cL;

@@ -46,13 +46,17 @@ constexpr bool update_short_blocks(int d, bool with_v, long long frames, int b, 
 }
 
 // Passes of the temporal factor over T frames.  Log-sum-exps: three short blocks to a unit or two long ones, at d = 128 level only in full
-// groups; products: as many at d = 64, at d = 128 two or one, and the short ones win (fitting sweep, 12 x 64 problems of 512 frames 207 / 218 us,
-// 8 x 100 of 300 110 / 150).
+// groups; products: as many at d = 64, at d = 128 two or one.  There the last sweep's pass takes long blocks where the rows are long (short /
+// long, us: 256 problems of 300 frames 29.3 / 36.7, 768 of 512 165 / 169, 512 of 2048 1343 / 1263, 400 of 3000 2150 / 1955), and the short
+// ones win the fitting sweep's second pass (12 x 64 of 512 207 / 218 with the log-sum-exps, 8 x 100 of 300 110 / 150).
+// (The one-tile kernel this pass ran on before took 158 and 1188 for 768 of 512 and 512 of 2048: up to 5 % less where rows fill blocks of 256
+// exactly, 5 .. 30 % more elsewhere.)
 constexpr bool temporal_lse_short_blocks(int d, long long problems, int T, int units) {
   return short_triples_faster(problems, T, units, d == 64 ? 0.92 : 1.04, 0.6, 0.4);
 }
-constexpr bool temporal_product_short_blocks(int d, long long problems, int T, int units) {
-  return d == 128 || short_triples_faster(problems, T, units, 0.92, 0.6, 0.4);
+constexpr bool temporal_product_short_blocks(int d, bool last, long long problems, int T, int units) {
+  if (d == 64) return short_triples_faster(problems, T, units, 0.92, 0.6, 0.4);
+  return !last || short_pairs_faster(problems, T, units, 1.10, 80.0);
 }
 
 // The backward at d = 128, all gradients: a unit holds two short blocks or one long one, both go in rounds.  Short / long, us: 130 frames of 300
