@@ -1,5 +1,6 @@
-"""R-updates of short frames: the kernel that takes a whole frame per workgroup, at the edges of its 32-row tiles, against the
-CPU oracle and against the streaming kernels (flash variant 1), which form the same sums in another order.
+"""R-updates of short frames: the kernel that takes a whole frame per workgroup, at the edges of its 32-row tiles and on both sides of its
+limits, against the CPU oracle and against the kernels of flash variant 0, which no such call takes by default and which form the same
+sums in another order.
 
 Tolerance: inputs, outputs and the softmax weights are bf16 (half an ulp is 2^-9 relative); alpha_L and y carry one rounding
 of every weight and one of the result, both random: sqrt(2) 2^-9 = 2.8e-3 in the relative norm at most.  Against the
@@ -44,9 +45,9 @@ def test_r_update_of_short_frames(env, b, d, with_v):
     call = lambda: [None if x is None else U.from_device(x) for x in
                     binding.r_update_lse(tq, tc, tk, tv if with_v else None, T, 1, b, s, 0.1)]
     aL, cL, y, lse = call()
-    binding.set_flash_variant(1)
+    binding.set_flash_variant(0)
     try:
-        streamed = call()
+        other = call()
     finally:
         binding.set_flash_variant(2)
     for h in range(2):
@@ -56,19 +57,19 @@ def test_r_update_of_short_frames(env, b, d, with_v):
         z = np.einsum("jid,jld->jil", q3 * s / c[:, :, None], k3)
         ref_lse = (np.log(np.exp(z - z.max(2, keepdims=True)).sum(2)) + z.max(2)).reshape(-1)
         assert U.rel_l2(aL[h], oaL.transpose(1, 0, 2).reshape(T * b, d)) <= 4e-3
-        assert U.rel_l2(aL[h], streamed[0][h]) <= 6e-3
+        assert U.rel_l2(aL[h], other[0][h]) <= 6e-3
         assert U.max_abs(cL[h], ocL.T.reshape(-1)) <= 2.0 ** -8
         assert U.max_abs(lse[h], ref_lse) <= 2.0 ** -8
         if with_v:
             assert U.rel_l2(y[h], np.matmul(R, v3).reshape(T * b, d)) <= 4e-3
-            assert U.rel_l2(y[h], streamed[2][h]) <= 6e-3
+            assert U.rel_l2(y[h], other[2][h]) <= 6e-3
 
 
 @pytest.mark.parametrize("b", [257, 319, 320, 321, 352, 353, 383, 384, 385])
 @pytest.mark.parametrize("with_v", [True, False])
-def test_r_update_in_blocks_of_128_rows(env, b, with_v):
-    """More frames of 257 .. 384 tokens than fill the card once: every frame against the streaming kernels, the first and the
-    last one against the oracle."""
+def test_r_update_of_many_frames_beyond_the_whole_frame_kernel(env, b, with_v):
+    """Frames of two to four query blocks of 128 rows of the streaming kernel, full ones and ragged ones: every frame against the
+    kernels of variant 0, the first and the last one against the oracle."""
     torch, binding, dev = env
     T, d, s = 65, 64, 0.125
     aR, K, V, cR = _inputs(T, b, d, b)
@@ -77,16 +78,16 @@ def test_r_update_in_blocks_of_128_rows(env, b, with_v):
     call = lambda: [None if x is None else U.from_device(x) for x in
                     binding.r_update_lse(tq, tc, tk, tv if with_v else None, T, 1, b, s, 0.1)]
     aL, cL, y, lse = call()
-    binding.set_flash_variant(1)
+    binding.set_flash_variant(0)
     try:
-        streamed = call()
+        other = call()
     finally:
         binding.set_flash_variant(2)
     for h in range(2):
         for j in range(T):
             rows = slice(j * b, (j + 1) * b)
-            assert U.rel_l2(aL[h][rows], streamed[0][h][rows]) <= 6e-3
-            assert not with_v or U.rel_l2(y[h][rows], streamed[2][h][rows]) <= 6e-3
+            assert U.rel_l2(aL[h][rows], other[0][h][rows]) <= 6e-3
+            assert not with_v or U.rel_l2(y[h][rows], other[2][h][rows]) <= 6e-3
             if j not in (0, T - 1):
                 continue
             c = np.maximum(cR[h][rows].astype(np.float64), 0.1)[None]
@@ -124,8 +125,8 @@ def test_many_frames_and_no_row_scale(env, d):
 @pytest.mark.parametrize("d,b,frames", [(64, 256, 512), (64, 260, 16), (64, 449, 256), (128, 161, 8), (128, 193, 300), (128, 1290, 256), (128, 1281, 16)])
 @pytest.mark.parametrize("with_v", [False, True])
 def test_query_blocks_of_the_streaming_kernel(env, d, b, frames, with_v):
-    """Updates take query blocks of 128 or of 256 rows by the size of the launch: the same two frames, repeated
-    as often as it takes to reach either, against the oracle (bounds as above), every repeat bit-identical."""
+    """Updates take query blocks of 128 or of 256 rows by the size of the launch (test_gpu_long_blocks.py drives the long ones): the same two
+    frames in launches from a few blocks to several rounds, against the oracle (bounds as above), every repeat bit-identical."""
     torch, binding, dev = env
     s = 1.0 / math.sqrt(d)
     aR, K, V, cR = _inputs(1, b, d, 11 * b + d)

@@ -107,13 +107,14 @@ def test_r_update_matches_oracle(env, T, Hs, Ws, d, dt, with_v, with_cr, mode):
             assert U.rel_l2(gy, ref_y) <= rel_tol and U.max_abs(gy, ref_y) <= abs_tol
 
 
-@pytest.fixture(params=["one-wave", "wave-pair", "two-pass"])
+@pytest.fixture(params=["streaming", "wave-pair", "two-pass"])
 def fused(request, env):
-    """The three forms of the bf16 MFMA R-update: one wave per SIMD with two query tiles (alpha_L, c_L and, with values,
-    y from one softmax); two waves per SIMD, alpha_L, c_L and y from one pass shared by a wave pair; two waves per
-    SIMD, a pass for alpha_L / c_L and a second one for y."""
+    """The three forms of the bf16 MFMA R-update: the streaming kernel (alpha_L, c_L and, with values, y from one softmax; launches as
+    small as the ones here take its blocks with one query tile per wave, the ones with two are driven by test_gpu_long_blocks.py); two
+    waves per SIMD, alpha_L, c_L and y from one pass shared by a wave pair; two waves per SIMD, a pass for alpha_L / c_L and a second one
+    for y."""
     binding = env[1]
-    binding.set_flash_variant(1 if request.param == "one-wave" else 0)
+    binding.set_flash_variant(1 if request.param == "streaming" else 0)
     binding.set_fused_apply(request.param != "two-pass")
     yield request.param
     binding.set_fused_apply(True)
@@ -188,8 +189,8 @@ def test_r_update_when_the_reference_max_moves_in_every_tile(env, d, fused, spik
     spikes with different strength: the kernels' reference maxima move in almost every tile, in the wave that
     produces the probabilities and in the one that adopts them, while the mass below the spikes still matters for
     many rows.  Spikes of 7 per tile raise the strongest rows' maxima by 2^8 per tile (the margin of the kernels
-    with two waves per SIMD), spikes of 72 by more than 2^56 (margin plus headroom of the kernel with one), spikes of 400 by more than
-    2^192, so that the weights of a sub-tile overflow before its reference has moved."""
+    with two waves per SIMD), spikes of 72 by more than 2^56 (several times the margin of the streaming kernel over a few tiles), spikes of
+    400 by more than 2^192, so that the weights of a sub-tile overflow before its reference has moved."""
     torch, binding, dev = env
     b = 600                                           # 10 key tiles, ragged; 5 query blocks of 128
     rng = np.random.default_rng(77 + d)
@@ -313,10 +314,11 @@ def test_l_update_matches_oracle(env, T, Hs, Ws, d, dt, final):
 
 
 # ------------------------------------------------------------------ first-frame recomputation
-@pytest.fixture(params=["two-tile", "one-tile"])
+@pytest.fixture(params=["streaming", "one-tile"])
 def first_frame_kernel(request, env):
-    """Exact attention of contiguous rows runs on the kernel with two query tiles per wave by default and on the
-    one-tile kernel when flash variant 0 is selected (bf16, d = 64 or 128; other cases take neither)."""
+    """Exact attention of contiguous rows runs on the streaming kernel by default (one query tile per wave in launches as small as the ones
+    here; test_gpu_long_blocks.py drives two) and on the one-tile kernel when flash variant 0 is selected (bf16, d = 64 or 128; other
+    cases take neither)."""
     binding = env[1]
     default = binding.get_flash_variant()
     binding.set_flash_variant(0 if request.param == "one-tile" else default)

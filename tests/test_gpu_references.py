@@ -51,6 +51,30 @@ def test_c_L_of_ordinary_rows(env, d, b, frames, with_v, deviation):
     assert rms(error) <= rms(bound)
 
 
+@pytest.mark.parametrize("deviation", [20.0, 40.0])
+@pytest.mark.parametrize("d,b,frames", [(64, 300, 130), (64, 1560, 2), (64, 1000, 64), (128, 200, 130), (128, 1560, 2), (128, 1100, 100)])
+@pytest.mark.parametrize("with_v", [False, True])
+def test_c_L_of_sharp_rows(env, d, b, frames, with_v, deviation):
+    """Rows of few heavy keys, whose references have headroom and move: every element within four times the rounding of these keys' t, up to 96
+    binary orders (67 in natural units) from the reference, and of the logits (log2(d) / 2 roundings), which move c_L by sum R |log R - c|
+    times as much."""
+    torch, binding, dev = env
+    rng = np.random.default_rng(b + d)
+    q, k = (synth.f32_to_bf16_bits((math.sqrt(deviation) * rng.standard_normal((frames * b, d))).astype(np.float32)) for _ in range(2))
+    tq, tk = (U.to_device([x], torch, dev) for x in (q, k))
+    s = 1.0 / math.sqrt(d)
+    _, cL, _ = binding.r_update(tq, None, tk, tk if with_v else None, frames, 1, b, s, 0.1)
+    cL = U.from_device(cL)[0].reshape(frames, b).astype(np.float64)
+    u = 2.0 ** -24
+    for j in (0, frames - 1):
+        z = U.to_f64(q)[j * b:(j + 1) * b] @ U.to_f64(k)[j * b:(j + 1) * b].T * s
+        log_R = z - z.max(1, keepdims=True)
+        log_R -= np.log(np.exp(log_R).sum(1, keepdims=True))
+        c = (np.exp(log_R) * log_R).sum(1)
+        spread = (np.exp(log_R) * np.abs(log_R - c[:, None])).sum(1)
+        assert np.all(np.abs(cL[j] - c) <= 4 * u * (67 + np.abs(c) + 0.5 * math.log2(d) * np.abs(z).max(1) * spread))
+
+
 @pytest.mark.parametrize("exponent", [-90, -110])
 @pytest.mark.parametrize("d", [64, 128])
 def test_values_near_the_bottom_of_the_range(env, d, exponent):

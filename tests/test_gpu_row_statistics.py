@@ -14,6 +14,7 @@ import pytest
 
 from paper_2601_22275_amd import synth
 from tests import util as U
+from tests.test_gpu_long_blocks import LONG_SPIKES
 
 pytestmark = pytest.mark.gpu
 
@@ -21,9 +22,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("common", [0.0, 300.0, 1000.0, 5000.0])
 @pytest.mark.parametrize("d,b,frames,with_v", [
     (64, 40, 3, True), (64, 40, 3, False), (128, 40, 3, True), (128, 40, 3, False),  # a whole frame per workgroup
-    (64, 300, 130, True), (64, 300, 130, False),                                     # 128 rows of one
-    (64, 500, 2, True), (64, 500, 2, False), (128, 500, 2, True),                    # two query tiles per wave
-    (128, 500, 2, False),                                                            # one query tile per wave
+    (64, 300, 130, True), (64, 300, 130, False),                                     # one query tile per wave
+    (64, 500, 2, True), (64, 500, 2, False), (128, 500, 2, True), (128, 500, 2, False),
+    *((d, *LONG_SPIKES[d, v], v) for d, v in LONG_SPIKES),                           # two query tiles per wave
 ])
 @pytest.mark.parametrize("spread", [0.3, 4.0])
 def test_large_common_part(d, b, frames, with_v, common, spread):
