@@ -46,11 +46,15 @@ constexpr int W2 = 4;             // waves per workgroup
 // lets grow; both carry the UNROUNDED p here, beside the rounded sum that the outputs are divided by.  And c_L = h / l - log2 l is a
 // difference of two numbers of the size of t at the keys that matter, so the reference belongs at the row's maximum: see
 // HEADROOM2.
-constexpr float STEP_MAX2 = 18446744073709551616.0f;  // 2^64: leaves the accumulators 2^47 of room at 2^17 keys
+constexpr float STEP_MAX2 = 18446744073709551616.0f;  // 2^64
+// Weights that large leave the accumulators 2^47 of room at 2^17 keys.  Sums above this one are rare (a row has grown by 2^32 and more since
+// its reference was set); they send a wave to look whether the sub-tile multiplies elements of 2^40 or more, and then its references move too.
+// (A limit of 2^64 alone overflows where values of 1e24 meet sharp rows; the look costs 252 frames of 1560 of deviation 20 / 30 1 / 5 %.)
+constexpr float STEP_LARGE2 = 4294967296.0f;  // 2^32
 // A reference is put at the row's maximum.  Only where attention is sharp it is put above it, by up to this much (log2 units), because
 // moving one passes the accumulators through ordinary registers and forms a sub-tile twice, and the maxima of such rows jump from
 // tile to tile (c_R raises logits up to tenfold): with first references and moves at the maximum itself 252 frames of 1560, d = 128, logits of
-// deviation 20 / 30 in natural units, take 394 / 513 us without values, with this headroom 347 / 362.  Sharp are rows whose first 32 logits
+// deviation 20 / 30 in natural units, take 394 / 513 us without values, with this headroom 351 / 369 (ordinary logits 340).  Sharp are rows whose first 32 logits
 // span more than 40 log2 units, and rows that have to move; the fp32 rounding of logits of that size costs c_L as much as the headroom does.
 // Every row 2^64 above its maximum instead cost c_L a digit: largest error for deviations 1 / 3 / 20, 2 x 1560 rows, d = 128: 1.9e-5 /
 // 3.5e-5 / 2.1e-5, now 1.3e-6 / 4.5e-6 / 8.4e-6; d = 64 2.0e-5 / 2.4e-5 / 1.9e-5, now 1.2e-6 / 4.9e-6 / 8.4e-6 (flash_kernel, at most 2^8
@@ -532,6 +536,25 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
     F2_FENCE();
   };
 
+  // Whether the sub-tile at byte offset `off` holds elements of 2^40 and more (infinities and NaN among them) in a tensor that is multiplied
+  auto large_elements = [&](int off) __attribute__((always_inline)) -> bool {
+    typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+    typedef __attribute__((address_space(3))) const u32x4* lds_u32x4_ptr;
+    typedef __attribute__((__vector_size__(2 * sizeof(uint16_t)))) uint16_t u16x2;
+    const unsigned at = lds_base + off + 16 * (threadIdx.x & 63);
+    u16x2 largest = {0, 0};
+#pragma unroll(TIGHT ? 2 : 4)
+    for (int i = 0; i < 32 * ROW_BYTES; i += 1024) {
+#pragma unroll
+      for (int x = 0; x < NX; ++x) {
+        const u32x4 w = *(lds_u32x4_ptr)(unsigned long long)(at + i + (x == XV && OUT_V ? V_OFF : 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) largest = __builtin_elementwise_max(largest, __builtin_bit_cast(u16x2, w[e] & 0x7fff7fffu));
+      }
+    }
+    return __any(max(largest[0], largest[1]) >= 0x5380);  // bf16 bits of 2^40
+  };
+
   // S_OFF / PV_OFF: byte offsets (slot and sub-tile) this step's logits and products read;
   // NS_OFF / NPV_OFF: the same for the step that follows (its first operands are requested here).
   auto step = [&](auto s_c, auto pv_c, auto ns_c, auto npv_c, f32x16 (&scur)[Q2], f32x16 (&snext)[Q2], bf16x8 (&pbprev)[Q2][2],
@@ -577,7 +600,10 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
 #pragma unroll
     for (int qt = 0; qt < Q2; ++qt)
       if (!LSE_ONLY) asm volatile("" : "+v"(pbcur[qt][0]), "+v"(pbcur[qt][1]));
-    if (BIAS != 2 && __any(ltstep[0] > STEP_MAX2 || ltstep[Q2 - 1] > STEP_MAX2)) redo(NPV_OFF, pbcur, keys_left, sub);
+    constexpr float LIMIT = LSE_ONLY ? STEP_MAX2 : STEP_LARGE2;
+    if (BIAS != 2 && __any(ltstep[0] > LIMIT || ltstep[Q2 - 1] > LIMIT)) {
+      if (LSE_ONLY || __any(ltstep[0] > STEP_MAX2 || ltstep[Q2 - 1] > STEP_MAX2) || large_elements(NPV_OFF)) redo(NPV_OFF, pbcur, keys_left, sub);
+    }
 #pragma unroll
     for (int qt = 0; qt < Q2; ++qt) {
       ltil[qt] += ltstep[qt];
@@ -617,8 +643,8 @@ __device__ __forceinline__ void flash2_block(const FlashParams& P, const int bid
           head[qt] = first_headroom(sA[qt], sc[qt], msc[qt]);
           sharp = sharp || head[qt] >= HEADROOM2;
         }
-        // in sharp rows the first 32 logits say little of the rest: the maxima of all keys that are here (deviation 30: moves
-        // from 462 to 362 us where 340 need none)
+        // in sharp rows the first 32 logits say little of the rest: the maxima of all keys that are here (252 frames of 1560, d = 128, deviation
+        // 30: 462 -> 362 us)
         if (__any(sharp)) {
           const int subs = min(2, ntiles) * (BT / 32);
 #pragma unroll 1

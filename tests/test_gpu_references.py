@@ -75,16 +75,16 @@ def test_c_L_of_sharp_rows(env, d, b, frames, with_v, deviation):
         assert np.all(np.abs(cL[j] - c) <= 4 * u * (67 + np.abs(c) + 0.5 * math.log2(d) * np.abs(z).max(1) * spread))
 
 
-@pytest.mark.parametrize("exponent", [-90, -110])
+@pytest.mark.parametrize("exponent,deviation", [(-90, 2.0), (-110, 2.0), (-60, 40.0), (77, 40.0), (95, 2.0)])
 @pytest.mark.parametrize("d", [64, 128])
-def test_values_near_the_bottom_of_the_range(env, d, exponent):
-    """Values of the size 2^exponent through every pass that multiplies values: the same relative error as at size one (weights and
-    result rounded to bf16, sqrt(2) 2^-9; 4e-3 allowed)."""
+def test_values_near_the_ends_of_the_range(env, d, exponent, deviation):
+    """Values of the size 2^exponent through every pass that multiplies values, in ordinary rows and in sharp ones, whose weights grow to
+    many orders above one: the same relative error as at size one (weights and result rounded to bf16, sqrt(2) 2^-9; 4e-3 allowed)."""
     torch, binding, dev = env
     rng = np.random.default_rng(d)
     T, b, s = 5, 400, 1.0 / math.sqrt(d)
     N = T * b
-    q, k, v = (U.random_bits(rng, (N, d), 1.5, True) for _ in range(3))
+    q, k, v = (U.random_bits(rng, (N, d), scale, True) for scale in (math.sqrt(deviation), math.sqrt(deviation), 1.5))
     v = synth.f32_to_bf16_bits((U.to_f64(v) * 2.0 ** exponent).astype(np.float32))
     tq, tk, tv = (U.to_device([x], torch, dev) for x in (q, k, v))
     q, k, v = (U.to_f64(x) for x in (q, k, v))
