@@ -20,7 +20,7 @@ constexpr double work_per_unit(long long problems, long long n, int rows, int un
 // launch is long and the device's power is the limit.  A unit works through its blocks in groups as large as it holds, so the two
 // launches' times follow from the blocks per unit, with a group's time measured against that of the long blocks' full group.  The
 // constants are chosen for the least loss against the better of the two over 129 .. 470 launches a pass (8 .. 4000 problems x 129 .. 4000
-// rows, random inputs with logits of deviation 3 and video-like ones).  The rule's mean loss is 0.0 .. 0.4 %, its largest 1 .. 8 %, where
+// rows, random inputs with logits of deviation 3 and video-like ones).  The rule's mean loss is 0.0 .. 0.4 %, its largest 1 .. 10 %, where
 // one or two blocks to a unit are near each other.
 //
 // A unit holds two short blocks or one long one.  A pair of short ones takes `a - b / n` of a long one's time, n the length of the loop (a
